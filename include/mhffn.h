@@ -123,7 +123,9 @@ typedef struct {
  * prefill) the blocks of eq:flash-ffn-loop are shared out over several
  * workgroups per token tile and their fp32 partial outputs, n_split * N *
  * d_model * 4 bytes (a few output-sized buffers, never d_ff-sized ones), pass
- * through the workspace; ask this function rather than relying on the rule.  For MHFFN_OP_BACKWARD it is the gating weights R and
+ * through the workspace; ask this function rather than relying on the rule.
+ * For fp32 the forward's workspace is optional: mhffn_forward shares the blocks out as far as
+ * the bytes it is given allow, and runs without any.  For MHFFN_OP_BACKWARD it is the gating weights R and
  * their gradient as [H][E][N] fp32, the partial sums of dW_r, and, for the
  * neuron groups that would otherwise leave CUs idle in the last round of
  * workgroups, fp32 partial weight gradients of a few token segments (a multiple

@@ -128,8 +128,8 @@ size_t mhffn_workspace_bytes(const mhffn_desc* desc, int op) {
   if (check_desc(desc, &p) != MHFFN_OK) return 0;
   switch (op) {
     case MHFFN_OP_FORWARD:
-      if (desc->dtype != MHFFN_BF16 || check_fused_shape(desc, p) != MHFFN_OK) return 0;
-      return mhffn::fwd_bf16_workspace_bytes(p);
+      if (check_fused_shape(desc, p) != MHFFN_OK) return 0;
+      return desc->dtype == MHFFN_BF16 ? mhffn::fwd_bf16_workspace_bytes(p) : mhffn::fwd_f32_workspace_bytes(p);
     case MHFFN_OP_BACKWARD:
       if (check_fused_shape(desc, p, true) != MHFFN_OK) return 0;
       return mhffn::bwd_workspace_bytes(p, desc->dtype);
@@ -179,11 +179,21 @@ int forward_impl(const mhffn_desc* desc, const void* X, const void* W_gate, cons
       rc = check_workspace(need, workspace, workspace_bytes);
       if (rc) return rc;
     }
+  } else if (static_scratch) {
+    workspace_bytes = 0;   // fp32 needs none: it takes what fits
+    if (mhffn::fwd_f32_workspace_bytes(p)) {
+      rc = static_scratch_address(&workspace);
+      if (rc) return rc;
+      workspace_bytes = MHFFN_STATIC_SCRATCH_BYTES;
+    }
+  } else if (!aligned16(workspace)) {
+    workspace = nullptr;
   }
   const int e = (desc->dtype == MHFFN_BF16)
                     ? mhffn::launch_fwd_bf16(p, X, W_gate, W_up, W_down, route, Y, workspace,
                                              hip_stream)
-                    : mhffn::launch_fwd_f32(p, X, W_gate, W_up, W_down, route, Y, hip_stream);
+                    : mhffn::launch_fwd_f32(p, X, W_gate, W_up, W_down, route, Y, workspace,
+                                            workspace_bytes, hip_stream);
   return e == 0 ? MHFFN_OK : MHFFN_ERR_LAUNCH;
 }
 }  // namespace

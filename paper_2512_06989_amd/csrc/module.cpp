@@ -19,7 +19,9 @@ Problem inner(const Problem& p) {
   return q;
 }
 
-size_t fused_fwd_ws(const Problem& p, int dtype) { return dtype == 1 ? fwd_bf16_workspace_bytes(inner(p)) : 0; }
+size_t fused_fwd_ws(const Problem& p, int dtype) { 
+  return dtype == 1 ? fwd_bf16_workspace_bytes(inner(p)) : fwd_f32_workspace_bytes(inner(p));
+}
 
 // scratch of the projection products of one pass (they run one after the other and share it)
 size_t gemm_ws(const Problem& p, int dtype, bool backward) {
@@ -77,7 +79,7 @@ int launch_module_forward(const Problem& p, int dtype, const void* X, const void
   int e = product_nn(dtype, X, p.ldx, W_in, dm, Q, dm, p.N, dm, dm, gws, stream);
   if (e) return e;
   e = dtype == 1 ? launch_fwd_bf16(q, Q, Wg, Wu, Wd, Wr, S, ws, stream)
-                 : launch_fwd_f32(q, Q, Wg, Wu, Wd, Wr, S, stream);
+                 : launch_fwd_f32(q, Q, Wg, Wu, Wd, Wr, S, ws, fused_fwd_ws(p, dtype), stream);
   if (e) return e;
   // O[l][j] = sum_i S[l][i] W_out[i][j]
   return product_nn(dtype, S, dm, W_out, dm, O, p.ldy, p.N, dm, dm, gws, stream);
