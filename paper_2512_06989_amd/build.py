@@ -16,7 +16,7 @@ CALIB_LIB = os.path.join(HERE, "libmhffn_calib.so")   # calibration kernels of t
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 SOURCES = ["api.cpp", "module.cpp", "fwd_bf16.hip", "fwd_f32.hip", "bwd.hip", "bwd_f32.hip",
-           "unfused.hip", "gemm_bf16.hip"]
+           "bwd_finish.hip", "unfused.hip", "gemm_bf16.hip"]
 # Packed-fp32 VALU forms are switched off for all device code.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

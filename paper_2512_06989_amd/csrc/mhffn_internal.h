@@ -53,6 +53,20 @@ int launch_bwd_f32(const Problem& p, const void* X, const void* Wg, const void* 
                    const void* Wd, const void* route, const void* dY, void* dX, void* dWg,
                    void* dWu, void* dWd, void* d_route, void* ws, void* stream);
 
+// Last step of a token-major backward that shared its sub-networks out (bwd_finish.hip)
+struct BwdFinish {
+  const float* P;      // [shares][N][H*dh] partial dX
+  const float* R;      // [H][E][N] gating weights
+  float* DP;           // [H][E][N] dr_e in, dp_e out (params mode)
+  const float* Zinv;   // [H][N] 1 / (Z + eps) (params mode)
+  const void* Wr;      // [H][dh][E], storage type (params mode)
+  void* dX;            // may be NULL
+  int64_t N, ldx;
+  int H, dh, E, shares;
+  bool params;
+};
+int launch_bwd_tok_finish(int dtype, const BwdFinish& a, void* stream);
+
 // ---- unfused baseline ------------------------------------------------------
 size_t unfused_workspace_bytes(const Problem& p, int dtype, bool backward);
 int launch_unfused(const Problem& p, int dtype, const void* X, const void* Wg,
