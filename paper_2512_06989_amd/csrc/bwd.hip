@@ -14,6 +14,13 @@
 //         dX^T += W_r dp^T                                 (MFMA)
 //       R and dp are left in the workspace as [H][E][N] fp32 for the other
 //       kernels (E values per token and head, not d_ff values).
+//       With few tokens the sub-networks of a token block are shared out over several
+//       workgroups; the derivative and the sum of the partial dX then run in
+//       bwd_finish.hip.  1536 tokens, H = 16, E = 22, d_e = 384 (96 blocks on 256 CUs):
+//       0.489 ms as one workgroup per block, 0.30 + 0.01 ms as two.  What a workgroup does
+//       before and after its steps is 30 us of 450 at the 1.3B shape (it was 60 with a
+//       device-wide fence, two gating passes and a load behind every store of dp: 1.80 ->
+//       1.67 ms for the kernel).
 //   bwd_wgt16_kernel (appendix algorithm "Backward (dK,dU,dV)")
 //       one wave = 16 neurons of one head, K/U/V rows resident in registers as
 //       MFMA operands, loop over all tokens:
@@ -101,6 +108,11 @@ struct BwdArgs {
   // others share the tokens out over `wsplit` workgroups each and leave fp32 partials
   // [wsplit][3][8 * (gpx - full_px) groups][128 rows][128]
   int gpx, full_px, n_groups;
+  // token-major kernel with the sub-networks of a token block shared out over `shares`
+  // workgroups (few tokens): partial dX [shares][N][H*dh] fp32 and 1 / (Z + eps) [H][N]
+  float* XPws;
+  float* Zws;
+  int shares, subs_per_share;
   int64_t N, ldx, ldy, n_tiles, n_items;
   int H, E, de, dh, route_mode, n_split;
   float eps;
@@ -115,6 +127,7 @@ constexpr int tok_stage_bytes(int dh) { return 3 * 32 * dh * 2; }  // K, U, V ti
 // per thread), by direct global -> LDS loads into three stages, requested two steps ahead:
 // no staging registers, no LDS stores, and the step ends on a counted wait and a bare barrier.
 constexpr int tok_stages(bool dma) { return dma ? 3 : 2; }
+constexpr int kTokMaxSub = 96;   // sub-networks per head (d_h = 256: 64)
 
 // PHASED (with DMA): the two waves of a SIMD run half a step apart.  A step is two halves,
 // the gate/up/dA products (MFMA only) and the activation arithmetic plus the dX products
@@ -150,8 +163,10 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
   const int r = lane & 31, g = lane >> 5;
   const int64_t item = xcd_work_item(blockIdx.x, a.n_items);
   if (item >= a.n_items) return;
-  const int h = (int)(item / a.n_tiles);
-  const int64_t tile_tok0 = (item % a.n_tiles) * BM;
+  const int share = (int)(item % a.shares);       // the shares of a token block sit next to each other
+  const int64_t ht = item / a.shares;
+  const int h = (int)(ht / a.n_tiles);
+  const int64_t tile_tok0 = (ht % a.n_tiles) * BM;
   const int wtok = wave * 32 * TB;
   const int E = a.E;
   const int64_t N = a.N;
@@ -159,8 +174,10 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
   float* DPh = a.DPws + (size_t)h * E * N;
 
   const int tiles_per_sub = a.de / 32;
-  const int T = E * tiles_per_sub;
-  const size_t head_off = (size_t)h * E * a.de * DH;
+  const int e_begin = share * a.subs_per_share, e_end = min(E, e_begin + a.subs_per_share);
+  const int T = (e_end - e_begin) * tiles_per_sub;   // this workgroup's tiles
+  float* DRw = DRs + e_begin * BM;                   // dr of its sub-networks
+  const size_t head_off = ((size_t)h * E + e_begin) * a.de * DH;
   const uint16_t* Kh = a.Wg + head_off;
   const uint16_t* Uh = a.Wu + head_off;
   const uint16_t* Vh = a.Wd + head_off;
@@ -195,6 +212,35 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
   // starts from the first)
   unsigned char* scratch = stage_base + (DMA ? 2 * kTokStageBytes : 0);
 
+  // W_r of the head, 16 bytes per thread and round, requested ahead of everything else
+  constexpr int kWrRounds = (DH * (DH == 256 ? 64 : kTokMaxSub) / 8 + THREADS - 1) / THREADS;
+  u32x4 wr[kWrRounds];
+  const uint16_t* Wr = reinterpret_cast<const uint16_t*>(a.route) + (size_t)h * DH * E;
+  auto load_wr = [&]() {
+#pragma unroll
+    for (int i = 0; i < kWrRounds; ++i) {
+      const int c = tid + THREADS * i;
+      wr[i] = u32x4{0, 0, 0, 0};
+      if (c < DH * E / 8) wr[i] = *reinterpret_cast<const u32x4*>(Wr + 8 * c);
+    }
+  };
+  // element (j, e) of what load_wr fetched goes to LDS byte at(j, e)
+  auto store_wr = [&](unsigned char* dst, auto at) {
+#pragma unroll
+    for (int i = 0; i < kWrRounds; ++i) {
+      const int c = tid + THREADS * i;
+      if (c < DH * E / 8) {
+        int j = (8 * c) / E, e = 8 * c - j * E;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          *reinterpret_cast<uint16_t*>(dst + at(j, e)) = (uint16_t)(wr[i][k >> 1] >> (16 * (k & 1)));
+          if (++e == E) { e = 0; ++j; }
+        }
+      }
+    }
+  };
+  if (a.route_mode == 0) load_wr();
+
   bf16x8 q[TB][KS], dy[TB][KS];
   int64_t tok[TB];
   bool valid[TB];
@@ -225,64 +271,68 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
   for (int tb = 0; tb < TB; ++tb) inv[tb] = 0.f;
   if (a.route_mode == 0) {
     const int EB = (E + 31) >> 5;
-    // W_r^T as [32*EB][DH] bf16, swizzled rows
-    const uint16_t* Wr = reinterpret_cast<const uint16_t*>(a.route) + (size_t)h * DH * E;
-    for (int idx = tid; idx < DH * E; idx += THREADS) {
-      const int j = idx / E, e = idx - j * E;
-      *reinterpret_cast<uint16_t*>(scratch + btile_off<DH>(e, j >> 3) + (j & 7) * 2) = Wr[idx];
-    }
-    for (int idx = tid; idx < (32 * EB - E) * DH; idx += THREADS) {
-      const int e = E + idx / DH, j = idx % DH;
-      *reinterpret_cast<uint16_t*>(scratch + btile_off<DH>(e, j >> 3) + (j & 7) * 2) = 0;
-    }
+    // W_r^T as [32*EB][DH] bf16, swizzled rows (rows E.. keep whatever the memory held: a row
+    // of the product depends on its own row of the operand only, and rows E.. are masked below)
+    store_wr(scratch, [&](int j, int e) { return btile_off<DH>(e, j >> 3) + (j & 7) * 2; });
     __syncthreads();
     float zsum[TB];
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) zsum[tb] = 0.f;
-    for (int pass = 0; pass < 2; ++pass) {
-      for (int eb = 0; eb < EB; ++eb) {
+    // sigmoid(p_e) to LDS, then r_e = sigmoid(p_e) / (Z + eps) in its place; every lane comes
+    // back to its own elements
+    for (int eb = 0; eb < EB; ++eb) {
 #pragma unroll
-        for (int tb = 0; tb < TB; ++tb) {
-          f32x16 acc = {0};
+      for (int tb = 0; tb < TB; ++tb) {
+        f32x16 acc = {0};
 #pragma unroll
-          for (int ks = 0; ks < KS; ++ks) {
-            const bf16x8 af = *reinterpret_cast<const bf16x8*>(scratch + btile_off<DH>(32 * eb + r, 2 * ks + g));
-            acc = mfma32(af, q[tb][ks], acc);
-          }
+        for (int ks = 0; ks < KS; ++ks) {
+          const bf16x8 af = *reinterpret_cast<const bf16x8*>(scratch + btile_off<DH>(32 * eb + r, 2 * ks + g));
+          acc = mfma32(af, q[tb][ks], acc);
+        }
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int e = 32 * eb + 8 * (v / 4) + 4 * g + (v % 4);
-            const float s = (e < E) ? sigmoid_fast(acc[v]) : 0.f;
-            if (pass == 0) {
-              zsum[tb] += s;
-            } else if (e < E) {
-              const float rv = s * inv[tb];
-              if (valid[tb]) Rh[(size_t)e * N + tok[tb]] = rv;
-              DRs[e * BM + wtok + 32 * tb + r] = rv;   // until sub-network e has been swept
-            }
-          }
+        for (int v = 0; v < 16; ++v) {
+          const int e = 32 * eb + 8 * (v / 4) + 4 * g + (v % 4);
+          const float s = (e < E) ? sigmoid_fast(acc[v]) : 0.f;
+          zsum[tb] += s;
+          if (e < E) DRs[e * BM + wtok + 32 * tb + r] = s;
         }
       }
-      if (pass == 0) {
+    }
+    if constexpr (DMA) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), ahead of the stores of R
 #pragma unroll
-        for (int tb = 0; tb < TB; ++tb) {
-          const float z = zsum[tb] + __shfl_xor(zsum[tb], 32);
-          inv[tb] = 1.0f / (z + a.eps);
+    for (int tb = 0; tb < TB; ++tb) {
+      const float z = zsum[tb] + __shfl_xor(zsum[tb], 32);
+      inv[tb] = 1.0f / (z + a.eps);
+      for (int eb = 0; eb < EB; ++eb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int e = 32 * eb + 8 * (v / 4) + 4 * g + (v % 4);
+          if (e < E) {
+            const float rv = DRs[e * BM + wtok + 32 * tb + r] * inv[tb];
+            DRs[e * BM + wtok + 32 * tb + r] = rv;   // until sub-network e has been swept
+            if (valid[tb] && e >= e_begin && e < e_end) Rh[(size_t)e * N + tok[tb]] = rv;
+          }
         }
-      }
     }
   } else {
     const float* R = reinterpret_cast<const float*>(a.route);
+#pragma unroll 4
     for (int idx = tid; idx < BM * E; idx += THREADS) {
       const int tl = idx / E, e = idx - tl * E;
       const int64_t t = tile_tok0 + tl;
-      const float rv = (t < N) ? R[((size_t)t * a.H + h) * E + e] : 0.f;
-      if (t < N) Rh[(size_t)e * N + t] = rv;
-      DRs[e * BM + tl] = rv;
+      DRs[e * BM + tl] = (t < N) ? R[((size_t)t * a.H + h) * E + e] : 0.f;
+    }
+    __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0), ahead of the stores of R
+    __syncthreads();
+    for (int idx = tid; idx < BM * (e_end - e_begin); idx += THREADS) {   // along the tokens
+      const int e = e_begin + idx / BM, tl = idx % BM;
+      if (tile_tok0 + tl < N) Rh[(size_t)e * N + tile_tok0 + tl] = DRs[e * BM + tl];
     }
   }
-  __threadfence();   // R written above is read back (by this workgroup) in the epilogue
-  __syncthreads();   // (waits for every load in flight: direct staging has tiles 0 and 1 in place)
+  // R written above is read back in the epilogue, by the workgroup that wrote it: the barrier
+  // orders that (a device-wide fence here wrote back a whole L2 per wave).  Direct staging has
+  // tiles 0 and 1 in place: both branches waited for them.
+  __syncthreads();
 
   // ---- main loop -------------------------------------------------------------
   u32x4 kreg[DMA ? 1 : CH], ureg[DMA ? 1 : CH], vreg[DMA ? 1 : CH];
@@ -485,7 +535,7 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
     auto step = [&](int t, auto S_) __attribute__((always_inline)) {
       constexpr int S = decltype(S_)::value;
       const int e = t / tiles_per_sub;
-      if (t % tiles_per_sub == 0) rw[0] = DRs[e * BM + wtok + r];
+      if (t % tiles_per_sub == 0) rw[0] = DRw[e * BM + wtok + r];
       const int st_t = t % 3, st_n = (t + 1) % 3, st_r = (t + 2) % 3;
       if (t + 2 < T) row_products(sto0 + st_n * kTokStageBytes, std::integral_constant<int, 1 - S>{}, std::true_type{}, std::true_type{}, t + 2, st_r);
       else if (t + 1 < T) row_products(sto0 + st_n * kTokStageBytes, std::integral_constant<int, 1 - S>{}, std::true_type{}, std::false_type{}, 0, 0);
@@ -493,7 +543,7 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
       window_products(sto0 + st_t * kTokStageBytes, S_);
       if ((t + 1) % tiles_per_sub == 0) {
         const float dr = drp[0] + __shfl_xor(drp[0], 32);
-        if (g == 0) DRs[e * BM + wtok + r] = dr;
+        if (g == 0) DRw[e * BM + wtok + r] = dr;
         drp[0] = 0.f;
       }
       asm volatile("" ::: "memory");
@@ -629,7 +679,7 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
     auto step = [&](int t, auto FIRST_) {
       constexpr bool kFirst = decltype(FIRST_)::value;
       const int e = t / tiles_per_sub;
-      if (t % tiles_per_sub == 0) rw[0] = DRs[e * BM + wtok + r];
+      if (t % tiles_per_sub == 0) rw[0] = DRw[e * BM + wtok + r];
       const unsigned sto_cur = sto0 + stage * kTokStageBytes, sto_prev = sto0 + prev * kTokStageBytes;
       // ---- half A
       const bool request = !late && t >= 1 && t + 1 < T;
@@ -649,7 +699,7 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
       __builtin_amdgcn_s_setprio(0);
       if ((t + 1) % tiles_per_sub == 0) {
         const float dr = drp[0] + __shfl_xor(drp[0], 32);
-        if (g == 0) DRs[e * BM + wtok + r] = dr;
+        if (g == 0) DRw[e * BM + wtok + r] = dr;
         drp[0] = 0.f;
       }
       close_half(!late, true, sto_cur);
@@ -673,7 +723,7 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
     // included).
     if (t % tiles_per_sub == 0) {
 #pragma unroll
-      for (int tb = 0; tb < TB; ++tb) rw[tb] = DRs[e * BM + wtok + 32 * tb + r];
+      for (int tb = 0; tb < TB; ++tb) rw[tb] = DRw[e * BM + wtok + 32 * tb + r];
     }
     if constexpr (DMA) {
       // the stage that step t-1 retired (for the late waves; the early ones wait half a step)
@@ -773,7 +823,7 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
 #pragma unroll
       for (int tb = 0; tb < TB; ++tb) {
         const float dr = drp[tb] + __shfl_xor(drp[tb], 32);
-        if (g == 0) DRs[e * BM + wtok + 32 * tb + r] = dr;
+        if (g == 0) DRw[e * BM + wtok + 32 * tb + r] = dr;
         drp[tb] = 0.f;
       }
     }
@@ -798,32 +848,64 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
   }
 
   // ---- derivative through the gating weights ------------------------------------
-  if (a.route_mode == 0) {
+  const bool whole = a.shares == 1;
+  if (!whole && a.route_mode == 0) {
+    // a share leaves its dr_e; the sum over all sub-networks is taken by bwd_finish.hip
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb)
+      if (valid[tb]) {
+        for (int e = e_begin + g; e < e_end; e += 2) DPh[(size_t)e * N + tok[tb]] = DRs[e * BM + wtok + 32 * tb + r];
+        if (share == 0 && g == 0) a.Zws[(size_t)h * N + tok[tb]] = inv[tb];
+      }
+  } else if (a.route_mode == 0) {
     // stage W_r[h] as rows j, columns e (zero padded to 32*EB), for the A operand
     const int EB = (E + 31) >> 5;
     const int wr_stride = 64 * EB + 16;  // bytes per row; +16 keeps rows off the same banks
-    const uint16_t* Wr = reinterpret_cast<const uint16_t*>(a.route) + (size_t)h * DH * E;
-    for (int idx = tid; idx < DH * 32 * EB; idx += THREADS) {
-      const int j = idx / (32 * EB), e = idx - j * (32 * EB);
-      *reinterpret_cast<uint16_t*>(stage_base + j * wr_stride + e * 2) = (e < E) ? Wr[j * E + e] : 0;
+    load_wr();
+    // (weights r_e come back from the workspace in batches: a load behind every store of dp
+    // would be waited for alone)
+    constexpr int kBatch = 24;
+    float rr[TB][kBatch], dot[TB];
+    auto load_r = [&](int tb, int e0) {
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        const int e = e0 + 2 * i;
+        rr[tb][i] = (valid[tb] && e < E) ? Rh[(size_t)e * N + tok[tb]] : 0.f;
+      }
+    };
+    // lanes g = 0 and g = 1 of a token split the sub-networks between them
+#pragma unroll
+    for (int tb = 0; tb < TB; ++tb) {
+      const float* drcol = DRs + wtok + 32 * tb + r;
+      dot[tb] = 0.f;
+      for (int e0 = g; e0 < E; e0 += 2 * kBatch) {
+        load_r(tb, e0);
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i)
+          if (e0 + 2 * i < E) dot[tb] = fmaf(drcol[(e0 + 2 * i) * BM], rr[tb][i], dot[tb]);
+      }
+      dot[tb] += __shfl_xor(dot[tb], 32);
     }
+    store_wr(stage_base, [&](int j, int e) { return j * wr_stride + e * 2; });
+    const int epad = 32 * EB - E;   // zeros
+    for (int idx = tid; idx < DH * epad; idx += THREADS)
+      *reinterpret_cast<uint16_t*>(stage_base + (idx / epad) * wr_stride + (E + idx % epad) * 2) = 0;
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) {
       float* drcol = DRs + wtok + 32 * tb + r;
-      float dot = 0.f;
-      if (valid[tb])
-        for (int e = 0; e < E; ++e) dot = fmaf(drcol[e * BM], Rh[(size_t)e * N + tok[tb]], dot);
       const float zpe = 1.0f / inv[tb];
-      // lanes g = 0 and g = 1 of a token split the sub-networks between them
-      for (int e = g; e < E; e += 2) {
-        float dp = 0.f;
-        if (valid[tb]) {
-          const float rr = Rh[(size_t)e * N + tok[tb]];
-          const float s = rr * zpe;
-          dp = (drcol[e * BM] - dot) * inv[tb] * s * (1.0f - s);
-          DPh[(size_t)e * N + tok[tb]] = dp;
+      for (int e0 = g; e0 < E; e0 += 2 * kBatch) {
+        if (E > 2 * kBatch) load_r(tb, e0);   // else they are still there
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+          const int e = e0 + 2 * i;
+          if (e < E) {
+            const float s = rr[tb][i] * zpe;
+            const float dp = valid[tb] ? (drcol[e * BM] - dot[tb]) * inv[tb] * s * (1.0f - s) : 0.f;
+            if (valid[tb]) DPh[(size_t)e * N + tok[tb]] = dp;
+            drcol[e * BM] = dp;
+          }
         }
-        drcol[e * BM] = dp;
       }
     }
     __syncthreads();  // W_r staged; dp of both half-waves visible
@@ -854,7 +936,7 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) {
       if (valid[tb]) {
-        for (int e = g; e < E; e += 2) {
+        for (int e = e_begin + g; e < e_end; e += 2) {
           const float dr = DRs[e * BM + wtok + 32 * tb + r];
           if (dR) dR[((size_t)tok[tb] * a.H + h) * E + e] = dr;
         }
@@ -865,7 +947,15 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
   if (a.dX) {
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) {
-      if (valid[tb]) {
+      if (valid[tb] && !whole) {
+        float* dst = a.XPws + (((size_t)share * N + tok[tb]) * a.H + h) * DH + 4 * g;
+#pragma unroll
+        for (int jb = 0; jb < JB; ++jb)
+#pragma unroll
+          for (int vq = 0; vq < 4; ++vq)
+            *reinterpret_cast<f32x4*>(dst + 32 * jb + 8 * vq) =
+                f32x4{dXa[tb][jb][4 * vq], dXa[tb][jb][4 * vq + 1], dXa[tb][jb][4 * vq + 2], dXa[tb][jb][4 * vq + 3]};
+      } else if (valid[tb]) {
         uint16_t* dst = a.dX + tok[tb] * a.ldx + h * DH + 4 * g;
 #pragma unroll
         for (int jb = 0; jb < JB; ++jb) {
@@ -2315,7 +2405,7 @@ __global__ __launch_bounds__(kW2Threads) void bwd_wgt256_kernel(BwdArgs a) {
 // ---------------------------------------------------------------------------
 constexpr int kRouteSplit = 16;                 // workgroups per head
 constexpr int kRouteParts = kRouteSplit * 4;    // one partial per wave
-constexpr int kRouteMaxSub = 96;
+constexpr int kRouteMaxSub = kTokMaxSub;
 
 // D[j][e] += sum_tok q^T[j][tok] dp[tok][e] on the MFMA: the A operand is the
 // transposing LDS read of a [32 tok][d_h] tile of X, the B operand (contraction
@@ -2454,18 +2544,48 @@ bool tok_direct_staging(const Problem& p) {
   return (p.dh == 128 || p.dh == 256) && tok_lds_bytes(p, true) <= kLdsBytesPerWorkgroup;
 }
 
+// Shares of the sub-networks per token block: few tokens leave CUs without a workgroup, or the
+// last round of workgroups mostly empty.  Microseconds, measured: a step of 32 neurons takes
+// about 2.1 (d_h = 64, two workgroups on a CU: 1.1), a workgroup 20 (14) before and after its
+// steps; a share's partial dX is written and read back at about 4 TB/s; the launch that adds
+// them up costs about 10.
+struct TokShares { int shares, subs; };
+TokShares plan_tok_shares(const Problem& p) {
+  const int bm = tok_block_tokens(p.dh);
+  const int64_t items = ((p.N + bm - 1) / bm) * p.H;
+  const int slots = p.dh == 64 ? 512 : 256;      // workgroups that run at once
+  const double sub_us = (p.dh == 64 ? 1.1 : 2.1) * (p.de / 32), ends_us = p.dh == 64 ? 14.0 : 20.0;
+  const double part_us = 2.0 * p.N * p.H * p.dh * sizeof(float) / 4e6;
+  TokShares best{1, p.E};
+  double best_us = 0;
+  for (int s = 1; s <= 16 && s <= p.E; ++s) {
+    const int subs = (p.E + s - 1) / s;
+    if ((p.E + subs - 1) / subs != s) continue;  // s workgroups would not all have a sub-network
+    const double us = (double)((items * s + slots - 1) / slots) * (subs * sub_us + ends_us) + (s > 1 ? 10.0 + s * part_us : 0.0);
+    if (s == 1 || us < best_us) { best = {s, subs}; best_us = us; }
+  }
+  return best;
+}
+size_t tok_share_bytes(const Problem& p) {
+  const int s = plan_tok_shares(p).shares;
+  return s > 1 ? (size_t)s * p.N * p.H * p.dh * sizeof(float) : 0;
+}
+
 template <int DH, int TB, int NW, bool DMA = false, bool PHASED = false, bool PIPE = false>
 int launch_tok(const Problem& p, BwdArgs a, hipStream_t stream) {
   constexpr int BM = 32 * TB * NW;
   static_assert(BM == tok_block_tokens(DH), "bwd_bf16_lds_bytes assumes this block size");
   a.n_tiles = (p.N + BM - 1) / BM;
-  a.n_items = a.n_tiles * p.H;
+  a.n_items = a.n_tiles * p.H * a.shares;
   const size_t lds = tok_lds_bytes(p, DMA);
   if (hipError_t e = LdsLimit<&bwd_tok_kernel<DH, TB, NW, DMA, PHASED, PIPE>, kFullLds>::ensure(); e != hipSuccess)
     return (int)e;
   hipLaunchKernelGGL((bwd_tok_kernel<DH, TB, NW, DMA, PHASED, PIPE>), dim3((unsigned)xcd_grid_size(a.n_items)),
                      dim3(64 * NW), lds, stream, a);
-  return (int)hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.shares == 1) return (int)e;
+  const BwdFinish f{a.XPws, a.Rws, a.DPws, a.Zws, a.route, a.dX, p.N, p.ldx, p.H, p.dh, p.E, a.shares, p.route_mode == 0};
+  return launch_bwd_tok_finish(1, f, stream);
 }
 
 int launch_wgt16(const Problem& p, BwdArgs a, hipStream_t stream) {
@@ -2565,7 +2685,9 @@ size_t bwd_workspace_bytes(const Problem& p, int dtype) {
   if (p.N == 0) return 0;   // an empty batch only zero-fills the weight gradients
   const size_t nhe = align256((size_t)p.N * p.H * p.E * sizeof(float));
   const size_t wr = align256((size_t)p.H * kRouteParts * p.dh * p.E * sizeof(float));
-  return 2 * nhe + wr + wgt_split_bytes(p);
+  // (the token-major kernel's partials are used up before the weight-major one starts)
+  const size_t wp = wgt_split_bytes(p), xp = tok_share_bytes(p);
+  return 2 * nhe + wr + (xp ? align256((size_t)p.N * p.H * sizeof(float)) : 0) + (wp > xp ? wp : xp);
 }
 
 int launch_bwd(const Problem& p, int dtype, const void* X, const void* Wg, const void* Wu,
@@ -2620,8 +2742,14 @@ int launch_bwd(const Problem& p, int dtype, const void* X, const void* Wg, const
   a.Rws = reinterpret_cast<float*>(static_cast<unsigned char*>(ws));
   a.DPws = reinterpret_cast<float*>(static_cast<unsigned char*>(ws) + nhe);
   a.WRws = reinterpret_cast<float*>(static_cast<unsigned char*>(ws) + 2 * nhe);
-  a.WPws = reinterpret_cast<float*>(static_cast<unsigned char*>(ws) + 2 * nhe +
-                                    align256((size_t)p.H * kRouteParts * p.dh * p.E * sizeof(float)));
+  unsigned char* rest = static_cast<unsigned char*>(ws) + 2 * nhe +
+                        align256((size_t)p.H * kRouteParts * p.dh * p.E * sizeof(float));
+  const TokShares ts = plan_tok_shares(p);
+  a.shares = ts.shares;
+  a.subs_per_share = ts.subs;
+  a.Zws = reinterpret_cast<float*>(rest);
+  if (ts.shares > 1) rest += align256((size_t)p.N * p.H * sizeof(float));
+  a.XPws = a.WPws = reinterpret_cast<float*>(rest);
   a.wsplit = 1;
   a.blocks_per_seg = (p.N + 31) / 32;
   a.gpx = 0; a.full_px = 0; a.n_groups = 0;

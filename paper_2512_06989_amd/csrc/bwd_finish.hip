@@ -5,7 +5,8 @@
 //   dX   = sum_shares partial + dp W_r^T
 // A wave takes 16 tokens of one head.  The lane group gq of a token walks the sub-networks
 // 4 k + gq, which is how the fp32 product dp W_r^T (f32_tiles.h) wants its operand, so nothing
-// passes through LDS.  Bound: reading the partials.
+// passes through LDS.  Bound: reading the partials (two shares of 1536 x 2048: 10 us with the
+// rest of the call's traffic in L2, 3.8 TB/s; a quad of one share at a time took twice that).
 #include "f32_tiles.h"
 #include "mhffn_internal.h"
 
@@ -35,21 +36,28 @@ __global__ __launch_bounds__(256) void bwd_tok_finish_kernel(BwdFinish a) {
 
   f32x4 acc[JG][4];
   if (a.dX) {
+    // (all quads of a share in flight at once: there are few waves, and this is what they wait for)
     const size_t stride = (size_t)a.N * a.H * dh;
-    const float* src = a.P + ((size_t)t * a.H + h) * dh;
+    const float* src = a.P + ((size_t)t * a.H + h) * dh + 16 * gq;
+    f32x4 sum[JG][4];   // [J][v]
 #pragma unroll
     for (int J = 0; J < JG; ++J)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int col = 64 * J + 16 * gq + 4 * v;
-        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-        if (col < dh) {
-#pragma unroll 4
-          for (int s = 0; s < a.shares; ++s) sum += *reinterpret_cast<const f32x4*>(src + s * stride + col);
-        }
+      for (int v = 0; v < 4; ++v) sum[J][v] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+    for (int s = 0; s < a.shares; ++s, src += stride) {
 #pragma unroll
-        for (int n = 0; n < 4; ++n) acc[J][n][v] = sum[n];
-      }
+      for (int J = 0; J < JG; ++J)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (64 * J + 16 * gq + 4 * v < dh) sum[J][v] += *reinterpret_cast<const f32x4*>(src + 64 * J + 4 * v);
+    }
+#pragma unroll
+    for (int J = 0; J < JG; ++J)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int n = 0; n < 4; ++n) acc[J][n][v] = sum[J][v][n];
   }
   if (a.params) {
     const float* R = a.R + (size_t)h * E * a.N + t;
