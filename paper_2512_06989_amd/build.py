@@ -12,6 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmhffn.so")
+HOST_LIB = os.path.join(HERE, "_host.so")             # argument marshalling (csrc/binding.cpp)
 CALIB_LIB = os.path.join(HERE, "libmhffn_calib.so")   # calibration kernels of the bench
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
@@ -41,12 +42,29 @@ def _compile(src):
     return obj, err
 
 
+def _compile_binding():
+    """csrc/binding.cpp with the host compiler, against the headers of the installed torch."""
+    import sysconfig
+    from torch.utils import cpp_extension
+    obj = os.path.join(OBJDIR, "binding.o")
+    rocm = os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include")
+    inc = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"], rocm]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           *["-I" + d for d in inc], "-c", os.path.join(CSRC, "binding.cpp"), "-o", obj]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on binding.cpp:\n%s" % r.stderr)
+    return obj
+
+
 def build(force: bool = True, verbose: bool = False) -> str:
-    if not force and os.path.exists(LIB) and os.path.getmtime(LIB) >= _deps_mtime():
+    if not force and all(os.path.exists(f) and os.path.getmtime(f) >= _deps_mtime() for f in (LIB, HOST_LIB)):
         return LIB
     os.makedirs(OBJDIR, exist_ok=True)
-    with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with concurrent.futures.ThreadPoolExecutor(max_workers=8) as ex:
+        binding = ex.submit(_compile_binding)
         results = list(ex.map(_compile, SOURCES))
+        binding_obj = binding.result()
     if verbose:
         for _, err in results:
             if err.strip():
@@ -55,6 +73,13 @@ def build(force: bool = True, verbose: bool = False) -> str:
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp,
                            *[o for o, _ in results]])
     os.replace(tmp, LIB)
+    # (torch's own libraries are in the process before this one is imported: no path to them)
+    from torch.utils import cpp_extension
+    tmp = HOST_LIB + ".tmp.%d" % os.getpid()
+    subprocess.check_call(["g++", "-shared", "-fPIC", "-o", tmp, binding_obj, "-L" + HERE, "-l:libmhffn.so",
+                           "-Wl,-rpath,$ORIGIN", *["-L" + d for d in cpp_extension.library_paths()],
+                           "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"])
+    os.replace(tmp, HOST_LIB)
     # the bench's calibration kernels: a library of their own, never loaded by the binding
     obj, _ = _compile("calib.hip")
     tmp = CALIB_LIB + ".tmp.%d" % os.getpid()

@@ -2,7 +2,9 @@
 
 Argument marshalling only: every step of the operation runs in the HIP kernels
 of the library.  PyTorch is used for device memory and the current stream.
-There is no fallback: if the library is missing or a call fails, this raises."""
+The calls of a serving or training loop are marshalled in native code (`_host.so`, built
+from csrc/binding.cpp); the checks here then say what is wrong with arguments it refuses.
+There is no fallback: if a library is missing or a call fails, this raises."""
 import ctypes
 import os
 
@@ -10,6 +12,7 @@ import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libmhffn.so")
+HOST_PATH = os.path.join(HERE, "_host.so")
 
 OK = 0
 F32, BF16 = 0, 1
@@ -44,7 +47,7 @@ def load():
     global _lib
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
+    if not (os.path.exists(LIB_PATH) and os.path.exists(HOST_PATH)):
         from . import build as _build
         _build.build(force=True)
     lib = ctypes.CDLL(LIB_PATH)
@@ -74,6 +77,30 @@ def load():
     lib.mhffn_init.restype = ctypes.c_int
     _lib = lib
     return lib
+
+
+_host = None
+
+
+def _load_host():
+    """The native marshalling module (linked against libmhffn.so)."""
+    global _host
+    load()
+    from . import _host as module
+    _host = module
+    return module
+
+
+def _raw(stream):
+    """A stream's handle; None stands for the current stream of the current device."""
+    return None if stream is None else stream.cuda_stream
+
+
+def _result(r, where):
+    """What a native call returned: its result, or the library's status as an exception."""
+    if type(r) is int:
+        raise MhffnError(r, where)
+    return r
 
 
 def status_string(status):
@@ -186,28 +213,26 @@ def forward(X, W_gate, W_up, W_down, route, eps=1e-6, route_mode=ROUTE_PARAMS, o
             stream=None, workspace=None):
     """Fused forward.  Returns Y [N, H*d_h] (dtype of X).  Scratch is needed only
     for small token counts (see mhffn_workspace_bytes); allocated here if not given."""
-    _check_params(X, W_gate, W_up, W_down, route, route_mode)
-    Y = torch.empty(X.shape, dtype=X.dtype, device=X.device) if out is None else out
-    d = make_desc(X, W_gate, route_mode, eps, Y)
-    workspace, have = _workspace(d, OP_FORWARD, X.device, workspace)
-    rc = load().mhffn_forward(ctypes.byref(d), _p(X), _p(W_gate), _p(W_up), _p(W_down),
-                              _p(route), _p(Y), _p(workspace), have, _stream(stream))
-    if rc != OK:
-        raise MhffnError(rc, "mhffn_forward")
-    return Y
+    r = (_host or _load_host()).forward(X, W_gate, W_up, W_down, route, eps, int(route_mode), out,
+                                        _raw(stream), workspace)
+    if r is None:
+        _check_params(X, W_gate, W_up, W_down, route, route_mode)
+        make_desc(X, W_gate, route_mode, eps, out)
+        raise ValueError("forward: invalid arguments")
+    return _result(r, "mhffn_forward")
 
 
 def forward_static(X, W_gate, W_up, W_down, route, out, eps=1e-6, route_mode=ROUTE_PARAMS,
                    stream=None):
     """mhffn_forward_static: the fused forward into the caller's `out`, with the scratch in the
     library's static device buffer.  Nothing is allocated here either."""
-    _check_params(X, W_gate, W_up, W_down, route, route_mode)
-    d = make_desc(X, W_gate, route_mode, eps, out)
-    rc = load().mhffn_forward_static(ctypes.byref(d), _p(X), _p(W_gate), _p(W_up), _p(W_down),
-                                     _p(route), _p(out), _stream(stream))
-    if rc != OK:
-        raise MhffnError(rc, "mhffn_forward_static")
-    return out
+    r = (_host or _load_host()).forward_static(X, W_gate, W_up, W_down, route, out, eps, int(route_mode),
+                                               _raw(stream))
+    if r is None:
+        _check_params(X, W_gate, W_up, W_down, route, route_mode)
+        make_desc(X, W_gate, route_mode, eps, out)
+        raise ValueError("forward_static: invalid arguments")
+    return _result(r, "mhffn_forward_static")
 
 
 def _grad_outputs(X, W_gate, W_up, W_down, route, want, out, ld_x):
@@ -234,21 +259,15 @@ def backward(X, W_gate, W_up, W_down, route, dY, eps=1e-6, route_mode=ROUTE_PARA
     """Fused recompute-based backward.  Returns a dict of the requested gradients.
     `phase_events`: optional list of raw hipEvent_t handles (ints) recorded between
     the phases of the backward (see mhffn_backward_phases)."""
-    _check_params(X, W_gate, W_up, W_down, route, route_mode)
-    d = make_desc(X, W_gate, route_mode, eps, dY)
-    out = _grad_outputs(X, W_gate, W_up, W_down, route, want, out, d.ld_x)
-    workspace, have = _workspace(d, OP_BACKWARD, X.device, workspace)
-    args = (ctypes.byref(d), _p(X), _p(W_gate), _p(W_up), _p(W_down), _p(route), _p(dY),
-            _p(out.get("dX")), _p(out.get("dW_gate")), _p(out.get("dW_up")),
-            _p(out.get("dW_down")), _p(out.get("d_route")), _p(workspace), have, _stream(stream))
-    if phase_events:
-        ev = (ctypes.c_void_p * len(phase_events))(*phase_events)
-        rc = load().mhffn_backward_phases(*args, ev, len(phase_events))
-    else:
-        rc = load().mhffn_backward(*args)
-    if rc != OK:
-        raise MhffnError(rc, "mhffn_backward")
-    return out
+    r = (_host or _load_host()).backward(X, W_gate, W_up, W_down, route, dY, eps, int(route_mode), tuple(want),
+                                         workspace, dict(out) if out else None, _raw(stream),
+                                         tuple(phase_events) if phase_events else None)
+    if r is None:
+        _check_params(X, W_gate, W_up, W_down, route, route_mode)
+        d = make_desc(X, W_gate, route_mode, eps, dY)
+        _grad_outputs(X, W_gate, W_up, W_down, route, want, out, d.ld_x)
+        raise ValueError("backward: invalid arguments")
+    return _result(r, "mhffn_backward")
 
 
 def reference_unfused(X, W_gate, W_up, W_down, route, eps=1e-6, route_mode=ROUTE_PARAMS,
@@ -290,53 +309,44 @@ def module_forward(X, W_in, W_gate, W_up, W_down, W_r, W_out, eps=1e-6, out=None
                    workspace=None):
     """The whole module: O = fused(X W_in) W_out.  Returns (O, Q, S); Q and S are the two
     d_model-wide activations that module_backward needs."""
-    _check_params(X, W_gate, W_up, W_down, W_r, ROUTE_PARAMS)
-    out = dict(out or {})
-    N, dm = X.shape
-    for k in ("O", "Q", "S"):
-        if k not in out:
-            out[k] = torch.empty((N, dm), dtype=X.dtype, device=X.device)
-    for k, w in (("W_in", W_in), ("W_out", W_out)):
-        _dense(k, w, (dm, dm), X.dtype, X.device)
-    for k in ("Q", "S"):
-        _dense(k, out[k], (N, dm), X.dtype, X.device)
-    d = make_desc(X, W_gate, ROUTE_PARAMS, eps, out["O"])
-    workspace, have = _workspace(d, OP_MODULE_FORWARD, X.device, workspace)
-    rc = load().mhffn_module_forward(ctypes.byref(d), _p(X), _p(W_in), _p(W_gate), _p(W_up),
-                                     _p(W_down), _p(W_r), _p(W_out), _p(out["O"]), _p(out["Q"]),
-                                     _p(out["S"]), _p(workspace), have, _stream(stream))
-    if rc != OK:
-        raise MhffnError(rc, "mhffn_module_forward")
-    return out["O"], out["Q"], out["S"]
+    r = (_host or _load_host()).module_forward(X, W_in, W_gate, W_up, W_down, W_r, W_out, eps,
+                                               dict(out) if out else None, _raw(stream), workspace)
+    if r is None:
+        _check_params(X, W_gate, W_up, W_down, W_r, ROUTE_PARAMS)
+        out, (N, dm) = dict(out or {}), X.shape
+        for k, w in (("W_in", W_in), ("W_out", W_out)):
+            _dense(k, w, (dm, dm), X.dtype, X.device)
+        for k in ("Q", "S"):
+            if k in out:
+                _dense(k, out[k], (N, dm), X.dtype, X.device)
+        make_desc(X, W_gate, ROUTE_PARAMS, eps, out.get("O"))
+        raise ValueError("module_forward: invalid arguments")
+    return _result(r, "mhffn_module_forward")
 
 
 def module_backward(X, W_in, W_gate, W_up, W_down, W_r, W_out, Q, S, dO, eps=1e-6,
                     want=MODULE_GRADS, out=None, stream=None, workspace=None):
     """Backward of module_forward from the saved Q and S.  Returns a dict of gradients."""
-    _check_params(X, W_gate, W_up, W_down, W_r, ROUTE_PARAMS)
-    out = dict(out or {})
-    N, dm = X.shape
-    like = {"dW_in": W_in, "dW_gate": W_gate, "dW_up": W_up, "dW_down": W_down,
-            "dW_r": W_r, "dW_out": W_out}
-    for k, w in (("W_in", W_in), ("W_out", W_out)):
-        _dense(k, w, (dm, dm), X.dtype, X.device)
-    for k, t in (("Q", Q), ("S", S)):
-        _dense(k, t, (N, dm), X.dtype, X.device)
-    d = make_desc(X, W_gate, ROUTE_PARAMS, eps, dO)
-    for k in want:
-        if k not in out:
-            out[k] = _empty_rows_like(X) if k == "dX" else torch.empty_like(like[k])
-    if out.get("dX") is not None:
-        _require(_rows("dX", out["dX"], X) == d.ld_x or N < 2,
-                 "dX must have X's row stride (%d), got %d" % (d.ld_x, out["dX"].stride(0)))
-    for k, ref in like.items():
-        if out.get(k) is not None:
-            _dense(k, out[k], ref.shape, ref.dtype, ref.device)
-    workspace, have = _workspace(d, OP_MODULE_BACKWARD, X.device, workspace)
-    rc = load().mhffn_module_backward(
-        ctypes.byref(d), _p(X), _p(W_in), _p(W_gate), _p(W_up), _p(W_down), _p(W_r), _p(W_out),
-        _p(Q), _p(S), _p(dO), *[_p(out.get(k)) for k in MODULE_GRADS], _p(workspace), have,
-        _stream(stream))
-    if rc != OK:
-        raise MhffnError(rc, "mhffn_module_backward")
-    return {k: out[k] for k in want}
+    r = (_host or _load_host()).module_backward(X, W_in, W_gate, W_up, W_down, W_r, W_out, Q, S, dO, eps,
+                                                tuple(want), dict(out) if out else None, _raw(stream), workspace)
+    if r is None:
+        _check_params(X, W_gate, W_up, W_down, W_r, ROUTE_PARAMS)
+        out, (N, dm) = dict(out or {}), X.shape
+        like = {"dW_in": W_in, "dW_gate": W_gate, "dW_up": W_up, "dW_down": W_down,
+                "dW_r": W_r, "dW_out": W_out}
+        for k, w in (("W_in", W_in), ("W_out", W_out)):
+            _dense(k, w, (dm, dm), X.dtype, X.device)
+        for k, t in (("Q", Q), ("S", S)):
+            _dense(k, t, (N, dm), X.dtype, X.device)
+        d = make_desc(X, W_gate, ROUTE_PARAMS, eps, dO)
+        if out.get("dX") is not None:
+            _require(_rows("dX", out["dX"], X) == d.ld_x or N < 2,
+                     "dX must have X's row stride (%d), got %d" % (d.ld_x, out["dX"].stride(0)))
+        for k in want:
+            _require(k == "dX" or k in like, "unknown gradient %r" % (k,))
+        for k, ref in like.items():
+            if out.get(k) is not None:
+                _dense(k, out[k], ref.shape, ref.dtype, ref.device)
+        raise ValueError("module_backward: invalid arguments")
+    r = _result(r, "mhffn_module_backward")
+    return {k: r[k] for k in want}
