@@ -10,23 +10,27 @@
 //   dX = dY W^T  A = dY row form,  B = W row form
 //   dW = X^T dY  A = X transposed, B = dY transposed
 //
-// Workgroup = 16 waves = 256 (m) x 256 (n) output tile, wave = 64 x 64 (2 x 2 products of
-// 32 x 32), k in slices of 64.  What sets the shape is the global -> LDS rate: measured,
-// a CU takes about 27 bytes per clock through direct loads (14 TB/s over the chip), so a
-// 256 x 128 tile (1.6 GB of operand traffic for a 16384 x 2048 x 2048 product) spends
-// 0.116 ms on loads alone; 256 x 256 needs 1.07 GB.  Four waves per SIMD at 128 registers
-// then hide each other's LDS latency without a second register set.  The n side sits on
-// the MFMA row axis and the m side on the column axis, so a lane ends up with four
-// consecutive n of one row m and stores 8 bytes.  Operand slices go global -> LDS
-// directly into two 64 KB stages (four wave-wide loads per wave and slice), requested
-// one slice ahead; one bare barrier per slice.
-// LDS images: row form [rows][64] with the eight 16-byte chunks of a row permuted,
-// transposed form the swizzled [32][128] tile of the fused kernels; both are free of
-// bank conflicts for their reads.  Operand reads are issued untracked, eight at a time,
-// and waited for by count.
-// With a transposed operand in play the contraction slots of one MFMA step follow the
-// transposing read (slot s of lane group g <-> k = 8 (s / 4) + 4 g + s % 4); a row-form
-// partner is then read as two 8-byte halves with the same mapping.
+// A workgroup owns a BM x BN tile of C (256 x 256 where there are enough of them, smaller
+// ones otherwise: plan_tiles), its waves take TM x TN pieces as products of 32 x 32, and k
+// runs in slices of 32.  What bounds it:
+//   * the global -> LDS rate: measured, a CU takes about 27 bytes per clock through direct
+//     loads (14 TB/s over the chip), so a slice of 256 + 256 rows (32 KB) costs 1200 clocks
+//     against 1024 of products;
+//   * their latency, about 2 us when all CUs load: the slices go into a ring of up to five
+//     stages, requested as many slices ahead, with counted waits (two stages of 64, waited for
+//     with one slice of look-ahead, made every 64 of k cost 4600 clocks);
+//   * LDS reads: a wave of 128 x 64 reads six operands for eight products (of 64 x 64: eight
+//     for eight).
+// The n side sits on the MFMA row axis and the m side on the column axis, so a lane ends up
+// with four consecutive n of one row m; the tile goes out through LDS as whole rows.
+// LDS images: row form [rows][32 k], 64-byte rows whose four 16-byte chunks are permuted by
+// (row / 4) % 4; transposed form the swizzled [32 k][128] tile of the fused kernels; both are
+// free of bank conflicts for their reads.  Operand reads are issued untracked, six to eight
+// instructions ahead and across slice boundaries, and waited for by count.
+// Rates (row x transposed form): 16384 x 2048 x 2048 126 us (1090 TFLOP/s; 16 waves of 64 x 64
+// on two stages of 64: 136 .. 162), 16384 x 1024 x 1024 42 us (54), 4000 x 2048 x 2048 41 us
+// (62 with its partials), 1000 x 2048 x 2048 19 us (33); weight gradient of 16384 rows,
+// 1024 x 1024: 60 us (71).
 #include "mhffn_device.h"
 #include "mhffn_internal.h"
 
@@ -35,16 +39,7 @@
 namespace mhffn {
 namespace {
 
-constexpr int kGWaves = 16, kGThreads = 64 * kGWaves;
-constexpr int kGTileM = 256, kGTileN = 256, kGBK = 64;
-constexpr int kGMBytes = kGTileM * kGBK * 2;   // 32 KB
-constexpr int kGNBytes = kGTileN * kGBK * 2;   // 32 KB
-constexpr int kGStageBytes = kGMBytes + kGNBytes;
-constexpr int kGStages = 2;
-constexpr int kGLdsBytes = kGStages * kGStageBytes;   // 128 KB
-constexpr int kGLoads = (kGStageBytes / 1024) / kGWaves;   // wave-wide 1 KB loads per wave and slice
-static_assert(kGLdsBytes <= (int)kLdsBytesPerWorkgroup, "both stages must fit in LDS");
-static_assert(kGLoads == 4, "2 images of the m side and 2 of the n side per wave");
+constexpr int kGBK = 32;   // k per slice
 
 struct TunedGemmArgs {
   const uint16_t* A;   // m side
@@ -68,242 +63,246 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-// LDS image of one side of a slice (256 rows):
-//   row form:        [rows][64 k], 128-byte rows, chunks permuted as in the 64-wide tile
-//   transposed form: swizzled [32 k][128] tiles, tile index = (k / 32) * (rows / 128) + row / 128
-// Both are contiguous in 1 KB images (8 rows, or 4 k rows of one tile), which is what one
-// wave-wide direct load writes.
+// Tile shapes: output tile, waves along m and n, stages of the ring
+template <int BM_, int BN_, int WM_, int WN_, int S_>
+struct GemmTile {
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, S = S_;
+  static constexpr int NW = WM * WN, TM = BM / WM, TN = BN / WN, IM = TM / 32, IN = TN / 32;
+  static constexpr int kMBytes = BM * kGBK * 2, kNBytes = BN * kGBK * 2, kStage = kMBytes + kNBytes;
+  static constexpr int kLoads = kStage / 1024 / NW;      // wave-wide 1 KB loads per wave and slice
+  static constexpr int kLds = S * kStage > NW * TM * TN * 2 ? S * kStage : NW * TM * TN * 2;
+  static_assert(kLoads * 1024 * NW == kStage && kMBytes / 1024 % NW == 0 && BN % 128 == 0, "whole loads per wave");
+  static_assert(kLds <= (int)kLdsBytesPerWorkgroup, "stages and the output tile must fit in LDS");
+};
+using Tile256x256 = GemmTile<256, 256, 2, 4, 5>;
+using Tile256x128 = GemmTile<256, 128, 4, 2, 6>;
+using Tile128x128 = GemmTile<128, 128, 2, 4, 4>;
+using Tile64x128 = GemmTile<64, 128, 2, 2, 5>;   // (m side in row form: a transposed image is 128 wide)
 
-template <bool A_TR, bool B_TR>
-__global__ __launch_bounds__(kGThreads) void gemm_bf16_kernel(TunedGemmArgs a) {
-  constexpr bool kTrSlots = A_TR || B_TR;   // contraction slots follow the transposing read
+// byte offset of 16-byte chunk `chunk` of `row` in a row-form image
+__device__ __forceinline__ int row_image_off(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 2) & 3)) << 4); }
+
+template <bool A_TR, bool B_TR, typename G>
+__global__ __launch_bounds__(64 * G::NW, G::BM == 256 ? 2 : 4) void gemm_bf16_kernel(TunedGemmArgs a) {
+  constexpr int IM = G::IM, IN = G::IN, S = G::S, NW = G::NW;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 31, g = lane >> 5;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  const int wm = wave_u >> 2, wn = wave_u & 3;      // 4 x 4 waves
+  const int wm = wave_u / G::WN, wn = wave_u % G::WN;
   const int64_t item = xcd_work_item(blockIdx.x, a.n_items);
   if (item >= a.n_items) return;
   const int split = (int)(item % a.splits);
   const int64_t tile = item / a.splits;
-  const int64_t m0 = (tile / a.tiles_n) * kGTileM, n0 = (tile % a.tiles_n) * kGTileN;
+  const int64_t m0 = (tile / a.tiles_n) * G::BM, n0 = (tile % a.tiles_n) * G::BN;
   const int64_t K = a.K;
   const int64_t KT_all = (K + kGBK - 1) / kGBK;
   const int64_t kbase = split * a.slices_per_split;           // first slice of this workgroup
   const int64_t kend = kbase + a.slices_per_split < KT_all ? kbase + a.slices_per_split : KT_all;
-  const int64_t KT = kend - kbase;                            // its number of slices (>= 1)
+  const int KT = (int)(kend - kbase);                         // its number of slices (>= 1)
 
-  // ---- staging: four wave-wide 1 KB loads per wave and slice -----------------------------
-  // images 2w, 2w+1 of the 32 of the m side and of the 32 of the n side.
-  // Row form: image i = rows 8i .. 8i+7, lane l -> row 8i + l/8, physical chunk l%8.
-  // Transposed form: image i = k rows 4(i%8) .. +3 of tile i/8, lane l -> k row + l/16,
-  // physical chunk l%16.  Rows / columns past the edge are clamped (their products are never
-  // stored); k rows past K are clamped too and their slots cleared before use.
-  const uint16_t* src[kGLoads];
-  int64_t kstride[kGLoads];   // transposed form: element stride of k
-  int krow[kGLoads];          // transposed form: k row of this lane inside a slice (else -1)
-  int lds_img[kGLoads];       // byte offset of the image inside a stage
-  auto setup = [&](int slot, bool tr, const uint16_t* base, int64_t ld, int64_t row0, int64_t rows,
-                   int tile_rows, int img, int side_off) {
-    if (!tr) {
-      const int row = 8 * img + (lane >> 3);
-      const int u = row >> 1;
-      const int sw = ((u & 1) << 1) | ((u & 2) << 1) | ((u >> 2) & 1);   // as in tile_off_dh<64>
-      const int chunk = (lane & 7) ^ sw;
-      int64_t gr = row0 + row;
-      gr = gr < rows ? gr : rows - 1;
-      src[slot] = base + gr * ld + chunk * 8;
-      kstride[slot] = 0;
-      krow[slot] = -1;
+  // ---- staging: wave-wide 1 KB loads, kLoads per wave and slice ---------------------------
+  // Load q of wave w is image q NW + w of the stage: first the m side's, then the n side's.
+  // Row form: image i = rows 16 i .. + 15, lane l -> row + l / 4, physical chunk l % 4.
+  // Transposed form: image i = k rows 4 (i % 8) .. + 3 of the 128-wide tile i / 8, lane l -> k
+  // row + l / 16, physical chunk l % 16.  Rows / columns past the edge are clamped (their
+  // products are never stored); k rows past K are clamped too and their slots cleared before use.
+  // A request is a wave-uniform base (advanced with the slice) plus a 32-bit byte offset per lane.
+  constexpr bool kRagged = A_TR && B_TR;   // only then may K end inside a slice (gemm_bf16_supported)
+  unsigned goff[G::kLoads], glast[G::kLoads];   // glast: for the last slice, k rows past K repeat row K - 1
+  const int k_left = (int)(K - (KT_all - 1) * kGBK);
+#pragma unroll
+  for (int q = 0; q < G::kLoads; ++q) {
+    const bool m_side = q < G::kMBytes / 1024 / NW;           // (a compile-time fact)
+    const int img = q * NW + wave_u - (m_side ? 0 : G::kMBytes / 1024);
+    const int64_t ld = m_side ? a.lda : a.ldb, row0 = m_side ? m0 : n0, rows = m_side ? a.M : a.N;
+    if (!(m_side ? A_TR : B_TR)) {
+      const int row = 16 * img + (lane >> 2);
+      const int64_t gr = row0 + row < rows ? row : rows - 1 - row0;
+      goff[q] = glast[q] = (unsigned)(gr * ld * 2 + (((lane & 3) ^ ((row >> 2) & 3)) << 4));
     } else {
-      const int tile = img >> 3, halves = tile_rows >> 7;
-      const int kr = 32 * (tile / halves) + 4 * (img & 7) + (lane >> 4);
-      const int chunk = (lane & 15) ^ swz(kr & 31);
-      int64_t gc = row0 + 128 * (tile % halves) + chunk * 8;
-      gc = gc + 8 <= rows ? gc : rows - 8;
-      src[slot] = base + gc;      // + k row * ld, added per slice (clamped)
-      kstride[slot] = ld;
-      krow[slot] = kr;
+      const int kr = 4 * (img & 7) + (lane >> 4);
+      int64_t gc = row0 + 128 * (img >> 3) + (((lane & 15) ^ swz(kr)) << 3);
+      gc = (gc + 8 <= rows ? gc : rows - 8) - row0;
+      goff[q] = (unsigned)((kr * ld + gc) * 2);
+      glast[q] = (unsigned)(((kr < k_left ? kr : k_left - 1) * ld + gc) * 2);
     }
-    lds_img[slot] = side_off + img * 1024;
-  };
+  }
+  const unsigned char* const abase =
+      reinterpret_cast<const unsigned char*>(a.A + (A_TR ? m0 + kbase * kGBK * a.lda : m0 * a.lda + kbase * kGBK));
+  const unsigned char* const bbase =
+      reinterpret_cast<const unsigned char*>(a.B + (B_TR ? n0 + kbase * kGBK * a.ldb : n0 * a.ldb + kbase * kGBK));
+  const int64_t astep = (A_TR ? a.lda : 1) * (kGBK * 2), bstep = (B_TR ? a.ldb : 1) * (kGBK * 2);
+  auto request = [&](int kt, int stage) {
+    const bool last = kRagged && kbase + kt == KT_all - 1;
+    const unsigned char* const pa = abase + kt * astep;
+    const unsigned char* const pb = bbase + kt * bstep;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) setup(i, A_TR, a.A, a.lda, m0, a.M, kGTileM, 2 * wave_u + i, 0);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) setup(2 + i, B_TR, a.B, a.ldb, n0, a.N, kGTileN, 2 * wave_u + i, kGMBytes);
-  auto dma_one = [&](int64_t kt, int stage, int s) {
-    const uint16_t* p;
-    if (krow[s] < 0) {
-      p = src[s] + kt * kGBK;
-    } else {
-      int64_t k = kt * kGBK + krow[s];
-      k = k < K ? k : K - 1;
-      p = src[s] + k * kstride[s];
+    for (int q = 0; q < G::kLoads; ++q) {
+      const unsigned off = last ? glast[q] : goff[q];
+      global_to_lds_16B((q < G::kMBytes / 1024 / NW ? pa : pb) + off, smem + stage * G::kStage + (q * NW + wave_u) * 1024);
     }
-    global_to_lds_16B(p, smem + stage * kGStageBytes + lds_img[s]);
-  };
-  auto dma = [&](int64_t kt, int stage) {
-#pragma unroll
-    for (int s = 0; s < kGLoads; ++s) dma_one(kt, stage, s);
   };
 
-  // ---- operand addresses inside a stage --------------------------------------------------
-  // item = (t2, idx, side): t2 = 16-wide contraction step 0..3, idx = 32-row block of the
-  // wave's 64, side 0 = n (MFMA rows), 1 = m (MFMA columns).  Split reads (8 bytes twice)
-  // whenever the contraction slots follow the transposing read.  What does not depend on
-  // the lane goes into the instruction's offset field:
-  //   row form:        register per t2 (the chunk permutation is an XOR), idx = +32 rows = +4096
-  //   transposed form: register per idx, t2 = +16 k rows (+4096) and, from t2 = 2 on, the
-  //                    next group of 32-row tiles; the swizzle does not depend on t2
+  // ---- operand addresses inside a stage ----------------------------------------------------
+  // operand (side, idx, t2): 32-row block idx of the wave's piece, 16-wide contraction step t2.
+  //   row form:        one 16-byte read; register per t2 (the chunk permutation is an XOR), + 2048 per idx
+  //   transposed form: two transposing reads of four k rows each, register per idx, + 4096 per t2;
+  //                    slots 8 g .. 8 g + 7 are k rows 16 t2 + 8 g .. as in the row form
   const unsigned lbase = lds_addr_of(smem);
-  unsigned arow[2][4], arow2[2][4];   // row form [side][t2]: first / second half of a split read
-  unsigned atr[2][2], atr2[2][2];     // transposed form [side][idx]: k rows .. and .. + 8
+  unsigned arow[2][2];                              // row form [side][t2]
+  unsigned atr[2][IM > IN ? IM : IN][2];            // transposed form [side][idx]: k rows .. and .. + 4
 #pragma unroll
   for (int side = 0; side < 2; ++side) {
     const bool tr = side ? A_TR : B_TR;
-    const int wrow = side ? 64 * wm : 64 * wn;
-    const unsigned sbase = lbase + (side ? 0 : kGMBytes);
+    const int wrow = side ? G::TM * wm : G::TN * wn;
+    const unsigned sbase = lbase + (side ? 0 : G::kMBytes);
     if (!tr) {
 #pragma unroll
-      for (int t2 = 0; t2 < 4; ++t2) {
-        const int row = wrow + r;
-        arow[side][t2] = sbase + (kTrSlots ? tile_off_dh<64>(row, 2 * t2) + 8 * g
-                                           : tile_off_dh<64>(row, 2 * t2 + g));
-        arow2[side][t2] = sbase + tile_off_dh<64>(row, 2 * t2 + 1) + 8 * g;
-      }
+      for (int t2 = 0; t2 < 2; ++t2) arow[side][t2] = sbase + row_image_off(wrow + r, 2 * t2 + g);
     } else {
 #pragma unroll
-      for (int idx = 0; idx < 2; ++idx) {
-        const int li = lane & 15;
-        const int kr = 4 * g + (li >> 2);
+      for (int idx = 0; idx < (side ? IM : IN); ++idx) {
+        const int li = lane & 15, kr = 8 * g + (li >> 2);
         const int col = wrow + 32 * idx + 16 * ((lane >> 4) & 1) + 4 * (li & 3);
-        atr[side][idx] = sbase + (col >> 7) * 8192 + tile_off8(kr, col & 127);
-        atr2[side][idx] = sbase + (col >> 7) * 8192 + tile_off8(kr + 8, col & 127);
+        atr[side][idx][0] = sbase + (col >> 7) * 8192 + tile_off8(kr, col & 127);
+        atr[side][idx][1] = sbase + (col >> 7) * 8192 + tile_off8(kr + 4, col & 127);
       }
     }
   }
 
-  f32x16 acc[2][2];   // [n block][m block]
+  f32x16 acc[IN][IM];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < IN; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{0};
+    for (int j = 0; j < IM; ++j) acc[i][j] = f32x16{0};
 
-  // ---- main loop ----------------------------------------------------------------------------
-  // Two stages.  Iteration kt: barrier (slice kt has landed everywhere, everyone is done with
-  // slice kt-1), request slice kt+1 into the other stage, then the slice in two halves of
-  // two contraction steps: eight operand reads issued, eight products consumed with counted
-  // waits.  Four waves share a SIMD, so one wave's LDS latency is another's MFMA time.
-  constexpr bool kSplit = kTrSlots;
-  constexpr int kInstr = kSplit ? 2 : 1;   // LDS read instructions per operand
-  struct Half {
-    s16x4 lo[8], hi[8];   // split reads
-    bf16x8 full[8];       // 16-byte reads
+  // ---- main loop ------------------------------------------------------------------------------
+  // Top of slice kt: wait for this wave's part of slice kt + 1 (the requests behind it stay in
+  // flight), barrier (slices kt and kt + 1 have landed everywhere, everyone is done with slice
+  // kt - 1), request slice kt + S - 1 into the stage of slice kt - 1.  Items c of a slice:
+  // contraction step t2 = c / (IN + IM), first the n operands, then the m operands; an m operand
+  // is followed by its IN products.  Reads run kWin items ahead and across the slice boundary,
+  // so that no wave starts a slice by waiting for LDS.
+  constexpr int OPS = IN + IM, NOP = 2 * OPS, kWin = OPS;
+  constexpr int kNInstr = B_TR ? 2 : 1, kMInstr = A_TR ? 2 : 1;   // LDS instructions per operand
+  constexpr int kPending = IN * kNInstr + IM * kMInstr;           // of the OPS items behind any item
+  static_assert(kPending <= 15, "lgkmcnt holds four bits");
+  s16x4 lo[NOP], hi[NOP];
+  bf16x8 full[NOP], nf[IN];
+  auto issue = [&](auto C_, unsigned so) {
+    constexpr int c = decltype(C_)::value, t2 = c / OPS, o = c % OPS;
+    constexpr int side = o < IN ? 0 : 1, idx = side ? o - IN : o;
+    if constexpr (side ? A_TR : B_TR) {
+      lo[c] = lds_read_tr16_untracked<t2 * 4096>(atr[side][idx][0] + so);
+      hi[c] = lds_read_tr16_untracked<t2 * 4096>(atr[side][idx][1] + so);
+    } else {
+      full[c] = lds_read_b128_untracked<2048 * idx>(arow[side][t2] + so);
+    }
   };
-  auto issue_half = [&](Half& f, unsigned so, auto HB_) {
-    static_for<0, 8>([&](auto IT_) {
-      constexpr int it = decltype(IT_)::value, t2 = 2 * decltype(HB_)::value + (it >> 2);
-      constexpr int idx = (it >> 1) & 1, side = it & 1;
-      constexpr bool tr = side ? A_TR : B_TR;
-      if constexpr (tr) {
-        constexpr int OFF = (t2 & 1) * 4096 + (t2 >> 1) * 16384;   // two 32-row tiles per group of 32 k rows
-        f.lo[it] = lds_read_tr16_untracked<OFF>(atr[side][idx] + so);
-        f.hi[it] = lds_read_tr16_untracked<OFF>(atr2[side][idx] + so);
-      } else if constexpr (kSplit) {
-        f.lo[it] = lds_read_b64_untracked<4096 * idx>(arow[side][t2] + so);
-        f.hi[it] = lds_read_b64_untracked<4096 * idx>(arow2[side][t2] + so);
+  auto slice = [&](int kt, unsigned so, unsigned so_next) {
+    const bool ragged_last = (A_TR && B_TR) && (kbase + kt == KT_all - 1) && (K % kGBK) != 0;
+    static_for<0, NOP>([&](auto C_) {
+      constexpr int c = decltype(C_)::value, t2 = c / OPS, o = c % OPS;
+      constexpr int side = o < IN ? 0 : 1;
+      if constexpr (c + kWin < NOP) issue(std::integral_constant<int, c + kWin>{}, so);
+      else issue(std::integral_constant<int, c + kWin - NOP>{}, so_next);   // (past the last slice: never used)
+      bf16x8 v;
+      if constexpr (side ? A_TR : B_TR) {
+        lds_wait<kPending>(lo[c], hi[c]);
+        v = join_tr(lo[c], hi[c]);
       } else {
-        f.full[it] = lds_read_b128_untracked<4096 * idx>(arow[side][t2] + so);
+        lds_wait<kPending>(full[c]);
+        v = full[c];
+      }
+      if constexpr (side == 0) {
+        if (ragged_last) {   // k rows past K were clamped: clear their slots on the n side
+#pragma unroll
+          for (int sl = 0; sl < 8; ++sl)
+            if ((kbase + kt) * kGBK + 16 * t2 + 8 * g + sl >= K) v[sl] = (__bf16)0.0f;
+        }
+        nf[o] = v;
+      } else {
+#pragma unroll
+        for (int jn = 0; jn < IN; ++jn) acc[jn][o - IN] = mfma32(nf[jn], v, acc[jn][o - IN]);
       }
     });
   };
-  auto compute_half = [&](Half& f, int64_t kt, auto HB_) {
-    const bool ragged_last = kTrSlots && (kt == KT_all - 1) && (K % kGBK) != 0;
-    static_for<0, 2>([&](auto TT_) {
-      constexpr int tt = decltype(TT_)::value, t2 = 2 * decltype(HB_)::value + tt;
-      bf16x8 nf[2], mf[2];
-      static_for<0, 4>([&](auto Q_) {
-        constexpr int it = 4 * tt + decltype(Q_)::value, idx = (it >> 1) & 1, side = it & 1;
-        constexpr int pending = (7 - it) * kInstr;   // reads issued after this item
-        bf16x8 v;
-        if constexpr (kSplit) {
-          lds_wait<pending>(f.lo[it], f.hi[it]);
-          v = join_tr(f.lo[it], f.hi[it]);
-        } else {
-          lds_wait<pending>(f.full[it]);
-          v = f.full[it];
-        }
-        if constexpr (side == 0) {
-          if (ragged_last) {
-            // k rows past K were clamped when the slice was requested: clear their slots on the
-            // n side (slot s of lane group g <-> k = 16 t2 + 8 (s / 4) + 4 g + s % 4)
-#pragma unroll
-            for (int sl = 0; sl < 8; ++sl)
-              if (kt * kGBK + 16 * t2 + 8 * (sl >> 2) + 4 * g + (sl & 3) >= K) v[sl] = (__bf16)0.0f;
-          }
-          nf[idx] = v;
-        } else {
-          mf[idx] = v;
-        }
-      });
-      acc[0][0] = mfma32(nf[0], mf[0], acc[0][0]);
-      acc[1][0] = mfma32(nf[1], mf[0], acc[1][0]);
-      acc[0][1] = mfma32(nf[0], mf[1], acc[0][1]);
-      acc[1][1] = mfma32(nf[1], mf[1], acc[1][1]);
-    });
-  };
 
-  dma(kbase, 0);
-  auto iteration = [&](int64_t kt, auto STAGE_) {
-    constexpr int stage = decltype(STAGE_)::value;
+  for (int i = 0; i < S - 1 && i < KT; ++i) request(i, i);
+  constexpr int kAhead = G::kLoads * (S - 3);   // this wave's loads behind slice kt + 1
+  static_assert(S >= 3 && kAhead < 64, "vmcnt holds six bits");
+  int stage = 0;
+  for (int kt = 0; kt < KT; ++kt) {
     asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's part of slice kt
+    if (kt + S - 2 < KT) __builtin_amdgcn_s_waitcnt(0x0F70 | (kAhead & 15) | ((kAhead >> 4) << 14));   // vmcnt(kAhead)
+    else __builtin_amdgcn_s_waitcnt(0x0F70);                                                          // vmcnt(0)
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    if (kt + 1 < KT) dma(kbase + kt + 1, stage ^ 1);
-    Half f;
-    issue_half(f, stage * kGStageBytes, std::integral_constant<int, 0>{});
-    compute_half(f, kbase + kt, std::integral_constant<int, 0>{});
-    issue_half(f, stage * kGStageBytes, std::integral_constant<int, 1>{});
-    compute_half(f, kbase + kt, std::integral_constant<int, 1>{});
-  };
-  for (int64_t kt = 0; kt < KT; kt += 2) {
-    iteration(kt, std::integral_constant<int, 0>{});
-    if (kt + 1 < KT) iteration(kt + 1, std::integral_constant<int, 1>{});
+    if (kt == 0) static_for<0, kWin>([&](auto C_) { issue(C_, 0u); });
+    if (kt + S - 1 < KT) request(kt + S - 1, stage == 0 ? S - 1 : stage - 1);
+    const int next = stage + 1 == S ? 0 : stage + 1;
+    slice(kt, stage * G::kStage, next * G::kStage);
+    stage = next;
   }
+  __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): the reads issued for a slice that never comes
 
   // ---- store: lane = row m, registers = four consecutive n per group ----------------------
+  if (a.splits > 1 || a.accumulate) {
 #pragma unroll
-  for (int im = 0; im < 2; ++im) {
-    const int64_t m = m0 + 64 * wm + 32 * im + r;
-    if (m >= a.M) continue;
+    for (int im = 0; im < IM; ++im) {
+      const int64_t m = m0 + G::TM * wm + 32 * im + r;
+      if (m >= a.M) continue;
 #pragma unroll
-    for (int jn = 0; jn < 2; ++jn) {
+      for (int jn = 0; jn < IN; ++jn) {
 #pragma unroll
-      for (int vq = 0; vq < 4; ++vq) {
-        const int64_t n = n0 + 64 * wn + 32 * jn + 8 * vq + 4 * g;
-        if (n + 4 > a.N) continue;
-        if (a.splits > 1) {
-          const f32x4 v = {acc[jn][im][4 * vq], acc[jn][im][4 * vq + 1], acc[jn][im][4 * vq + 2],
-                           acc[jn][im][4 * vq + 3]};
-          *reinterpret_cast<f32x4*>(a.P + ((size_t)split * a.M + m) * a.N + n) = v;
-        } else {
+        for (int vq = 0; vq < 4; ++vq) {
+          const int64_t n = n0 + G::TN * wn + 32 * jn + 8 * vq + 4 * g;
+          if (n + 4 > a.N) continue;
           float o[4] = {acc[jn][im][4 * vq], acc[jn][im][4 * vq + 1], acc[jn][im][4 * vq + 2],
                         acc[jn][im][4 * vq + 3]};
-          u32x2* dst = reinterpret_cast<u32x2*>(a.C + m * a.ldc + n);
-          if (a.accumulate) {
-            const u32x2 old = *dst;
-            o[0] += __builtin_bit_cast(float, old[0] << 16);
-            o[1] += __builtin_bit_cast(float, old[0] & 0xFFFF0000u);
-            o[2] += __builtin_bit_cast(float, old[1] << 16);
-            o[3] += __builtin_bit_cast(float, old[1] & 0xFFFF0000u);
+          if (a.splits > 1) {
+            *reinterpret_cast<f32x4*>(a.P + ((size_t)split * a.M + m) * a.N + n) = f32x4{o[0], o[1], o[2], o[3]};
+            continue;
           }
-          u32x2 pk;
-          pk[0] = pack_bf16(o[0], o[1]);
-          pk[1] = pack_bf16(o[2], o[3]);
-          *dst = pk;
+          u32x2* dst = reinterpret_cast<u32x2*>(a.C + m * a.ldc + n);
+          const u32x2 old = *dst;
+          o[0] += __builtin_bit_cast(float, old[0] << 16);
+          o[1] += __builtin_bit_cast(float, old[0] & 0xFFFF0000u);
+          o[2] += __builtin_bit_cast(float, old[1] << 16);
+          o[3] += __builtin_bit_cast(float, old[1] & 0xFFFF0000u);
+          *dst = u32x2{pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3])};
         }
       }
+    }
+    return;
+  }
+  // whole rows: the wave's piece passes through LDS ([TM][TN] bf16, the 16-byte chunks of a row
+  // permuted by the row so that neither side meets more than two lanes per bank)
+  constexpr int CR = G::TN / 8;                        // chunks per row
+  __syncthreads();                                     // the stages are done with
+  unsigned char* piece = smem + wave * (G::TM * G::TN * 2);
+#pragma unroll
+  for (int im = 0; im < IM; ++im)
+#pragma unroll
+    for (int jn = 0; jn < IN; ++jn)
+#pragma unroll
+      for (int vq = 0; vq < 4; ++vq) {
+        const int row = 32 * im + r, chunk = (4 * jn + vq) ^ (row & (CR - 1));
+        const u32x2 pk = {pack_bf16(acc[jn][im][4 * vq], acc[jn][im][4 * vq + 1]),
+                          pack_bf16(acc[jn][im][4 * vq + 2], acc[jn][im][4 * vq + 3])};
+        *reinterpret_cast<u32x2*>(piece + row * (G::TN * 2) + chunk * 16 + 8 * g) = pk;
+      }
+  // (the piece is this wave's own: its reads follow its writes in the same queue)
+#pragma unroll 4
+  for (int i = lane; i < G::TM * CR; i += 64) {
+    const int row = i / CR, chunk = i % CR;
+    const int64_t m = m0 + G::TM * wm + row, n = n0 + G::TN * wn + 8 * chunk;
+    const u32x4 v = *reinterpret_cast<const u32x4*>(piece + row * (G::TN * 2) + ((chunk ^ (row & (CR - 1))) << 4));
+    if (m < a.M && n + 8 <= a.N) {
+      u32x2* dst = reinterpret_cast<u32x2*>(a.C + m * a.ldc + n);   // (ldc is a multiple of four)
+      if ((a.ldc & 7) == 0) *reinterpret_cast<u32x4*>(dst) = v;
+      else { dst[0] = u32x2{v[0], v[1]}; dst[1] = u32x2{v[2], v[3]}; }
     }
   }
 }
@@ -346,6 +345,7 @@ __global__ void gemm_bf16_reduce_kernel(TunedGemmArgs a) {
 constexpr int kSkinnyWaves = 16, kSkinnyRows = 32, kSkinnyCols = 32;
 constexpr int kSkinnyWaveLds = 2 * 4096;   // a slice of B and one of A
 constexpr int kSkinnyLds = kSkinnyWaves * kSkinnyWaveLds;
+constexpr int kSkinnyK = 64;               // k per slice of this kernel
 constexpr int kSkinnySlices = 2;           // k slices in flight per wave (registers)
 
 template <bool B_TR>
@@ -355,7 +355,7 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void gemm_bf16_skinny_kernel(Tun
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 31, g = lane >> 5;
   const int64_t n0 = (int64_t)blockIdx.x * kSkinnyCols, m0 = (int64_t)blockIdx.y * kSkinnyRows;
-  const int KT = (int)(a.K / kGBK);
+  const int KT = (int)(a.K / kSkinnyK);
   unsigned char* btile = smem + wave * kSkinnyWaveLds;   // [64 k][32 n], or [32 n][64 k] swizzled
   unsigned char* atile = btile + 4096;                   // [32 m][64 k], swizzled
   // row-form pieces: load i takes rows 8 i + lane / 8, 16-byte chunk lane % 8
@@ -371,7 +371,7 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void gemm_bf16_skinny_kernel(Tun
     for (int s = 0; s < SL; ++s) {
       const int sl = s0 + NW * s;
       if (sl >= KT) continue;
-      const int64_t k0 = (int64_t)sl * kGBK;
+      const int64_t k0 = (int64_t)sl * kSkinnyK;
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         w[s][i] = *reinterpret_cast<const u32x4*>(B_TR ? bsrc + (k0 + 16 * i) * a.ldb : bsrc + 8 * i * a.ldb + k0);
@@ -439,27 +439,38 @@ int launch_skinny(const TunedGemmArgs& a, hipStream_t stream) {
   return (int)hipGetLastError();
 }
 
-// Split k only when the output tiles alone leave most of the chip idle (the weight-gradient
-// products: d_model x d_model outputs, contraction over all tokens).
-struct SplitK { int splits; int64_t slices_per_split; };
-SplitK plan_split_k(int64_t M, int64_t N, int64_t K) {
-  const int64_t tiles = ((M + kGTileM - 1) / kGTileM) * ((N + kGTileN - 1) / kGTileN);
+// Tile shape and split of the contraction, from what was measured (clocks of a CU at 2.2 GHz):
+// a slice of k costs a workgroup kSliceClocks (the smaller shapes share the CU, so two of them
+// take as long as one after the other); a workgroup starts in about 4000 and stores its tile at
+// 9 bytes per clock (all CUs do so at the same time: 5 TB/s); the sum of the partials is a launch
+// of about 9000 and reads 2600 bytes per clock.
+struct GemmPlan { int shape, splits; int64_t slices_per_split; double clocks; };
+constexpr int kShapeM[4] = {256, 256, 128, 64}, kShapeN[4] = {256, 128, 128, 128};
+constexpr double kSliceClocks[2][4] = {{1900, 1220, 770, 550}, {1980, 1300, 850, 0}};   // [A transposed]
+GemmPlan plan_tiles(bool a_tr, int64_t M, int64_t N, int64_t K) {
   const int64_t KT = (K + kGBK - 1) / kGBK;
-  int64_t want = tiles >= 192 ? 1 : (256 + tiles - 1) / tiles;
-  if (want > 16) want = 16;
-  if (want > KT / 8) want = KT / 8 > 0 ? KT / 8 : 1;   // at least eight slices per workgroup
-  SplitK s;
-  s.slices_per_split = (KT + want - 1) / want;
-  s.splits = (int)((KT + s.slices_per_split - 1) / s.slices_per_split);
-  return s;
+  GemmPlan best{0, 1, KT, 0.0};
+  for (int sh = 0; sh < (a_tr ? 3 : 4); ++sh) {
+    const int64_t tiles = ((M + kShapeM[sh] - 1) / kShapeM[sh]) * ((N + kShapeN[sh] - 1) / kShapeN[sh]);
+    for (int want = 1; want <= 16; ++want) {
+      const int64_t per = (KT + want - 1) / want;
+      if (want > 1 && (per < 8 || (KT + per - 1) / per != want)) continue;   // at least eight slices per workgroup
+      const double out = kShapeM[sh] * kShapeN[sh] * (want > 1 ? 4 : 2) / 9.0;
+      double cost = (double)((tiles * want + 255) / 256) * (per * kSliceClocks[a_tr][sh] + 4000 + out);
+      if (want > 1) cost += 9000 + (double)want * M * N * 4 / 2600;
+      if (best.clocks == 0.0 || cost < best.clocks) best = {sh, want, per, cost};
+    }
+  }
+  return best;
 }
 
-template <bool A_TR, bool B_TR>
-int launch_form(const TunedGemmArgs& a, hipStream_t stream) {
-  if (hipError_t e0 = LdsLimit<&gemm_bf16_kernel<A_TR, B_TR>, kGLdsBytes>::ensure(); e0 != hipSuccess)
-    return (int)e0;
-  hipLaunchKernelGGL((gemm_bf16_kernel<A_TR, B_TR>), dim3((unsigned)xcd_grid_size(a.n_items)),
-                     dim3(kGThreads), kGLdsBytes, stream, a);
+template <bool A_TR, bool B_TR, typename G>
+int launch_shape(TunedGemmArgs a, hipStream_t stream) {
+  a.tiles_n = (a.N + G::BN - 1) / G::BN;
+  a.n_items = ((a.M + G::BM - 1) / G::BM) * a.tiles_n * a.splits;
+  if (hipError_t e0 = LdsLimit<&gemm_bf16_kernel<A_TR, B_TR, G>, G::kLds>::ensure(); e0 != hipSuccess) return (int)e0;
+  hipLaunchKernelGGL((gemm_bf16_kernel<A_TR, B_TR, G>), dim3((unsigned)xcd_grid_size(a.n_items)), dim3(64 * G::NW),
+                     G::kLds, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.splits == 1) return (int)e;
   const int64_t n4 = a.M * a.N / 4;
@@ -467,17 +478,27 @@ int launch_form(const TunedGemmArgs& a, hipStream_t stream) {
                      stream, a);
   return (int)hipGetLastError();
 }
+template <bool A_TR, bool B_TR>
+int launch_form(const TunedGemmArgs& a, int shape, hipStream_t stream) {
+  switch (shape) {
+    case 0: return launch_shape<A_TR, B_TR, Tile256x256>(a, stream);
+    case 1: return launch_shape<A_TR, B_TR, Tile256x128>(a, stream);
+    case 2: return launch_shape<A_TR, B_TR, Tile128x128>(a, stream);
+    default: break;
+  }
+  if constexpr (A_TR) return -1;
+  else return launch_shape<A_TR, B_TR, Tile64x128>(a, stream);
+}
 
 }  // namespace
 
-// Where the few-rows kernel is the faster one.  A round of its workgroups (one per CU) takes
-// 0.22 us per 64-wide slice of k (4.4 us at K = 1024, 7 us at K = 2048), the tiled kernel and
-// the sum of its partials 28 to 32 us up to about 1000 rows whatever the shape (measured at
-// d_model 1024 and 2048; 500 rows: 9.0 against 31, 28 against 31).
+// Where the few-rows kernel is the faster one: a round of its workgroups (one per CU) takes
+// about 520 clocks per 64-wide slice of k and 2000 around them (4.4 us at K = 1024, 7 us at K =
+// 2048).  300 rows at K = 2048 and 700 at K = 1024 is where the tiled kernel takes over.
 bool skinny_takes(int64_t M, int64_t N, int64_t K) {
-  if (N % kSkinnyCols != 0 || K % kGBK != 0) return false;
+  if (N % kSkinnyCols != 0 || K % kSkinnyK != 0) return false;
   const int64_t wgs = ((M + kSkinnyRows - 1) / kSkinnyRows) * (N / kSkinnyCols);
-  return (wgs + 255) / 256 * (K / kGBK) <= 96;
+  return (double)((wgs + 255) / 256) * (520.0 * (K / kSkinnyK) + 2000) < plan_tiles(false, M, N, K).clocks;
 }
 
 bool gemm_bf16_supported(bool a_tr, bool b_tr, const void* A, int64_t lda, const void* B,
@@ -485,17 +506,19 @@ bool gemm_bf16_supported(bool a_tr, bool b_tr, const void* A, int64_t lda, const
   auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
   if (M < 1 || N < 8 || K < 1 || N % 8 != 0) return false;
   if (!al16(A) || !al16(B) || !al16(C) || lda % 8 != 0 || ldb % 8 != 0 || ldc % 4 != 0) return false;
-  // a row-form operand is read in whole 32-wide slices of k; a transposed one in whole
+  // a row-form operand is read in whole slices of k; a transposed one in whole
   // 8-wide groups of its row index
   if ((!a_tr || !b_tr) && K % kGBK != 0) return false;
+  if (lda > (1 << 22) || ldb > (1 << 22)) return false;   // lane offsets inside a tile are 32-bit
   if (a_tr && (M < 8 || M % 8 != 0)) return false;
   if (b_tr && N % 8 != 0) return false;
   return true;
 }
 
 size_t gemm_bf16_workspace_bytes(int64_t M, int64_t N, int64_t K) {
-  const SplitK sk = plan_split_k(M, N, K);
-  return sk.splits > 1 ? (size_t)sk.splits * M * N * sizeof(float) : 0;
+  const int s0 = plan_tiles(false, M, N, K).splits, s1 = plan_tiles(true, M, N, K).splits;
+  const int splits = s0 > s1 ? s0 : s1;
+  return splits > 1 ? (size_t)splits * M * N * sizeof(float) : 0;
 }
 
 int launch_gemm_bf16(bool a_tr, bool b_tr, const void* A, int64_t lda, const void* B, int64_t ldb,
@@ -507,19 +530,18 @@ int launch_gemm_bf16(bool a_tr, bool b_tr, const void* A, int64_t lda, const voi
   a.B = static_cast<const uint16_t*>(B);
   a.C = static_cast<uint16_t*>(C);
   a.M = M; a.N = N; a.K = K; a.lda = lda; a.ldb = ldb; a.ldc = ldc;
-  a.tiles_n = (N + kGTileN - 1) / kGTileN;
-  const SplitK sk = plan_split_k(M, N, K);
-  a.splits = sk.splits;
-  a.slices_per_split = sk.slices_per_split;
+  const GemmPlan plan = plan_tiles(a_tr, M, N, K);
+  a.tiles_n = 0; a.n_items = 0;
+  a.splits = plan.splits;
+  a.slices_per_split = plan.slices_per_split;
   a.P = static_cast<float*>(ws);
-  a.n_items = ((M + kGTileM - 1) / kGTileM) * a.tiles_n * a.splits;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (!a_tr && skinny_takes(M, N, K) && !accumulate)
     return b_tr ? launch_skinny<true>(a, st) : launch_skinny<false>(a, st);
   if (a.splits > 1 && !ws) return -1;
-  if (!a_tr && b_tr) return launch_form<false, true>(a, st);
-  if (!a_tr && !b_tr) return launch_form<false, false>(a, st);
-  if (a_tr && b_tr) return launch_form<true, true>(a, st);
+  if (!a_tr && b_tr) return launch_form<false, true>(a, plan.shape, st);
+  if (!a_tr && !b_tr) return launch_form<false, false>(a, plan.shape, st);
+  if (a_tr && b_tr) return launch_form<true, true>(a, plan.shape, st);
   return -1;   // transposed A with row-form B: no caller
 }
 
