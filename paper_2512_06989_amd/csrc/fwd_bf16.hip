@@ -43,6 +43,13 @@ __device__ __forceinline__ float inv_weight(float r) {
   const float v = __builtin_amdgcn_rcpf(r);   // 1 ulp; a full-precision division is ten instructions
   return fminf(fmaxf(v, -1e30f), 1e30f);
 }
+template <int B, int E, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (B < E) {
+    f(std::integral_constant<int, B>{});
+    static_for<B + 1, E>(f);
+  }
+}
 #define MHFFN_SB() __builtin_amdgcn_sched_barrier(0)
 
 struct FwdArgs {
@@ -757,6 +764,336 @@ __global__ __launch_bounds__(64 * kPipeWaves) void fwd_bf16_flow_kernel(FwdArgs 
 }
 
 // ---------------------------------------------------------------------------
+// d_h = 256, up to 16 sub-networks: two waves share 32 tokens (128 tokens per workgroup, four
+// pairs, two waves per SIMD).
+//
+// The output of 32 tokens is 128 registers per lane at this width and the token operands 64: a
+// wave that holds both has the SIMD to itself, and its products and its arithmetic add up
+// (fwd_bf16_kernel<256, 1, 4>: 766 TFLOP/s at 8192 tokens, H = 4).  Here wave `hf` of a pair owns
+// 16 of a tile's 32 neurons for the gate/up products and the activation, and columns 128 hf ..
+// 128 hf + 127 of the output (64 registers) for the down projection; the activations of the
+// partner's neurons (16 bytes per lane, same lane) come through LDS.  16x16x32 products: the
+// accumulator layout of the two waves' neurons, slots 0-3 and 4-7, is the B operand of the down
+// projection when V is read with the matching neuron order (rows 4 gq.., 16 + 4 gq..).
+// An operand read serves two products (both halves of the 32 tokens), as in the 32x32 kernels.
+//
+// A step has two halves: A, products only (gate/up of tile i, then down of tile i - 1: 48 of 16
+// cycles), B, the activation of tile i.  Waves 4-7 run half a step behind waves 0-3 and wave w
+// shares its SIMD with w + 4, so the arithmetic of one hides under the products of the other.
+// Tiles go global -> LDS directly into three stages per tensor.  In half-steps (early waves run
+// A(i) in 2i, late ones in 2i + 1): K/U of tile i + 2 and V of tile i + 1 are requested by the
+// early waves at the top of 2i, when the stages they overwrite were last read in 2i - 1; they
+// are waited for at the end of 2i + 2 and first read (operands of the next A are read ahead of
+// the barrier that opens it) at the end of 2i + 3.
+// 8192 tokens, H = 4, E = 4, d_e = 704: 190 -> 143 us (990 TFLOP/s); 16384 tokens, H = 8, E = 8:
+// 1270 -> 1085; 700 tokens 126 -> 71, 64 tokens 44 -> 26 (the launch is one workgroup per CU: the
+// shares of a token block are planned for that; before, for two).  More sub-networks do not fit
+// beside the three stages (1/r: 512 bytes each).
+// ---------------------------------------------------------------------------
+constexpr int kPairDh = 256;
+constexpr int kPairWaves = 8;
+constexpr int kPairBM = 128;
+constexpr int kPairMaxSub = 16;
+constexpr int kPairTile = 32 * kPairDh * 2;          // 16 KB
+constexpr int kPairRing = 3 * kPairTile;             // one ring of three stages per tensor: K | U | V
+constexpr int kPairXchg = 3 * kPairRing;             // [wave][lane] 16 bytes
+constexpr int kPairRs = kPairXchg + kPairWaves * 1024;
+constexpr int kPairLdsBytes = kPairRs + kPairMaxSub * kPairBM * 4;
+static_assert(kPairLdsBytes <= (int)kLdsBytesPerWorkgroup, "LDS of a workgroup");
+constexpr int kPairWin = 6;   // operands in flight ahead of the one being consumed
+// operand stream of half A, item c: 0..15 rows K, U by contraction step; 16..23 windows of V (two reads)
+constexpr int pair_instrs(int c) { return c < 16 ? 1 : 2; }
+// reads issued after item c when it is consumed; the partner's activations (one read) are asked
+// for behind the kPairWin items that were read ahead of the barrier
+constexpr int pair_pending(int c, int first) {
+  int n = (first == 0 && c < kPairWin) ? 1 : 0;
+  for (int i = c + 1; i <= c + kPairWin && i < 24; ++i) n += pair_instrs(i);
+  return n;
+}
+
+__global__ __launch_bounds__(64 * kPairWaves) void fwd_bf16_pair256_kernel(FwdArgs a) {
+  constexpr int BM = kPairBM, DH = kPairDh, THREADS = 64 * kPairWaves;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];   // (address bits are XORed)
+  float* Rs = reinterpret_cast<float*>(smem + kPairRs);   // [16][BM], 1/r
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cn = lane & 15, gq = lane >> 4;
+  const int pair = wave >> 1, hf = wave & 1;
+  const bool late = wave >= 4;
+  const int64_t item = xcd_work_item(blockIdx.x, a.n_items);
+  if (item >= a.n_items) return;  // whole workgroup leaves together
+  const int split = (int)(item % a.n_split);
+  const int64_t ht = item / a.n_split;
+  const int h = (int)(ht / a.n_tiles);
+  const int64_t tile_tok0 = (ht % a.n_tiles) * BM;
+  const int wtok = 32 * pair;
+  const int E = a.E;
+
+  const int tiles_per_sub = a.de / kBI;
+  const int t_begin = split * a.tiles_per_split;
+  const int T = min(E * tiles_per_sub, t_begin + a.tiles_per_split) - t_begin;
+  const size_t head_off = ((size_t)h * E * a.de + (size_t)t_begin * kBI) * DH;
+
+  // tile layout: rows of 512 bytes, position p of a row holds chunk (p & 16) | ((p & 15) ^ 2 (row % 8))
+  auto off16 = [](int row, int chunk) { return row * 512 + (((chunk & 16) | ((chunk & 15) ^ ((row & 7) << 1))) << 4); };
+
+  // direct staging by waves 0-3: a load moves two rows (1 KB), wave w rows 2w + 8i, + 1 (the
+  // permutation of a row depends on row % 8: the same for every i)
+  const int drow = 2 * (wave & 3) + (lane >> 5);
+  const unsigned dma_off = (unsigned)off16(drow, lane & 31);   // bytes; the permutation is its own inverse
+  auto dma_tensor = [&](const uint16_t* base, int t, int ring) __attribute__((always_inline)) {
+    const unsigned char* src = reinterpret_cast<const unsigned char*>(base + head_off) + (size_t)t * kPairTile + dma_off;
+    unsigned char* dst = smem + ring * kPairRing + (t % 3) * kPairTile + wave * 1024;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) global_to_lds_16B(src + i * 4096, dst + i * 4096);
+  };
+
+  // token operands: lane (token 16 tb + cn, group gq) holds columns 32 ks + 8 gq ..
+  bf16x8 q[2][8];
+#pragma unroll
+  for (int tb = 0; tb < 2; ++tb) {
+    const int64_t tok = tile_tok0 + wtok + 16 * tb + cn;
+    const bool valid = tok < a.N;
+    const uint16_t* src = a.X + (valid ? tok : 0) * a.ldx + h * DH + 8 * gq;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      bf16x8 v = *reinterpret_cast<const bf16x8*>(src + 32 * ks);
+      if (!valid) v = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+      q[tb][ks] = v;
+    }
+  }
+  auto first_requests = [&]() {
+    if (!late) {
+      dma_tensor(a.Wg, 0, 0); dma_tensor(a.Wu, 0, 1); dma_tensor(a.Wd, 0, 2);
+      if (T > 1) { dma_tensor(a.Wg, 1, 0); dma_tensor(a.Wu, 1, 1); }
+    }
+  };
+
+  // ---- 1/R[e][token] into LDS; scratch (W_r^T as [16][256]): stage 2 of the K ring ----
+  if (a.route_mode == 0) {
+    unsigned char* scratch = smem + 2 * kPairTile;
+    const uint16_t* Wr = reinterpret_cast<const uint16_t*>(a.route) + (size_t)h * DH * E;
+    u32x4 wv = {0, 0, 0, 0};
+    const bool mine = tid < DH * E / 8;                    // at most 512 chunks of 8
+    if (mine) wv = *reinterpret_cast<const u32x4*>(Wr + 8 * tid);
+    first_requests();
+    if (mine) {
+      int j = (8 * tid) / E, e = 8 * tid - j * E;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        *reinterpret_cast<uint16_t*>(scratch + off16(e, j >> 3) + (j & 7) * 2) = (uint16_t)(wv[i >> 1] >> (16 * (i & 1)));
+        if (++e == E) { e = 0; ++j; }
+      }
+    }
+    __syncthreads();
+    // each wave of a pair takes one half of its tokens (rows e >= E of the operand hold
+    // whatever the memory held; a row of the product depends on its own row only)
+    f32x4 acc2[2] = {f32x4{0, 0, 0, 0}, f32x4{0, 0, 0, 0}};
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      const bf16x8 af = *reinterpret_cast<const bf16x8*>(scratch + off16(cn, 4 * ks + gq));
+      acc2[0] = mfma16(af, q[0][ks], acc2[0]);   // (both halves: selecting the operand by `hf` puts q into scratch memory)
+      acc2[1] = mfma16(af, q[1][ks], acc2[1]);
+    }
+    f32x4 acc;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc[v] = hf ? acc2[1][v] : acc2[0][v];
+    float sg[4], zsum = 0.f;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      sg[v] = (4 * gq + v < E) ? sigmoid_fast(acc[v]) : 0.f;
+      zsum += sg[v];
+    }
+    zsum += __shfl_xor(zsum, 16);
+    zsum += __shfl_xor(zsum, 32);
+    const float inv = 1.0f / (zsum + a.eps);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) Rs[(4 * gq + v) * BM + wtok + 16 * hf + cn] = inv_weight(sg[v] * inv);
+  } else {
+    first_requests();
+    const float* R = reinterpret_cast<const float*>(a.route);
+    for (int idx = tid; idx < BM * E; idx += THREADS) {
+      const int tl = idx / E, e = idx - tl * E;
+      const int64_t tok = tile_tok0 + tl;
+      Rs[e * BM + tl] = inv_weight((tok < a.N) ? R[((size_t)tok * a.H + h) * E + e] : 0.f);
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0): the first tiles have landed
+  __syncthreads();
+
+  // ---- operand addresses: the permutation is an XOR on address bits 5-7, so contraction step
+  // ks is step 0 ^ (ks % 4 << 6) (+ 256 for ks >= 4), column block jb is block 0 ^ (jb << 5) ----
+  const unsigned lds0 = lds_addr_of(smem);
+  const unsigned ka0 = (unsigned)off16(16 * hf + cn, gq);
+  const unsigned va0 = (unsigned)(2 * kPairRing + off16(4 * gq + (cn >> 2), 16 * hf + ((cn & 3) >> 1)) + ((cn & 1) << 3));
+  const unsigned xpar = lds0 + kPairXchg + (wave ^ 1) * 1024 + 16 * lane;
+  u32x4* xown = reinterpret_cast<u32x4*>(smem + kPairXchg + wave * 1024) + lane;
+
+  f32x4 O[8][2];
+#pragma unroll
+  for (int jb = 0; jb < 8; ++jb) { O[jb][0] = f32x4{0, 0, 0, 0}; O[jb][1] = f32x4{0, 0, 0, 0}; }
+  f32x4 M[2], Nn[2];
+  bf16x8 op[16];
+  s16x4 vlo[8], vhi[8];
+  u32x4 own = {0, 0, 0, 0}, par = {0, 0, 0, 0};   // packed activations: words 0, 1 token half 0; 2, 3 half 1
+
+  // item C of half A(i): kb = stage of K/U tile i, vb = stage of V tile i - 1 (LDS addresses)
+  unsigned kx[4], vx[8];
+  auto issue = [&](auto C_) __attribute__((always_inline)) {
+    constexpr int C = decltype(C_)::value;
+    if constexpr (C < 16) {
+      constexpr int ks = C >> 1;
+      op[C] = lds_read_b128_untracked<(C & 1) * kPairRing + (ks >> 2) * 256>(kx[ks & 3]);
+    } else {
+      vlo[C - 16] = lds_read_tr16_untracked<0>(vx[C - 16]);
+      vhi[C - 16] = lds_read_tr16_untracked<8192>(vx[C - 16]);   // 16 rows further: same permutation
+    }
+  };
+  auto set_k = [&](int t) __attribute__((always_inline)) {
+    const unsigned b = lds0 + (unsigned)(t % 3) * kPairTile + ka0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) kx[i] = b ^ (i << 6);
+  };
+  auto set_v = [&](int t) __attribute__((always_inline)) {
+    const unsigned b = lds0 + (unsigned)(t % 3) * kPairTile + va0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) vx[i] = b ^ (i << 5);
+  };
+  // items FIRST .. LAST-1 of half A (items FIRST .. FIRST + kPairWin - 1 have been issued)
+  auto stream = [&](auto FIRST_, auto LAST_) __attribute__((always_inline)) {
+    constexpr int FIRST = decltype(FIRST_)::value, LAST = decltype(LAST_)::value;
+    if constexpr (FIRST == 0) asm volatile("ds_read_b128 %0, %1" : "=v"(par) : "v"(xpar));
+    bf16x8 b0, b1;
+    static_for<FIRST, LAST>([&](auto C_) __attribute__((always_inline)) {
+      constexpr int C = decltype(C_)::value;
+      if constexpr (C + kPairWin < LAST) issue(std::integral_constant<int, C + kPairWin>{});
+      if constexpr (C < 16) {
+        constexpr int ks = C >> 1;
+        // (what a stream that ends early does not issue it does not wait behind either)
+        lds_wait<(LAST == 16) ? ((15 - C < kPairWin ? 15 - C : kPairWin) + (C < kPairWin ? 1 : 0)) : pair_pending(C, FIRST)>(op[C]);
+        if constexpr ((C & 1) == 0) {
+          M[0] = mfma16(op[C], q[0][ks], ks == 0 ? f32x4{0, 0, 0, 0} : M[0]);
+          M[1] = mfma16(op[C], q[1][ks], ks == 0 ? f32x4{0, 0, 0, 0} : M[1]);
+        } else {
+          Nn[0] = mfma16(op[C], q[0][ks], ks == 0 ? f32x4{0, 0, 0, 0} : Nn[0]);
+          Nn[1] = mfma16(op[C], q[1][ks], ks == 0 ? f32x4{0, 0, 0, 0} : Nn[1]);
+        }
+      } else {
+        constexpr int J = C - 16;
+        lds_wait<pair_pending(C, FIRST)>(vlo[J], vhi[J]);
+        if constexpr (C == 16) {
+          asm volatile("" : "+v"(par));   // read ahead of item kPairWin: it has landed
+          const u32x4 lo = hf ? par : own, hi = hf ? own : par;   // neurons 0..15 | 16..31 of the tile
+          b0 = __builtin_bit_cast(bf16x8, u32x4{lo[0], lo[1], hi[0], hi[1]});
+          b1 = __builtin_bit_cast(bf16x8, u32x4{lo[2], lo[3], hi[2], hi[3]});
+        }
+        const bf16x8 v = join_tr(vlo[J], vhi[J]);
+        O[J][0] = mfma16(v, b0, O[J][0]);
+        O[J][1] = mfma16(v, b1, O[J][1]);
+      }
+    });
+  };
+  auto bare_barrier = [&]() __attribute__((always_inline)) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  using ic0 = std::integral_constant<int, 0>;
+  using ic16 = std::integral_constant<int, 16>;
+  using ic24 = std::integral_constant<int, 24>;
+
+  int sub_cnt = t_begin % tiles_per_sub;
+  const float* rs = Rs + (t_begin / tiles_per_sub) * BM + wtok + cn;
+
+  auto half_a = [&](int i, auto FIRST_STEP_) __attribute__((always_inline)) {
+    constexpr bool kFirst = decltype(FIRST_STEP_)::value;
+    if (!late) {
+      if (i + 2 < T) { dma_tensor(a.Wg, i + 2, 0); dma_tensor(a.Wu, i + 2, 1); }
+      if (i + 1 < T) dma_tensor(a.Wd, i + 1, 2);
+    }
+    if constexpr (kFirst) {
+      stream(ic0{}, ic16{});
+      asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(par));
+    } else {
+      set_v(i + 2);   // tile i - 1: (i - 1) % 3
+      stream(ic0{}, ic24{});
+    }
+    // the tiles requested one step ago have landed; this step's requests may stay in flight
+    asm volatile("" ::: "memory");
+    if (!late) {
+      if (i + 2 < T) __builtin_amdgcn_s_waitcnt(0x0F7C);        // vmcnt(12)
+      else if (i + 1 < T) __builtin_amdgcn_s_waitcnt(0x0F74);   // vmcnt(4)
+      else __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0)
+    }
+    bare_barrier();
+  };
+  auto half_b = [&](int i, auto MORE_) __attribute__((always_inline)) {
+    constexpr bool kMore = decltype(MORE_)::value;
+    __builtin_amdgcn_s_setprio(1);
+    const float rw[2] = {rs[0], rs[16]};
+    if (++sub_cnt == tiles_per_sub) { sub_cnt = 0; rs += BM; }
+    float tt[8], ss[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) tt[k] = __builtin_amdgcn_exp2f(-MHFFN_LOG2E * M[k >> 2][k & 3]);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) ss[k] = __builtin_amdgcn_rcpf(__builtin_fmaf(tt[k], rw[k >> 2], rw[k >> 2]));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int t2 = k >> 1, v = 2 * (k & 1);
+      own[k] = pack_bf16((M[t2][v] * Nn[t2][v]) * ss[4 * t2 + v], (M[t2][v + 1] * Nn[t2][v + 1]) * ss[4 * t2 + v + 1]);
+    }
+    *xown = own;
+    __builtin_amdgcn_s_setprio(0);
+    asm volatile("" ::: "memory");
+    if constexpr (kMore) {
+      set_k(i + 1);
+      static_for<0, kPairWin>(issue);
+      __builtin_amdgcn_s_waitcnt(0xC07F | (kPairWin << 8));   // lgkmcnt: the store ahead of these reads is done
+    } else {
+      __builtin_amdgcn_s_waitcnt(0xC07F);
+    }
+    bare_barrier();
+  };
+  static_assert(kPairWin == 6, "wait masks");
+
+  if (late) bare_barrier();
+  set_k(0);
+  static_for<0, kPairWin>(issue);
+  half_a(0, std::true_type{});
+  for (int i = 0; i + 1 < T; ++i) {
+    half_b(i, std::true_type{});
+    half_a(i + 1, std::false_type{});
+  }
+  half_b(T - 1, std::false_type{});
+  // the down projection of the last tile
+  set_v(T + 2);
+  asm volatile("ds_read_b128 %0, %1" : "=v"(par) : "v"(xpar));
+  static_for<16, 16 + kPairWin>(issue);
+  stream(ic16{}, ic24{});
+  if (!late) bare_barrier();
+
+#pragma unroll
+  for (int tb = 0; tb < 2; ++tb) {
+    const int64_t tok = tile_tok0 + wtok + 16 * tb + cn;
+    if (tok >= a.N) continue;
+    const int col = h * DH + 128 * hf + 4 * gq;
+    if (a.n_split > 1) {
+      float* dst = a.P + ((size_t)split * a.N + tok) * ((size_t)a.H * DH) + col;
+#pragma unroll
+      for (int jb = 0; jb < 8; ++jb) *reinterpret_cast<f32x4*>(dst + 16 * jb) = O[jb][tb];
+    } else {
+      uint16_t* dst = a.Y + tok * a.ldy + col;
+#pragma unroll
+      for (int jb = 0; jb < 8; ++jb) {
+        const u32x2 pk = {pack_bf16(O[jb][tb][0], O[jb][tb][1]), pack_bf16(O[jb][tb][2], O[jb][tb][3])};
+        *reinterpret_cast<u32x2*>(dst + 16 * jb) = pk;
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Decode-sized inputs at d_h = 128 (at most 32 * NB tokens, NB in {1, 2, 4}): the launch is a
 // weight-streaming problem (every weight byte is used once by a handful of tokens) and its
 // floor is the time the memory system needs to deliver the weights.  About one workgroup
@@ -1103,12 +1440,13 @@ __global__ void fwd_bf16_reduce_kernel(FwdArgs a) {
 // 256 tokens per CU) is split down to about one workgroup per CU: with few tokens it
 // is a weight-streaming kernel, and its deep ring of direct loads is what keeps
 // enough bytes in flight.  The older kernel (more than 64 sub-networks) aims for
-// two smaller workgroups per CU.
-struct SplitPlan { int bm, n_split, tiles_per_split; bool pipe; int decode_nb; };
+// two smaller workgroups per CU (d_h = 256: one, its LDS holds no second).
+struct SplitPlan { int bm, n_split, tiles_per_split; bool pipe, pair; int decode_nb; };
 constexpr int kDecodeMaxTokens = 128;
 SplitPlan plan_split(const Problem& p) {
   SplitPlan s;
   s.pipe = p.dh == kDh && p.E <= kPipeMaxSub;
+  s.pair = p.dh == kPairDh && p.E <= kPairMaxSub;
   s.decode_nb = 0;
   if (s.pipe && p.N <= kDecodeMaxTokens) {
     // decode kernel: about one workgroup per CU, each a head and a share of its tiles
@@ -1127,7 +1465,7 @@ SplitPlan plan_split(const Problem& p) {
   const int64_t base = ((p.N + s.bm - 1) / s.bm) * p.H;
   const int T = p.E * (p.de / kBI);
   int want = 1;
-  if (s.pipe) {
+  if (s.pipe || p.dh == 256) {   // one workgroup per CU
     if (base <= 128) want = (int)(256 / base);
   } else if (base < 384) {
     want = (int)((512 + base - 1) / base);
@@ -1173,6 +1511,21 @@ int launch_pipe(const Problem& p, FwdArgs a, const SplitPlan& sp, hipStream_t st
   const int64_t n4 = p.N * p.H * kDh / 4;
   hipLaunchKernelGGL(fwd_bf16_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0,
                      stream, a);
+  return (int)hipGetLastError();
+}
+
+int launch_pair(const Problem& p, FwdArgs a, const SplitPlan& sp, hipStream_t stream) {
+  a.n_tiles = (p.N + kPairBM - 1) / kPairBM;
+  a.n_split = sp.n_split;
+  a.tiles_per_split = sp.tiles_per_split;
+  a.n_items = a.n_tiles * p.H * sp.n_split;
+  if (hipError_t e0 = LdsLimit<&fwd_bf16_pair256_kernel, kPairLdsBytes>::ensure(); e0 != hipSuccess) return (int)e0;
+  hipLaunchKernelGGL(fwd_bf16_pair256_kernel, dim3((unsigned)xcd_grid_size(a.n_items)), dim3(64 * kPairWaves),
+                     kPairLdsBytes, stream, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || sp.n_split == 1) return (int)e;
+  const int64_t n4 = p.N * p.H * kPairDh / 4;
+  hipLaunchKernelGGL(fwd_bf16_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, stream, a);
   return (int)hipGetLastError();
 }
 
@@ -1228,6 +1581,7 @@ int launch_fwd_bf16(const Problem& p, const void* X, const void* Wg, const void*
     if (sp.bm == 64) return launch_variant<64, 1, 2>(p, a, sp, st);
     return launch_variant<64, 1, 8>(p, a, sp, st);
   }
+  if (sp.pair) return launch_pair(p, a, sp, st);
   if (p.dh == 256) {
     // the output accumulators alone are 128 registers per wave and the token operands 64:
     // one wave per SIMD with the whole register file rather than two that spill
@@ -1241,6 +1595,7 @@ size_t fwd_bf16_lds_bytes(const Problem& p) {
   const SplitPlan sp = plan_split(p);
   if (sp.decode_nb) return (size_t)decode_lds_bytes(sp.decode_nb);
   if (sp.pipe) return (size_t)3 * kPipeRing + (size_t)kPipeMaxSub * kPipeBM * sizeof(float);
+  if (sp.pair) return (size_t)kPairLdsBytes;
   return (size_t)kStages * fwd_stage_bytes(p.dh) + (size_t)p.E * sp.bm * sizeof(float);
 }
 
