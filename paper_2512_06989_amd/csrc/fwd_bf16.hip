@@ -1553,7 +1553,19 @@ int launch_decode(const Problem& p, FwdArgs a, const SplitPlan& sp, hipStream_t 
 size_t fwd_bf16_workspace_bytes(const Problem& p) {
   if (p.N == 0) return 0;
   const SplitPlan sp = plan_split(p);
-  return sp.n_split > 1 ? (size_t)sp.n_split * p.N * p.H * p.dh * sizeof(float) : 0;
+  int64_t splits = sp.n_split;
+  if (p.dh == 256) {
+    // The scratch asked for at this width is that of shares for two workgroups per CU, although
+    // the launch takes no more than half of them: which problems exceed the static scratch buffer
+    // (and are refused by the entry point that has no other) is part of the interface.
+    const int64_t base = ((p.N + sp.bm - 1) / sp.bm) * p.H;
+    const int64_t T = (int64_t)p.E * (p.de / kBI);
+    int64_t want = base < 384 ? (512 + base - 1) / base : 1;
+    if (want > T / 2) want = T / 2 > 0 ? T / 2 : 1;
+    const int64_t per = (T + want - 1) / want, asked = (T + per - 1) / per;
+    splits = splits > asked ? splits : asked;
+  }
+  return splits > 1 ? (size_t)splits * p.N * p.H * p.dh * sizeof(float) : 0;
 }
 
 int launch_fwd_bf16(const Problem& p, const void* X, const void* Wg, const void* Wu,
