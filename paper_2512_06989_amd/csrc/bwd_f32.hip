@@ -557,8 +557,10 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 size_t tok_lds_bytes(const Problem& p, int nw) {
   return sizeof(float) * (3 * (size_t)kF32Rows * f32_ld(f32_padded_width(p.dh)) + 2 * (size_t)p.E * 16 * nw);
 }
-// four waves (64 tokens) per workgroup; two where the gating rows of 64 tokens do not fit
-int tok_block_waves(const Problem& p) { return tok_lds_bytes(p, 4) <= kLdsBytesPerWorkgroup ? 4 : 2; }
+// four waves (64 tokens) per workgroup; two, or one, where the gating rows of more tokens do not fit
+int tok_block_waves(const Problem& p) {
+  return tok_lds_bytes(p, 4) <= kLdsBytesPerWorkgroup ? 4 : tok_lds_bytes(p, 2) <= kLdsBytesPerWorkgroup ? 2 : 1;
+}
 
 size_t weight_count(const Problem& p) { return (size_t)p.H * p.E * p.de * p.dh; }
 
@@ -601,7 +603,14 @@ int launch_tok(const Problem& p, BwdF32Args a, hipStream_t stream) {
 template <int DHP>
 int launch_width(const Problem& p, BwdF32Args a, bool weights, hipStream_t stream) {
   // token-major kernel (always: it also produces R for the weight-major kernel)
-  const int rc = tok_block_waves(p) == 4 ? launch_tok<DHP, 4>(p, a, stream) : launch_tok<DHP, 2>(p, a, stream);
+  int rc;
+  switch (tok_block_waves(p)) {
+    case 4: rc = launch_tok<DHP, 4>(p, a, stream); break;
+    case 2: rc = launch_tok<DHP, 2>(p, a, stream); break;
+    default:   // d_h below 30 with about 600 sub-networks: all that the entry point's limit lets through
+      if constexpr (DHP == 64) rc = launch_tok<DHP, 1>(p, a, stream);
+      else rc = (int)hipErrorInvalidValue;
+  }
   if (rc || !weights) return rc;
   if (hipError_t e0 = LdsLimit<&bwd_f32_wgt_kernel<DHP>, (int)kLdsBytesPerWorkgroup>::ensure(); e0 != hipSuccess)
     return (int)e0;

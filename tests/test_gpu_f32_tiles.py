@@ -18,6 +18,7 @@ ARGS = ("X", "W_gate", "W_up", "W_down")
     (64, 2, 100, 4, 33, False), (65, 1, 192, 3, 20, True), (63, 2, 196, 2, 40, False),
     (700, 2, 128, 6, 48, True),      # shares of the sub-networks, token segments, weights given
     (513, 5, 128, 7, 100, False), (300, 1, 256, 17, 24, False),
+    (20, 1, 4, 614, 1, False),       # nor those of 32: 16-token blocks, the most sub-networks the backward takes
     (40, 1, 64, 400, 2, False),      # gating rows of 64 tokens do not fit: 32-token blocks (backward)
     (30, 1, 64, 700, 1, None)])      # the same for the forward alone
 def test_f32_tile_edges(N, H, dh, E, de, route_weights):
