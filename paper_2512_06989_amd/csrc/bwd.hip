@@ -2403,27 +2403,38 @@ __global__ __launch_bounds__(kW2Threads) void bwd_wgt256_kernel(BwdArgs a) {
 // dW_r[h][j][e] = sum_tok q[tok][j] dp[tok][e]: partial sums per token split,
 // then a fixed-order reduction (deterministic).
 // ---------------------------------------------------------------------------
-constexpr int kRouteSplit = 16;                 // workgroups per head
-constexpr int kRouteParts = kRouteSplit * 4;    // one partial per wave
+constexpr int kRouteParts = 64;                 // most workgroups per head; one partial each
 constexpr int kRouteMaxSub = kTokMaxSub;
 
 // D[j][e] += sum_tok q^T[j][tok] dp[tok][e] on the MFMA: the A operand is the
 // transposing LDS read of a [32 tok][d_h] tile of X, the B operand (contraction
 // slot s <-> token 16*t2 + 8*(s/4) + 4g + s%4, column e) comes straight from
-// the [H][E][N] dp array.  Each wave walks its own token blocks and leaves its
-// own partial [128][E] in the workspace.
+// the [H][E][N] dp array.  Each wave walks its own token blocks; the partials of a workgroup's
+// four waves are added up in wave order through LDS and leave as one [d_h][E].
+// Bound: a wave waits one memory latency per block, so what counts is waves in flight, and the
+// partials: about two workgroups per CU whatever the number of heads, against 16 per head with
+// a partial per wave and dp read word by word.  16384 tokens, H = 16, E = 44: 38 -> 32 us and
+// half the partials; H = 8, E = 7: 16.4 -> 12.5; 8192 tokens, H = 4, d_h = 256: 13.1 -> 10.8.
+inline int route_splits(int64_t N, int H) {
+  const int64_t most = ((N + 31) / 32 + 3) / 4;    // a block for every wave
+  int64_t s = 512 / H < 1 ? 1 : 512 / H;
+  if (s > kRouteParts) s = kRouteParts;
+  return (int)(s < most ? s : most);
+}
 template <int DH, int EB>
 __global__ __launch_bounds__(256) void bwd_route_partial_kernel(BwdArgs a) {
   constexpr int JB = DH / 32, CPR = DH / 8, kTileBytes = 32 * DH * 2;
-  __shared__ __attribute__((aligned(16))) unsigned char tiles[4 * kTileBytes];
+  constexpr int kSumBytes = 4 * EB * 4096;        // [wave][eb][register][lane] of one 32-row output tile
+  __shared__ __attribute__((aligned(16))) unsigned char tiles[4 * kTileBytes > kSumBytes ? 4 * kTileBytes : kSumBytes];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 31, g = lane >> 5;
   const int h = blockIdx.x;
-  const int part = blockIdx.y * 4 + wave;
+  const int part = blockIdx.y * 4 + wave, parts = a.n_split * 4;
   const int64_t N = a.N;
   const int E = a.E;
   const int64_t nb = (N + 31) / 32;
-  const int64_t iters = (nb + kRouteParts - 1) / kRouteParts;  // same for every wave
+  const int64_t iters = (nb + parts - 1) / parts;  // same for every wave
+  const bool quads = (N & 3) == 0;                // rows of dp start on 16 bytes
   const float* DPh = a.DPws + (size_t)h * E * N;
   unsigned char* tile = tiles + wave * kTileBytes;
   f32x16 acc[EB][JB];
@@ -2438,13 +2449,28 @@ __global__ __launch_bounds__(256) void bwd_route_partial_kernel(BwdArgs a) {
   u32x4 xv[XC];
   float dv[EB][2][8];
   auto request = [&](int64_t it) {
-    const int64_t tok0 = (it * kRouteParts + part) * 32;   // may lie beyond N: then everything loaded is zero
+    const int64_t tok0 = (it * parts + part) * 32;   // may lie beyond N: then everything loaded is zero
 #pragma unroll
     for (int i = 0; i < XC; ++i) {
       const int chunk = lane + 64 * i;
       const int64_t t = tok0 + chunk / CPR;
       xv[i] = u32x4{0, 0, 0, 0};
       if (t < N) xv[i] = *reinterpret_cast<const u32x4*>(a.X + t * a.ldx + h * DH + (chunk % CPR) * 8);
+    }
+    if (quads) {   // a quad of tokens is inside or outside as a whole
+#pragma unroll
+      for (int eb = 0; eb < EB; ++eb) {
+        const int e = 32 * eb + r;
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const int64_t t = tok0 + 8 * q4 + 4 * g;
+          f32x4 v = {0.f, 0.f, 0.f, 0.f};
+          if (e < E && t < N) v = *reinterpret_cast<const f32x4*>(DPh + (size_t)e * N + t);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) dv[eb][q4 >> 1][4 * (q4 & 1) + i] = v[i];
+        }
+      }
+      return;
     }
 #pragma unroll
     for (int eb = 0; eb < EB; ++eb) {
@@ -2486,18 +2512,23 @@ __global__ __launch_bounds__(256) void bwd_route_partial_kernel(BwdArgs a) {
       }
     }
   }
-  float* out = a.WRws + ((size_t)h * kRouteParts + part) * DH * E;
+  float* out = a.WRws + ((size_t)h * a.n_split + blockIdx.y) * DH * E;
+  float* sums = reinterpret_cast<float*>(tiles);
 #pragma unroll
-  for (int eb = 0; eb < EB; ++eb) {
-    const int e = 32 * eb + r;
-    if (e < E) {
+  for (int jb = 0; jb < JB; ++jb) {
+    __syncthreads();   // the tiles, or the sums of the tile before, have been read
 #pragma unroll
-      for (int jb = 0; jb < JB; ++jb)
+    for (int eb = 0; eb < EB; ++eb)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int j = 32 * jb + 8 * (v / 4) + 4 * g + (v % 4);
-          out[j * E + e] = acc[eb][jb][v];
-        }
+      for (int v = 0; v < 16; ++v) sums[((wave * EB + eb) * 16 + v) * 64 + lane] = acc[eb][jb][v];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4 * EB; ++k) {   // wave w: registers w, w + 4, ..
+      const int ev = 4 * k + wave, e = 32 * (ev >> 4) + r, v = ev & 15;
+      float sum = sums[ev * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < 4; ++w) sum += sums[(w * EB * 16 + ev) * 64 + lane];
+      if (e < E) out[(32 * jb + 8 * (v >> 2) + 4 * g + (v & 3)) * E + e] = sum;
     }
   }
 }
@@ -2654,7 +2685,7 @@ int launch_wgt64(const Problem& p, BwdArgs a, hipStream_t stream) {
 
 template <int DH>
 int launch_route(const Problem& p, const BwdArgs& a, hipStream_t stream) {
-  const dim3 rgrid(p.H, kRouteSplit);
+  const dim3 rgrid(p.H, a.n_split);
   if (p.E <= 32) hipLaunchKernelGGL((bwd_route_partial_kernel<DH, 1>), rgrid, dim3(256), 0, stream, a);
   else if (p.E <= 64) hipLaunchKernelGGL((bwd_route_partial_kernel<DH, 2>), rgrid, dim3(256), 0, stream, a);
   else if constexpr (DH <= 128) hipLaunchKernelGGL((bwd_route_partial_kernel<DH, 3>), rgrid, dim3(256), 0, stream, a);
@@ -2755,7 +2786,7 @@ int launch_bwd(const Problem& p, int dtype, const void* X, const void* Wg, const
   a.gpx = 0; a.full_px = 0; a.n_groups = 0;
   a.N = p.N; a.ldx = p.ldx; a.ldy = p.ldy;
   a.H = p.H; a.E = p.E; a.de = p.de; a.dh = p.dh; a.route_mode = p.route_mode; a.eps = p.eps;
-  a.n_split = kRouteParts;
+  a.n_split = route_splits(p.N, p.H);
 
   // token-major kernel (always: it also produces R for the weight-major kernel)
   int rc;
