@@ -245,7 +245,12 @@ __global__ __launch_bounds__(64 * G::NW, G::BM == 256 ? 2 : 4) void gemm_bf16_ke
     slice(kt, stage * G::kStage, next * G::kStage);
     stage = next;
   }
-  __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): the reads issued for a slice that never comes
+  // the reads issued for a slice that never comes: their registers stay taken until they have landed
+  static_for<0, kWin>([&](auto C_) {
+    constexpr int c = decltype(C_)::value;
+    if constexpr ((c % OPS < IN) ? B_TR : A_TR) lds_wait<0>(lo[c], hi[c]);
+    else lds_wait<0>(full[c]);
+  });
 
   // ---- store: lane = row m, registers = four consecutive n per group ----------------------
   if (a.splits > 1 || a.accumulate) {
