@@ -1156,6 +1156,7 @@ __global__ __launch_bounds__(kW16Threads) void bwd_wgt16_kernel(BwdArgs a) {
     constexpr int SO = S * kTileBytes, SN = SN1 * kTileBytes;   // tile offsets inside a ring
     const bool more2 = (b + 2 < b1), more3 = (b + 3 < b1);
     if (b == nb - 1) {   // rows past N were read from row N-1: give them r = 0
+      lds_wait<4>(rvc[0], rvc[1]);   // (r is in flight, ahead of the four reads of opc)
 #pragma unroll
       for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
