@@ -10,6 +10,7 @@
 //   None            where an argument is not what the kernels assume: mhffn.py then runs its
 //                   own checks, which say what is wrong.
 // Nothing is kept between calls.
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/ATen.h>
@@ -126,18 +127,18 @@ long integer(PyObject* o) {
 
 PyObject* status(int rc) { return PyLong_FromLong(rc); }
 
-// Runs `body`, which throws Refused for None and anything else as a Python exception
+// Runs `body`, which throws Refused for None; any other exception becomes the Python exception
+// that torch itself raises for it (a failed allocation: torch.OutOfMemoryError)
 template <typename F>
 PyObject* guarded(F&& body) {
+  HANDLE_TH_ERRORS
   try {
     return body();
   } catch (const Refused&) {
     PyErr_Clear();
     Py_RETURN_NONE;
-  } catch (const std::exception& e) {
-    if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, e.what());
-    return nullptr;
   }
+  END_HANDLE_TH_ERRORS
 }
 
 // Named outputs of a call: a copy of the caller's dict (or an empty one)
