@@ -226,8 +226,10 @@ __global__ void fwd_f32_reduce_kernel(F32Args a) {
 size_t lds_bytes(const Problem& p, int nw) {
   return sizeof(float) * (3 * (size_t)kF32Rows * f32_ld(f32_padded_width(p.dh)) + (size_t)p.E * 16 * nw);
 }
-// four waves (64 tokens) per workgroup; two where the gating weights of 64 tokens do not fit
-int block_waves(const Problem& p) { return lds_bytes(p, 4) <= kLdsBytesPerWorkgroup ? 4 : 2; }
+// four waves (64 tokens) per workgroup; two, or one, where the gating weights of more tokens do not fit
+int block_waves(const Problem& p) {
+  return lds_bytes(p, 4) <= kLdsBytesPerWorkgroup ? 4 : lds_bytes(p, 2) <= kLdsBytesPerWorkgroup ? 2 : 1;
+}
 
 int64_t tiles_of(const Problem& p) { return (int64_t)p.E * ((p.de + kF32Rows - 1) / kF32Rows); }
 
@@ -272,7 +274,16 @@ int launch_width(const Problem& p, const F32Args& a, hipStream_t stream) {
 
 }  // namespace
 
-size_t fwd_f32_lds_bytes(const Problem& p) { return lds_bytes(p, block_waves(p)); }
+// What the entry point takes: the tiles of a 32-token block, or, at d_h = 4 .. 16, unpadded rows of
+// 32 neurons and of 32 tokens beside the gating weights of 32 tokens (up to 1229 sub-networks
+// where the padded tiles leave room for 1178; those run as 16-token blocks).  The limit is part
+// of the interface and stays where it is.
+size_t fwd_f32_lds_bytes(const Problem& p) {
+  const size_t dh = p.dh;
+  const size_t narrow = sizeof(float) * (2 * 32 * dh + 2 * 32 * (dh + 1) + 32 * 33 + 32 * (size_t)p.E);
+  const size_t tiles = lds_bytes(p, 2);
+  return tiles < narrow ? tiles : narrow;
+}
 
 size_t fwd_f32_workspace_bytes(const Problem& p) {
   if (p.N == 0) return 0;
@@ -297,7 +308,11 @@ int launch_fwd_f32(const Problem& p, const void* X, const void* Wg, const void* 
   a.tiles_per_split = (int)((tiles_of(p) + a.n_split - 1) / a.n_split);
   a.n_tiles = 0; a.n_items = 0;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  return block_waves(p) == 4 ? launch_width<4>(p, a, st) : launch_width<2>(p, a, st);
+  switch (block_waves(p)) {
+    case 4: return launch_width<4>(p, a, st);
+    case 2: return launch_width<2>(p, a, st);
+    default: return launch<64, 1>(p, a, st);   // d_h <= 16 is all that the entry point's limit lets through
+  }
 }
 
 }  // namespace mhffn

@@ -183,3 +183,12 @@ def test_module_entry_points_validate_before_launching():
     assert lib.mhffn_module_forward(ctypes.byref(desc(d_head=96)), *fwd_args, None, 0, None) == 3
     # empty batch: nothing to launch in the forward
     assert lib.mhffn_module_forward(ctypes.byref(desc(n_tokens=0)), *fwd_args, None, 0, None) == 0
+
+
+@pytest.mark.parametrize("d_head,most", [(4, 1229), (8, 1213), (12, 1197), (16, 1181), (20, 1178), (64, 1178),
+                                         (128, 1082), (256, 890)])
+def test_most_sub_networks_of_the_fp32_forward(d_head, most):
+    """An empty batch passes exactly where the shape is taken."""
+    shape = dict(dtype=mhffn.F32, n_tokens=0, d_head=d_head, d_sub=1)
+    assert fwd(desc(n_sub=most, **shape)) == 0
+    assert fwd(desc(n_sub=most + 1, **shape)) == 3

@@ -20,7 +20,8 @@ ARGS = ("X", "W_gate", "W_up", "W_down")
     (513, 5, 128, 7, 100, False), (300, 1, 256, 17, 24, False),
     (20, 1, 4, 614, 1, False),       # nor those of 32: 16-token blocks, the most sub-networks the backward takes
     (40, 1, 64, 400, 2, False),      # gating rows of 64 tokens do not fit: 32-token blocks (backward)
-    (30, 1, 64, 700, 1, None)])      # the same for the forward alone
+    (30, 1, 64, 700, 1, None),       # the same for the forward alone
+    (20, 2, 4, 1229, 1, None), (33, 1, 16, 1181, 2, None)])   # nor those of 32: the most the forward takes
 def test_f32_tile_edges(N, H, dh, E, de, route_weights):
     import torch
     w = inputs.Workload("f32_edges", N, H, dh, E, de, "f32", w_std=0.1, route_scale=2.0, backward=True)
