@@ -114,7 +114,7 @@ typedef struct {
 
 /* Bytes of caller-provided scratch needed by `op` (an mhffn_op) for `desc`.
  * Returns 0 for an invalid descriptor as well; validate with the entry point.
- * For MHFFN_OP_FORWARD this is 0 whenever the token tiles alone give the chip
+ * For MHFFN_OP_FORWARD in bf16 this is 0 whenever the token tiles alone give the chip
  * enough workgroups (d_head = 128 with up to 64 sub-networks: more than 128
  * tiles of 256 tokens x heads, i.e. ceil(n_tokens / 256) * n_heads > 128; the
  * other kernels: at least 384 tiles): the fused forward then touches nothing
@@ -124,8 +124,9 @@ typedef struct {
  * workgroups per token tile and their fp32 partial outputs, n_split * N *
  * d_model * 4 bytes (a few output-sized buffers, never d_ff-sized ones), pass
  * through the workspace; ask this function rather than relying on the rule.
- * For fp32 the forward's workspace is optional: mhffn_forward shares the blocks out as far as
- * the bytes it is given allow, and runs without any.  For MHFFN_OP_BACKWARD it is the gating weights R and
+ * In fp32 it depends on how evenly blocks of 64 tokens load the chip (not 0 for many large
+ * inputs either), and it is optional: without it (or with less) the shares of a token block
+ * run one after the other, which is slower and gives the same result.  For MHFFN_OP_BACKWARD it is the gating weights R and
  * their gradient as [H][E][N] fp32, the partial sums of dW_r, and, for the
  * neuron groups that would otherwise leave CUs idle in the last round of
  * workgroups, fp32 partial weight gradients of a few token segments (a multiple
@@ -152,11 +153,12 @@ int mhffn_forward(const mhffn_desc* desc, const void* X, const void* W_gate,
  * MHFFN_STATIC_SCRATCH_BYTES that is part of the library's code object: every
  * GPU the library runs on holds one copy until the process ends, and the call
  * allocates nothing (its address on the current device is looked up at the first
- * use there, or by mhffn_init).  A problem whose mhffn_workspace_bytes exceeds
+ * use there, or by mhffn_init).  fp32 uses no scratch here: no fp32 problem is refused
+ * for its size and calls on different streams are independent.  A bf16 problem whose mhffn_workspace_bytes exceeds
  * that size returns MHFFN_ERR_STATIC_SCRATCH and launches nothing (d_head = 128
  * with up to 64 sub-networks never needs more than 32 MiB, whatever the token
  * count; the kernels of the other shapes can need up to 64 MiB at a few hundred
- * to a few thousand tokens and are then refused).  All calls on one GPU share the buffer: it keeps the last call's
+ * to a few thousand tokens and are then refused).  All bf16 calls on one GPU share the buffer: it keeps the last call's
  * partial sums (each call overwrites what it reads, nothing has to start at
  * zero), and two calls that overlap in time on one GPU (different streams) race
  * on it -- serialise them, or use mhffn_forward with workspaces of their own. */

@@ -179,15 +179,8 @@ int forward_impl(const mhffn_desc* desc, const void* X, const void* W_gate, cons
       rc = check_workspace(need, workspace, workspace_bytes);
       if (rc) return rc;
     }
-  } else if (static_scratch) {
-    workspace_bytes = 0;   // fp32 needs none: it takes what fits
-    if (mhffn::fwd_f32_workspace_bytes(p)) {
-      rc = static_scratch_address(&workspace);
-      if (rc) return rc;
-      workspace_bytes = MHFFN_STATIC_SCRATCH_BYTES;
-    }
-  } else if (!aligned16(workspace)) {
-    workspace = nullptr;
+  } else if (static_scratch || !aligned16(workspace)) {
+    workspace = nullptr;   // fp32 needs none: calls that overlap stay independent of each other
   }
   const int e = (desc->dtype == MHFFN_BF16)
                     ? mhffn::launch_fwd_bf16(p, X, W_gate, W_up, W_down, route, Y, workspace,

@@ -31,10 +31,11 @@ struct F32Args {
   const float* Wd;
   const void* route;
   float* Y;
-  float* P;     // [n_split][N][H*dh] partial outputs (only when n_split > 1)
+  float* P;     // [n_split][N][H*dh] partial outputs (only when n_split > 1 and there is scratch)
   int64_t N, ldx, ldy, n_tiles, n_items;
   int H, dh, E, de, route_mode;
   int n_split, tiles_per_split;
+  int workgroups;   // per token block: one per share, or, without scratch, one for all shares
   float eps;
 };
 
@@ -55,8 +56,8 @@ __global__ __launch_bounds__(64 * NW, DHP <= 64 ? 4 : DHP <= 128 ? 3 : 2) void f
   const int cpr = dh >> 2;                            // 16-byte chunks per row
   const int64_t item = xcd_work_item(blockIdx.x, a.n_items);
   if (item >= a.n_items) return;  // whole workgroup leaves together
-  const int split = (int)(item % a.n_split);
-  const int64_t ht = item / a.n_split;
+  const int split = (int)(item % a.workgroups);
+  const int64_t ht = item / a.workgroups;
   const int h = (int)(ht / a.n_tiles);
   const int64_t tok0 = (ht % a.n_tiles) * BT;
   const int wtok = 16 * wave + i16;                   // token of this lane inside the block
@@ -67,7 +68,7 @@ __global__ __launch_bounds__(64 * NW, DHP <= 64 ? 4 : DHP <= 128 ? 3 : 2) void f
   // (rows of a tile are contiguous in memory; rows past the sub-network's width are zero)
   const int cps = (de + kF32Rows - 1) / kF32Rows;     // tiles per sub-network
   const int t_begin = split * a.tiles_per_split;
-  const int t_end = min(E * cps, t_begin + a.tiles_per_split);
+  const int t_end = a.workgroups == 1 ? E * cps : min(E * cps, t_begin + a.tiles_per_split);
   const size_t head_off = (size_t)h * E * de * dh;
   int loff[CPT];
 #pragma unroll
@@ -160,7 +161,39 @@ __global__ __launch_bounds__(64 * NW, DHP <= 64 ? 4 : DHP <= 128 ? 3 : 2) void f
   const float* urow = Us + i16 * LD + 4 * gq;
   const float* vcol = Vs + 4 * gq * LD + 4 * i16;
   f32_settle(q);
+  // ---- store: lane = token, register v of the four tiles = columns 64 J + 16 gq + 4 v .. +3 ----
+  // Shares that one workgroup takes one after the other are added up in Y as the reduce kernel
+  // adds their partials, so the result does not depend on the scratch.
+  auto store = [&](int t) __attribute__((always_inline)) {
+    if (tok >= a.N) return;
+    const bool partial = a.workgroups > 1;
+    float* dst = partial ? a.P + (((size_t)split * a.N + tok) * a.H + h) * dh : a.Y + tok * a.ldy + (size_t)h * dh;
+#pragma unroll
+    for (int J = 0; J < JG; ++J)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int col = 64 * J + 16 * gq + 4 * v;
+        if (col < dh) {
+          f32x4 o = {O[J][0][v], O[J][1][v], O[J][2][v], O[J][3][v]};
+          if (!partial && a.n_split > 1) {
+            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+            o = (t < a.tiles_per_split ? zero : *reinterpret_cast<const f32x4*>(dst + col)) + o;
+          }
+          *reinterpret_cast<f32x4*>(dst + col) = o;
+        }
+      }
+  };
+  int left = a.tiles_per_split;   // tiles of the share that are left
   for (int t = t_begin; t < t_end; ++t) {
+    if (left == 0) {
+      store(t - 1);
+#pragma unroll
+      for (int J = 0; J < JG; ++J)
+#pragma unroll
+        for (int n = 0; n < 4; ++n) O[J][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+      left = a.tiles_per_split;
+    }
+    --left;
     __syncthreads();   // everyone is done with the previous tile (first pass: R and the padding are written)
 #pragma unroll
     for (int c = 0; c < CPT; ++c)
@@ -195,19 +228,7 @@ __global__ __launch_bounds__(64 * NW, DHP <= 64 ? 4 : DHP <= 128 ? 3 : 2) void f
         });
   }
 
-  // ---- store: lane = token, register v of the four tiles = columns 64 J + 16 gq + 4 v .. +3 ----
-  if (tok >= a.N) return;
-  float* dst = a.n_split > 1 ? a.P + (((size_t)split * a.N + tok) * a.H + h) * dh : a.Y + tok * a.ldy + (size_t)h * dh;
-#pragma unroll
-  for (int J = 0; J < JG; ++J)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int col = 64 * J + 16 * gq + 4 * v;
-      if (col < dh) {
-        const f32x4 o = {O[J][0][v], O[J][1][v], O[J][2][v], O[J][3][v]};
-        *reinterpret_cast<f32x4*>(dst + col) = o;
-      }
-    }
+  store(t_end - 1);
 }
 
 // Y[tok][col] = sum_s P[s][tok][col], fixed order
@@ -233,29 +254,27 @@ int block_waves(const Problem& p) {
 
 int64_t tiles_of(const Problem& p) { return (int64_t)p.E * ((p.de + kF32Rows - 1) / kF32Rows); }
 
-int plan_splits(const Problem& p, size_t ws_bytes) {
+size_t output_bytes(const Problem& p) { return (size_t)p.N * p.H * p.dh * sizeof(float); }
+int plan_splits(const Problem& p) {
   const int nw = block_waves(p);
   const int64_t items = ((p.N + 16 * nw - 1) / (16 * nw)) * p.H;
-  const size_t out = (size_t)p.N * p.H * p.dh * sizeof(float);
-  int most = (int)(ws_bytes / out < 32 ? ws_bytes / out : 32);
-  if (most < 2) return 1;
   // microseconds: a tile of 16 neurons takes 32 cycles for each of its 3 DHP / 4 products and
   // wave of a SIMD; a split's partials are written and read at about 4 TB/s, and the second
   // launch costs about 4
   const double tile_us = 0.0100 * f32_padded_width(p.dh) * nw / 4;
-  return f32_plan_splits(items, tiles_of(p), tile_us, 2.0 * out / 4e6, 4.0, most);
+  return f32_plan_splits(items, tiles_of(p), tile_us, 2.0 * output_bytes(p) / 4e6, 4.0, 32);
 }
 
 template <int DHP, int NW>
 int launch(const Problem& p, F32Args a, hipStream_t stream) {
   a.n_tiles = (p.N + 16 * NW - 1) / (16 * NW);
-  a.n_items = a.n_tiles * p.H * a.n_split;
+  a.n_items = a.n_tiles * p.H * a.workgroups;
   if (hipError_t e0 = LdsLimit<&fwd_f32_kernel<DHP, NW>, (int)kLdsBytesPerWorkgroup>::ensure(); e0 != hipSuccess)
     return (int)e0;
   hipLaunchKernelGGL((fwd_f32_kernel<DHP, NW>), dim3((unsigned)xcd_grid_size(a.n_items)), dim3(64 * NW),
                      lds_bytes(p, NW), stream, a);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.n_split == 1) return (int)e;
+  if (e != hipSuccess || a.workgroups == 1) return (int)e;
   const int64_t n4 = p.N * p.H * p.dh / 4;
   hipLaunchKernelGGL(fwd_f32_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, stream, a);
   return (int)hipGetLastError();
@@ -287,8 +306,8 @@ size_t fwd_f32_lds_bytes(const Problem& p) {
 
 size_t fwd_f32_workspace_bytes(const Problem& p) {
   if (p.N == 0) return 0;
-  const int s = plan_splits(p, (size_t)-1);
-  return s > 1 ? (size_t)s * p.N * p.H * p.dh * sizeof(float) : 0;
+  const int s = plan_splits(p);
+  return s > 1 ? s * output_bytes(p) : 0;
 }
 
 int launch_fwd_f32(const Problem& p, const void* X, const void* Wg, const void* Wu,
@@ -304,7 +323,8 @@ int launch_fwd_f32(const Problem& p, const void* X, const void* Wg, const void* 
   a.P = static_cast<float*>(ws);
   a.N = p.N; a.ldx = p.ldx; a.ldy = p.ldy;
   a.H = p.H; a.dh = p.dh; a.E = p.E; a.de = p.de; a.route_mode = p.route_mode; a.eps = p.eps;
-  a.n_split = plan_splits(p, ws ? ws_bytes : 0);
+  a.n_split = plan_splits(p);
+  a.workgroups = ws && ws_bytes >= a.n_split * output_bytes(p) ? a.n_split : 1;
   a.tiles_per_split = (int)((tiles_of(p) + a.n_split - 1) / a.n_split);
   a.n_tiles = 0; a.n_items = 0;
   hipStream_t st = static_cast<hipStream_t>(stream);

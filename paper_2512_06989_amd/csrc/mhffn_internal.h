@@ -26,9 +26,9 @@ size_t fwd_bf16_lds_bytes(const Problem& p);
 size_t fwd_bf16_workspace_bytes(const Problem& p);
 int launch_fwd_bf16(const Problem& p, const void* X, const void* Wg, const void* Wu,
                     const void* Wd, const void* route, void* Y, void* ws, void* stream);
-// fp32, d_h % 4 == 0, d_h <= 256.  The workspace is optional: with fwd_f32_workspace_bytes
-// of it the intermediate dimension is split as evenly as the chip wants, with less (or none)
-// over fewer workgroups.
+// fp32, d_h % 4 == 0, d_h <= 256.  The workspace is optional: with fwd_f32_workspace_bytes of
+// it the shares of the intermediate dimension run on workgroups of their own, with less (or
+// none) one after the other on one, with the same result.
 int launch_fwd_f32(const Problem& p, const void* X, const void* Wg, const void* Wu,
                    const void* Wd, const void* route, void* Y, void* ws, size_t ws_bytes, void* stream);
 size_t fwd_f32_workspace_bytes(const Problem& p);

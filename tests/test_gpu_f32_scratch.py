@@ -1,0 +1,53 @@
+"""The scratch of the fp32 forward is optional and changes nothing but its speed: shares of the
+intermediate dimension run on workgroups of their own with it and one after the other without, and
+the partial sums are the same.  mhffn_forward_static takes none, so that calls that overlap on two
+streams stay independent and no size is refused."""
+import pytest
+
+from paper_2512_06989_amd import inputs, mhffn
+from tests.helpers import device_inputs, small_workload
+
+pytestmark = pytest.mark.gpu
+ARGS = ("X", "W_gate", "W_up", "W_down", "W_r")
+
+
+def _problem(N, H, dh, E, de, seed=3):
+    w = small_workload("f32_scratch", N, H, E, de, "f32", dh=dh)
+    g = device_inputs(inputs.make_inputs(w, seed=seed, with_dy=False), "f32")
+    a = [g[k] for k in ARGS]
+    need = mhffn.workspace_bytes(mhffn.make_desc(a[0], a[1], mhffn.ROUTE_PARAMS, w.eps), mhffn.OP_FORWARD)
+    return a, need
+
+
+@pytest.mark.parametrize("N,H,dh,E,de", [
+    (2000, 6, 128, 16, 128), (33, 2, 128, 2, 64), (5, 1, 4, 40, 64), (500, 3, 64, 7, 40), (300, 1, 256, 17, 24),
+    (700, 2, 196, 5, 33), (100, 2, 72, 3, 100), (40, 1, 128, 700, 2),
+    (4200, 8, 128, 8, 128)])     # more scratch than the static buffer of mhffn_forward_static holds
+def test_every_amount_of_scratch_gives_the_same_sums(N, H, dh, E, de):
+    import torch
+    a, need = _problem(N, H, dh, E, de)
+    out = N * H * dh * 4
+    assert need % out == 0 and need >= 2 * out
+    want = mhffn.forward(*a)
+    buf = torch.empty(need + 256, dtype=torch.uint8, device="cuda")
+    wide = torch.full((N, H * dh + 8), 7.0, device="cuda")
+    for ws in (buf, buf[:need], buf[:need - 1], buf[:2 * out], buf[:0], buf[8:]):
+        assert torch.equal(mhffn.forward(*a, workspace=ws, out=wide[:, :H * dh]), want), ws.numel()
+        assert torch.all(wide[:, H * dh:] == 7.0)
+    assert torch.equal(mhffn.forward_static(*a, torch.full_like(want, float("nan"))), want)
+
+
+def test_static_calls_on_two_streams_are_independent():
+    import torch
+    pairs = [_problem(900, 2, 128, 6, 64, seed=s) for s in (1, 2)]
+    want = [mhffn.forward(*a) for a, _ in pairs]
+    got = [[torch.empty_like(want[i]) for _ in range(8)] for i in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for k in range(8):
+        for i, (a, _) in enumerate(pairs):
+            mhffn.forward_static(*a, got[i][k], stream=streams[i])
+    torch.cuda.synchronize()
+    for i in range(2):
+        for k in range(8):
+            assert torch.equal(got[i][k], want[i]), (i, k)
