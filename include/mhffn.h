@@ -126,7 +126,8 @@ typedef struct {
  * through the workspace; ask this function rather than relying on the rule.
  * In fp32 it depends on how evenly blocks of 64 tokens load the chip (not 0 for many large
  * inputs either), and it is optional: without it (or with less) the shares of a token block
- * run one after the other, which is slower and gives the same result.  For MHFFN_OP_BACKWARD it is the gating weights R and
+ * run one after the other, which is slower and gives the same result (mhffn_module_forward
+ * likewise).  For MHFFN_OP_BACKWARD it is the gating weights R and
  * their gradient as [H][E][N] fp32, the partial sums of dW_r, and, for the
  * neuron groups that would otherwise leave CUs idle in the last round of
  * workgroups, fp32 partial weight gradients of a few token segments (a multiple

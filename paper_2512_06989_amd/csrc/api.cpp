@@ -281,10 +281,14 @@ int mhffn_module_forward(const mhffn_desc* desc, const void* X, const void* W_in
   rc = check_fused_shape(desc, p);
   if (rc) return rc;
   if (empty) return MHFFN_OK;
-  rc = check_workspace(mhffn::module_workspace_bytes(p, desc->dtype, false), workspace, workspace_bytes);
-  if (rc) return rc;
+  if (desc->dtype == MHFFN_BF16) {
+    rc = check_workspace(mhffn::module_workspace_bytes(p, desc->dtype, false), workspace, workspace_bytes);
+    if (rc) return rc;
+  } else if (!aligned16(workspace)) {
+    workspace = nullptr;   // fp32 needs none
+  }
   const int e = mhffn::launch_module_forward(p, desc->dtype, X, W_in, W_gate, W_up, W_down, W_r,
-                                             W_out, O, Q, S, workspace, hip_stream);
+                                             W_out, O, Q, S, workspace, workspace_bytes, hip_stream);
   return e == 0 ? MHFFN_OK : MHFFN_ERR_LAUNCH;
 }
 

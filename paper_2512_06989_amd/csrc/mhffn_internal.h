@@ -102,7 +102,8 @@ int launch_gemm_bf16(bool a_tr, bool b_tr, const void* A, int64_t lda, const voi
 size_t module_workspace_bytes(const Problem& p, int dtype, bool backward);
 int launch_module_forward(const Problem& p, int dtype, const void* X, const void* W_in,
                           const void* Wg, const void* Wu, const void* Wd, const void* Wr,
-                          const void* W_out, void* O, void* Q, void* S, void* ws, void* stream);
+                          const void* W_out, void* O, void* Q, void* S, void* ws, size_t ws_bytes,
+                          void* stream);
 int launch_module_backward(const Problem& p, int dtype, const void* X, const void* W_in,
                            const void* Wg, const void* Wu, const void* Wd, const void* Wr,
                            const void* W_out, const void* Q, const void* S, const void* dO,

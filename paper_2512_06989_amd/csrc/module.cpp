@@ -19,7 +19,7 @@ Problem inner(const Problem& p) {
   return q;
 }
 
-size_t fused_fwd_ws(const Problem& p, int dtype) { 
+size_t fused_fwd_ws(const Problem& p, int dtype) {
   return dtype == 1 ? fwd_bf16_workspace_bytes(inner(p)) : fwd_f32_workspace_bytes(inner(p));
 }
 
@@ -70,7 +70,8 @@ size_t module_workspace_bytes(const Problem& p, int dtype, bool backward) {
 
 int launch_module_forward(const Problem& p, int dtype, const void* X, const void* W_in,
                           const void* Wg, const void* Wu, const void* Wd, const void* Wr,
-                          const void* W_out, void* O, void* Q, void* S, void* ws, void* stream) {
+                          const void* W_out, void* O, void* Q, void* S, void* ws, size_t ws_bytes,
+                          void* stream) {
   if (p.N == 0) return 0;
   const int64_t dm = (int64_t)p.H * p.dh;
   const Problem q = inner(p);
@@ -79,7 +80,7 @@ int launch_module_forward(const Problem& p, int dtype, const void* X, const void
   int e = product_nn(dtype, X, p.ldx, W_in, dm, Q, dm, p.N, dm, dm, gws, stream);
   if (e) return e;
   e = dtype == 1 ? launch_fwd_bf16(q, Q, Wg, Wu, Wd, Wr, S, ws, stream)
-                 : launch_fwd_f32(q, Q, Wg, Wu, Wd, Wr, S, ws, fused_fwd_ws(p, dtype), stream);
+                 : launch_fwd_f32(q, Q, Wg, Wu, Wd, Wr, S, ws, ws_bytes, stream);
   if (e) return e;
   // O[l][j] = sum_i S[l][i] W_out[i][j]
   return product_nn(dtype, S, dm, W_out, dm, O, p.ldy, p.N, dm, dm, gws, stream);

@@ -51,3 +51,16 @@ def test_static_calls_on_two_streams_are_independent():
     for i in range(2):
         for k in range(8):
             assert torch.equal(got[i][k], want[i]), (i, k)
+
+
+def test_the_module_forward_runs_without_scratch():
+    import torch
+    a, need = _problem(500, 3, 64, 7, 40)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    P = [torch.randn(192, 192, generator=g, device="cuda") * 192 ** -0.5 for _ in range(2)]
+    call = (a[0], P[0], *a[1:], P[1])
+    want = mhffn.module_forward(*call)
+    buf = torch.empty(need + 256, dtype=torch.uint8, device="cuda")
+    for ws in (buf, buf[:need], buf[:need - 1], buf[:0], buf[8:]):
+        for got, ref in zip(mhffn.module_forward(*call, workspace=ws), want):
+            assert torch.equal(got, ref), ws.numel()
