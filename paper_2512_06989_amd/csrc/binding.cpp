@@ -16,6 +16,7 @@
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
 
+#include <optional>
 #include <vector>
 
 #include "../../include/mhffn.h"
@@ -89,30 +90,45 @@ struct Problem {
   }
 };
 
-// The caller's workspace, or a fresh one of the size the library asks for
+// None: the current stream of the current device
+hipStream_t stream_of(PyObject* stream) {
+  if (stream != Py_None) {
+    void* s = PyLong_AsVoidPtr(stream);
+    require(!PyErr_Occurred());
+    return static_cast<hipStream_t>(s);
+  }
+  return c10::hip::getCurrentHIPStream().stream();
+}
+
+// Makes a stream the current one of the tensors' device for as long as it lives
+struct OnStream {
+  c10::hip::HIPStream before;
+  OnStream(hipStream_t stream, const at::Tensor& x) : before(c10::hip::getCurrentHIPStream(x.device().index())) {
+    c10::hip::setCurrentHIPStream(c10::hip::getStreamFromExternal(stream, x.device().index()));
+  }
+  ~OnStream() { c10::hip::setCurrentHIPStream(before); }
+  OnStream(const OnStream&) = delete;
+  OnStream& operator=(const OnStream&) = delete;
+};
+
+// The caller's workspace, or a fresh one of the size the library asks for.  It is given back when
+// the call returns, so it has to belong to the stream the kernels run on: only what follows
+// them there may get its memory.
 struct Workspace {
   at::Tensor t;
   size_t bytes = 0;
-  Workspace(const Problem& p, int op, PyObject* given) {
+  Workspace(const Problem& p, int op, PyObject* given, PyObject* stream) {
     if (given != Py_None) {
       t = tensor(given);
     } else if (const size_t need = mhffn_workspace_bytes(&p.d, op)) {
+      std::optional<OnStream> guard;
+      if (stream != Py_None && p.x.is_cuda()) guard.emplace(stream_of(stream), p.x);
       t = at::empty({(int64_t)need}, p.x.options().dtype(at::kByte));
     }
     if (t.defined()) bytes = (size_t)t.numel() * t.element_size();
   }
   void* ptr() const { return data(t); }
 };
-
-// None: the current stream of the current device
-void* stream_of(PyObject* stream) {
-  if (stream != Py_None) {
-    void* s = PyLong_AsVoidPtr(stream);
-    require(!PyErr_Occurred());
-    return s;
-  }
-  return c10::hip::getCurrentHIPStream().stream();
-}
 
 double number(PyObject* o) {
   const double v = PyFloat_AsDouble(o);
@@ -212,7 +228,7 @@ PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     Problem p(a[0], a[1], a[2], a[3], a[4], number(a[5]), integer(a[6]));
     const at::Tensor y = a[7] == Py_None ? at::empty(p.x.sizes(), p.x.options()) : tensor(a[7]);
     p.d.ld_y = rows(y, p.x);
-    const Workspace ws(p, MHFFN_OP_FORWARD, a[9]);
+    const Workspace ws(p, MHFFN_OP_FORWARD, a[9], a[8]);
     void* const stream = stream_of(a[8]);
     const int rc = unlocked([&] {
       return mhffn_forward(&p.d, data(p.x), data(p.wg), data(p.wu), data(p.wd), data(p.route), data(y),
@@ -257,7 +273,7 @@ PyObject* backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const Grad grads[5] = {{"dX", nullptr}, {"dW_gate", &p.wg}, {"dW_up", &p.wu}, {"dW_down", &p.wd}, {"d_route", &p.route}};
     at::Tensor t[5];
     gradients(p, a[8], out, grads, t);
-    const Workspace ws(p, MHFFN_OP_BACKWARD, a[9]);
+    const Workspace ws(p, MHFFN_OP_BACKWARD, a[9], a[11]);
     void* const stream = stream_of(a[11]);
     const int rc = unlocked([&] {
       return mhffn_backward_phases(&p.d, data(p.x), data(p.wg), data(p.wu), data(p.wd), data(p.route), data(dy),
@@ -286,7 +302,7 @@ PyObject* module_forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
       if (i > 0) dense(t[i], {N, dm}, p.x.scalar_type(), p.x.device());
     }
     p.d.ld_y = rows(t[0], p.x);
-    const Workspace ws(p, MHFFN_OP_MODULE_FORWARD, a[10]);
+    const Workspace ws(p, MHFFN_OP_MODULE_FORWARD, a[10], a[9]);
     void* const stream = stream_of(a[9]);
     const int rc = unlocked([&] {
       return mhffn_module_forward(&p.d, data(p.x), data(w_in), data(p.wg), data(p.wu), data(p.wd),
@@ -316,7 +332,7 @@ PyObject* module_backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
                            {"dW_down", &p.wd}, {"dW_r", &p.route}, {"dW_out", &w_out}};
     at::Tensor t[7];
     gradients(p, a[11], out, grads, t);
-    const Workspace ws(p, MHFFN_OP_MODULE_BACKWARD, a[14]);
+    const Workspace ws(p, MHFFN_OP_MODULE_BACKWARD, a[14], a[13]);
     void* const stream = stream_of(a[13]);
     const int rc = unlocked([&] {
       return mhffn_module_backward(&p.d, data(p.x), data(w_in), data(p.wg), data(p.wu), data(p.wd),
