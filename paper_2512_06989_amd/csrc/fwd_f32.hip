@@ -35,11 +35,13 @@ struct F32Args {
   int64_t N, ldx, ldy, n_tiles, n_items;
   int H, dh, E, de, route_mode;
   int n_split, tiles_per_split;
-  int workgroups;   // per token block: one per share, or, without scratch, one for all shares
   float eps;
 };
 
-template <int DHP, int NW>
+// SERIAL: the shares of a token block run one after the other (no scratch); a workgroup then adds
+// them up in Y as the reduce kernel adds their partials, so the result does not depend on the
+// scratch.  (An instantiation of its own: as a branch it cost the other one 3 %.)
+template <int DHP, int NW, bool SERIAL>
 __global__ __launch_bounds__(64 * NW, DHP <= 64 ? 4 : DHP <= 128 ? 3 : 2) void fwd_f32_kernel(F32Args a) {
   constexpr int THREADS = 64 * NW, BT = 16 * NW;
   constexpr int KC = DHP / 16, JG = f32_col_groups(DHP), LD = f32_ld(DHP), TILE = kF32Rows * LD;
@@ -56,8 +58,8 @@ __global__ __launch_bounds__(64 * NW, DHP <= 64 ? 4 : DHP <= 128 ? 3 : 2) void f
   const int cpr = dh >> 2;                            // 16-byte chunks per row
   const int64_t item = xcd_work_item(blockIdx.x, a.n_items);
   if (item >= a.n_items) return;  // whole workgroup leaves together
-  const int split = (int)(item % a.workgroups);
-  const int64_t ht = item / a.workgroups;
+  const int split = SERIAL ? 0 : (int)(item % a.n_split);
+  const int64_t ht = SERIAL ? item : item / a.n_split;
   const int h = (int)(ht / a.n_tiles);
   const int64_t tok0 = (ht % a.n_tiles) * BT;
   const int wtok = 16 * wave + i16;                   // token of this lane inside the block
@@ -68,7 +70,7 @@ __global__ __launch_bounds__(64 * NW, DHP <= 64 ? 4 : DHP <= 128 ? 3 : 2) void f
   // (rows of a tile are contiguous in memory; rows past the sub-network's width are zero)
   const int cps = (de + kF32Rows - 1) / kF32Rows;     // tiles per sub-network
   const int t_begin = split * a.tiles_per_split;
-  const int t_end = a.workgroups == 1 ? E * cps : min(E * cps, t_begin + a.tiles_per_split);
+  const int t_end = SERIAL ? E * cps : min(E * cps, t_begin + a.tiles_per_split);
   const size_t head_off = (size_t)h * E * de * dh;
   int loff[CPT];
 #pragma unroll
@@ -162,12 +164,10 @@ __global__ __launch_bounds__(64 * NW, DHP <= 64 ? 4 : DHP <= 128 ? 3 : 2) void f
   const float* vcol = Vs + 4 * gq * LD + 4 * i16;
   f32_settle(q);
   // ---- store: lane = token, register v of the four tiles = columns 64 J + 16 gq + 4 v .. +3 ----
-  // Shares that one workgroup takes one after the other are added up in Y as the reduce kernel
-  // adds their partials, so the result does not depend on the scratch.
-  auto store = [&](int t) __attribute__((always_inline)) {
+  auto store = [&](bool first) __attribute__((always_inline)) {
     if (tok >= a.N) return;
-    const bool partial = a.workgroups > 1;
-    float* dst = partial ? a.P + (((size_t)split * a.N + tok) * a.H + h) * dh : a.Y + tok * a.ldy + (size_t)h * dh;
+    float* dst = !SERIAL && a.n_split > 1 ? a.P + (((size_t)split * a.N + tok) * a.H + h) * dh
+                                          : a.Y + tok * a.ldy + (size_t)h * dh;
 #pragma unroll
     for (int J = 0; J < JG; ++J)
 #pragma unroll
@@ -175,9 +175,9 @@ __global__ __launch_bounds__(64 * NW, DHP <= 64 ? 4 : DHP <= 128 ? 3 : 2) void f
         const int col = 64 * J + 16 * gq + 4 * v;
         if (col < dh) {
           f32x4 o = {O[J][0][v], O[J][1][v], O[J][2][v], O[J][3][v]};
-          if (!partial && a.n_split > 1) {
+          if constexpr (SERIAL) {
             const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-            o = (t < a.tiles_per_split ? zero : *reinterpret_cast<const f32x4*>(dst + col)) + o;
+            o = (first ? zero : *reinterpret_cast<const f32x4*>(dst + col)) + o;
           }
           *reinterpret_cast<f32x4*>(dst + col) = o;
         }
@@ -185,15 +185,17 @@ __global__ __launch_bounds__(64 * NW, DHP <= 64 ? 4 : DHP <= 128 ? 3 : 2) void f
   };
   int left = a.tiles_per_split;   // tiles of the share that are left
   for (int t = t_begin; t < t_end; ++t) {
-    if (left == 0) {
-      store(t - 1);
+    if constexpr (SERIAL) {
+      if (left == 0) {
+        store(t == a.tiles_per_split);
 #pragma unroll
-      for (int J = 0; J < JG; ++J)
+        for (int J = 0; J < JG; ++J)
 #pragma unroll
-        for (int n = 0; n < 4; ++n) O[J][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-      left = a.tiles_per_split;
+          for (int n = 0; n < 4; ++n) O[J][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+        left = a.tiles_per_split;
+      }
+      --left;
     }
-    --left;
     __syncthreads();   // everyone is done with the previous tile (first pass: R and the padding are written)
 #pragma unroll
     for (int c = 0; c < CPT; ++c)
@@ -228,7 +230,7 @@ __global__ __launch_bounds__(64 * NW, DHP <= 64 ? 4 : DHP <= 128 ? 3 : 2) void f
         });
   }
 
-  store(t_end - 1);
+  store(false);
 }
 
 // Y[tok][col] = sum_s P[s][tok][col], fixed order
@@ -265,29 +267,38 @@ int plan_splits(const Problem& p) {
   return f32_plan_splits(items, tiles_of(p), tile_us, 2.0 * output_bytes(p) / 4e6, 4.0, 32);
 }
 
-template <int DHP, int NW>
+template <int DHP, int NW, bool SERIAL>
 int launch(const Problem& p, F32Args a, hipStream_t stream) {
   a.n_tiles = (p.N + 16 * NW - 1) / (16 * NW);
-  a.n_items = a.n_tiles * p.H * a.workgroups;
-  if (hipError_t e0 = LdsLimit<&fwd_f32_kernel<DHP, NW>, (int)kLdsBytesPerWorkgroup>::ensure(); e0 != hipSuccess)
+  a.n_items = a.n_tiles * p.H * (SERIAL ? 1 : a.n_split);
+  if (hipError_t e0 = LdsLimit<&fwd_f32_kernel<DHP, NW, SERIAL>, (int)kLdsBytesPerWorkgroup>::ensure(); e0 != hipSuccess)
     return (int)e0;
-  hipLaunchKernelGGL((fwd_f32_kernel<DHP, NW>), dim3((unsigned)xcd_grid_size(a.n_items)), dim3(64 * NW),
+  hipLaunchKernelGGL((fwd_f32_kernel<DHP, NW, SERIAL>), dim3((unsigned)xcd_grid_size(a.n_items)), dim3(64 * NW),
                      lds_bytes(p, NW), stream, a);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.workgroups == 1) return (int)e;
+  if (e != hipSuccess || SERIAL || a.n_split == 1) return (int)e;
   const int64_t n4 = p.N * p.H * p.dh / 4;
   hipLaunchKernelGGL(fwd_f32_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, stream, a);
   return (int)hipGetLastError();
 }
 
-template <int NW>
+template <int NW, bool SERIAL>
 int launch_width(const Problem& p, const F32Args& a, hipStream_t stream) {
   switch (f32_padded_width(p.dh)) {
-    case 64: return launch<64, NW>(p, a, stream);
-    case 96: return launch<96, NW>(p, a, stream);
-    case 128: return launch<128, NW>(p, a, stream);
-    case 192: return launch<192, NW>(p, a, stream);
-    default: return launch<256, NW>(p, a, stream);
+    case 64: return launch<64, NW, SERIAL>(p, a, stream);
+    case 96: return launch<96, NW, SERIAL>(p, a, stream);
+    case 128: return launch<128, NW, SERIAL>(p, a, stream);
+    case 192: return launch<192, NW, SERIAL>(p, a, stream);
+    default: return launch<256, NW, SERIAL>(p, a, stream);
+  }
+}
+
+template <bool SERIAL>
+int launch_block(const Problem& p, const F32Args& a, hipStream_t stream) {
+  switch (block_waves(p)) {
+    case 4: return launch_width<4, SERIAL>(p, a, stream);
+    case 2: return launch_width<2, SERIAL>(p, a, stream);
+    default: return launch<64, 1, SERIAL>(p, a, stream);   // d_h <= 16 is all that the entry point's limit lets through
   }
 }
 
@@ -324,15 +335,11 @@ int launch_fwd_f32(const Problem& p, const void* X, const void* Wg, const void* 
   a.N = p.N; a.ldx = p.ldx; a.ldy = p.ldy;
   a.H = p.H; a.dh = p.dh; a.E = p.E; a.de = p.de; a.route_mode = p.route_mode; a.eps = p.eps;
   a.n_split = plan_splits(p);
-  a.workgroups = ws && ws_bytes >= a.n_split * output_bytes(p) ? a.n_split : 1;
   a.tiles_per_split = (int)((tiles_of(p) + a.n_split - 1) / a.n_split);
   a.n_tiles = 0; a.n_items = 0;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  switch (block_waves(p)) {
-    case 4: return launch_width<4>(p, a, st);
-    case 2: return launch_width<2>(p, a, st);
-    default: return launch<64, 1>(p, a, st);   // d_h <= 16 is all that the entry point's limit lets through
-  }
+  const bool serial = a.n_split > 1 && !(ws && ws_bytes >= a.n_split * output_bytes(p));
+  return serial ? launch_block<true>(p, a, st) : launch_block<false>(p, a, st);
 }
 
 }  // namespace mhffn
