@@ -6,6 +6,8 @@
 #include "mhffn_device.h"
 #include "mhffn_internal.h"
 
+#include <string.h>
+
 #include <mutex>
 
 // Scratch of mhffn_forward_static: one copy per GPU that the library runs on, held until
@@ -143,6 +145,30 @@ size_t mhffn_workspace_bytes(const mhffn_desc* desc, int op) {
     case MHFFN_OP_UNFUSED_BACKWARD: return mhffn::unfused_workspace_bytes(p, desc->dtype, true);
     default: return 0;
   }
+}
+
+// Not part of the interface in include/mhffn.h: what a call with 16-byte aligned dense operands
+// would launch, for tests that have to know which path a shape takes.  Host only.  Returns a
+// status; `text` (of `size` bytes) receives the zero-terminated plan, cut to fit.
+int mhffn_plan_text(const mhffn_desc* desc, int op, char* text, size_t size) {
+  if (!text || size == 0) return MHFFN_ERR_NULL;
+  text[0] = 0;
+  Problem p;
+  int rc = check_desc(desc, &p);
+  if (rc) return rc;
+  const bool backward = op == MHFFN_OP_BACKWARD || op == MHFFN_OP_MODULE_BACKWARD;
+  const bool module = op == MHFFN_OP_MODULE_FORWARD || op == MHFFN_OP_MODULE_BACKWARD;
+  if (!backward && !module && op != MHFFN_OP_FORWARD) return MHFFN_ERR_UNSUPPORTED;
+  rc = check_fused_shape(desc, p, backward);
+  if (rc || p.N == 0) return rc;
+  const bool bf16 = desc->dtype == MHFFN_BF16;
+  const std::string plan = module     ? mhffn::module_plan(p, desc->dtype, backward)
+                           : backward ? mhffn::bwd_plan(p, desc->dtype)
+                           : bf16     ? mhffn::fwd_bf16_plan(p)
+                                      : mhffn::fwd_f32_plan(p);
+  strncpy(text, plan.c_str(), size - 1);
+  text[size - 1] = 0;
+  return MHFFN_OK;
 }
 
 namespace {

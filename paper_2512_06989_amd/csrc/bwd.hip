@@ -2712,6 +2712,15 @@ int bwd_bf16_max_sub(const Problem& p) { return p.dh == 256 ? 64 : kRouteMaxSub;
 
 size_t bwd_bf16_lds_bytes(const Problem& p) { return tok_lds_bytes(p, tok_direct_staging(p)); }
 
+std::string bwd_plan(const Problem& p, int dtype) {
+  if (dtype != 1) return bwd_f32_plan(p);
+  const bool runs = p.dh == kDh || wgt256_takes(p);   // token segments of the last round's groups only
+  return std::string("tok ") + (tok_direct_staging(p) ? "direct" : "registers") + " shares=" +
+         std::to_string(plan_tok_shares(p).shares) + "; wgt segs=" +
+         std::to_string(runs ? plan_wgt16(p).segs : plan_wgt_split(p).segs) + "; route parts=" +
+         std::to_string(route_splits(p.N, p.H));
+}
+
 size_t bwd_workspace_bytes(const Problem& p, int dtype) {
   if (dtype != 1) return bwd_f32_workspace_bytes(p);
   if (p.N == 0) return 0;   // an empty batch only zero-fills the weight gradients

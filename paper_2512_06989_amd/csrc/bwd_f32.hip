@@ -634,6 +634,11 @@ size_t bwd_f32_lds_bytes(const Problem& p) {
   return sizeof(float) * (2 * 32 * dh + 3 * 16 * (dh + 1) + 2 * 32 * 17 + 2 * 32 * (size_t)p.E + 32);
 }
 
+std::string bwd_f32_plan(const Problem& p) {
+  return "tok waves=" + std::to_string(tok_block_waves(p)) + " shares=" + std::to_string(plan_tok_shares(p)) +
+         "; wgt segs=" + std::to_string(plan_wgt_segs(p)) + "; route parts=" + std::to_string(plan_route_parts(p));
+}
+
 size_t bwd_f32_workspace_bytes(const Problem& p) {
   if (p.N == 0) return 0;
   const int segs = plan_wgt_segs(p), shares = plan_tok_shares(p);

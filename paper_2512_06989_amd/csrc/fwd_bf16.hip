@@ -1603,6 +1603,15 @@ int launch_fwd_bf16(const Problem& p, const void* X, const void* Wg, const void*
   return launch_variant<kDh, 1, 8>(p, a, sp, st);
 }
 
+std::string fwd_bf16_plan(const Problem& p) {
+  const SplitPlan sp = plan_split(p);
+  const std::string kernel = sp.decode_nb ? "decode" + std::to_string(32 * sp.decode_nb)
+                             : sp.pipe    ? "flow"
+                             : sp.pair    ? "pair256"
+                                          : "tiles" + std::to_string(sp.bm);
+  return kernel + " shares=" + std::to_string(sp.n_split);
+}
+
 size_t fwd_bf16_lds_bytes(const Problem& p) {
   const SplitPlan sp = plan_split(p);
   if (sp.decode_nb) return (size_t)decode_lds_bytes(sp.decode_nb);

@@ -315,6 +315,11 @@ size_t fwd_f32_lds_bytes(const Problem& p) {
   return tiles < narrow ? tiles : narrow;
 }
 
+std::string fwd_f32_plan(const Problem& p) {
+  return "f32 width=" + std::to_string(f32_padded_width(p.dh)) + " waves=" + std::to_string(block_waves(p)) +
+         " shares=" + std::to_string(p.N ? plan_splits(p) : 1);
+}
+
 size_t fwd_f32_workspace_bytes(const Problem& p) {
   if (p.N == 0) return 0;
   const int s = plan_splits(p);

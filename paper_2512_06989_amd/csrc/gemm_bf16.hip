@@ -520,6 +520,13 @@ bool gemm_bf16_supported(bool a_tr, bool b_tr, const void* A, int64_t lda, const
   return true;
 }
 
+std::string gemm_bf16_plan(bool a_tr, int64_t M, int64_t N, int64_t K) {
+  if (!a_tr && skinny_takes(M, N, K)) return "few rows";
+  const GemmPlan plan = plan_tiles(a_tr, M, N, K);
+  return std::to_string(kShapeM[plan.shape]) + "x" + std::to_string(kShapeN[plan.shape]) + " splits=" +
+         std::to_string(plan.splits);
+}
+
 size_t gemm_bf16_workspace_bytes(int64_t M, int64_t N, int64_t K) {
   const int s0 = plan_tiles(false, M, N, K).splits, s1 = plan_tiles(true, M, N, K).splits;
   const int splits = s0 > s1 ? s0 : s1;

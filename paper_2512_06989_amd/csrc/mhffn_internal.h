@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <string>
+
 namespace mhffn {
 
 // Problem description after validation; strides are always filled in.
@@ -109,5 +111,15 @@ int launch_module_backward(const Problem& p, int dtype, const void* X, const voi
                            const void* W_out, const void* Q, const void* S, const void* dO,
                            void* dX, void* dW_in, void* dWg, void* dWu, void* dWd, void* dWr,
                            void* dW_out, void* ws, void* stream);
+
+// ---- what a call would launch, as text (host only; for tests) ------------------
+// Kernel, tile shape and how the work is shared out, e.g. "pair256 shares=2"; products by form
+// (nn, nt, tn), e.g. "256x128 splits=4".
+std::string fwd_bf16_plan(const Problem& p);
+std::string fwd_f32_plan(const Problem& p);
+std::string bwd_plan(const Problem& p, int dtype);
+std::string bwd_f32_plan(const Problem& p);
+std::string gemm_bf16_plan(bool a_tr, int64_t M, int64_t N, int64_t K);
+std::string module_plan(const Problem& p, int dtype, bool backward);
 
 }  // namespace mhffn

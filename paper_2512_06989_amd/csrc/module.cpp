@@ -61,6 +61,13 @@ int product_tn(int dtype, const void* A, int64_t lda, const void* B, int64_t ldb
 
 }  // namespace
 
+std::string module_plan(const Problem& p, int dtype, bool backward) {
+  const int64_t dm = (int64_t)p.H * p.dh;
+  std::string s = "rows " + (dtype == 1 ? gemm_bf16_plan(false, p.N, dm, dm) : std::string("generic"));
+  if (backward) s += "; weights " + (dtype == 1 ? gemm_bf16_plan(true, dm, dm, p.N) : std::string("generic"));
+  return s + "; " + (backward ? bwd_plan(inner(p), dtype) : dtype == 1 ? fwd_bf16_plan(inner(p)) : fwd_f32_plan(inner(p)));
+}
+
 size_t module_workspace_bytes(const Problem& p, int dtype, bool backward) {
   if (p.N == 0) return 0;
   if (!backward) return align256(fused_fwd_ws(p, dtype)) + gemm_ws(p, dtype, false);

@@ -1,8 +1,10 @@
 """Shared plumbing of the GPU parity tests: moving the seeded inputs to the
 device in their storage dtype, widening them for the oracle, error norms."""
+import ctypes
+
 import numpy as np
 
-from paper_2512_06989_amd import inputs
+from paper_2512_06989_amd import inputs, mhffn
 from paper_2512_06989_amd.device import device_inputs, to_device, to_host  # noqa: F401
 
 TOL = {"f32": 1e-5, "bf16": 5e-3}   # relative Frobenius error bounds of the parity bar
@@ -73,3 +75,13 @@ def small_workload(name, N, H, E, de, dtype, dh=128, w_std=0.05, route_scale=4.0
                    backward=False):
     return inputs.Workload(name, N, H, dh, E, de, dtype, w_std=w_std,
                            route_scale=route_scale, backward=backward)
+
+
+def launch_plan(op, N, H, E, de, dtype="bf16", dh=128, route_weights=False):
+    """What a call of this shape launches (mhffn_plan_text): kernels, tile shapes, shares."""
+    d = mhffn.Desc(N, H, dh, E, de, 0, 0, mhffn.BF16 if dtype == "bf16" else mhffn.F32,
+                   mhffn.ROUTE_WEIGHTS if route_weights else mhffn.ROUTE_PARAMS, 1e-6)
+    text = ctypes.create_string_buffer(256)
+    rc = mhffn.load().mhffn_plan_text(ctypes.byref(d), ctypes.c_int(op), text, ctypes.c_size_t(256))
+    assert rc == 0, mhffn.status_string(rc)
+    return text.value.decode()

@@ -6,16 +6,25 @@ import pytest
 
 from oracle import mhffn_oracle as orc
 from paper_2512_06989_amd import inputs, mhffn
-from tests.helpers import TOL, check_parity, device_inputs, small_workload, to_host
+from tests.helpers import TOL, check_parity, device_inputs, launch_plan, small_workload, to_host
 
-pytestmark = pytest.mark.gpu
-
-
-@pytest.mark.parametrize("N,H,dh,E,de,route_weights", [
+CASES = [
     (1, 1, 128, 2, 32, False), (255, 2, 128, 7, 64, False), (257, 3, 128, 44, 32, True),
     (300, 2, 128, 90, 32, False),                 # register-staged tiles (E > 88)
     (129, 2, 64, 5, 96, False), (128, 1, 64, 33, 32, True),
-    (127, 2, 256, 3, 64, False), (130, 1, 256, 40, 32, True)])   # (E > 32: register-staged)
+    (127, 2, 256, 3, 64, False), (130, 1, 256, 40, 32, True),    # (E > 32: register-staged)
+    (1, 1, 128, 8, 64, False), (127, 2, 256, 6, 96, False), (1, 2, 256, 12, 64, True)]
+ONE_SHARE = [CASES[0], CASES[6]]                  # too little work to share out
+
+
+@pytest.mark.parametrize("N,H,dh,E,de,route_weights", CASES)
+def test_the_cases_are_shared_out(N, H, dh, E, de, route_weights):
+    plan = launch_plan(mhffn.OP_BACKWARD, N, H, E, de, dh=dh, route_weights=route_weights)
+    assert (" shares=1;" in plan) == ((N, H, dh, E, de, route_weights) in ONE_SHARE), plan
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,H,dh,E,de,route_weights", CASES)
 def test_shared_sub_networks(N, H, dh, E, de, route_weights):
     import torch
     w = small_workload("shares", N, H, E, de, "bf16", dh=dh, backward=True)
