@@ -1443,6 +1443,18 @@ __global__ void fwd_bf16_reduce_kernel(FwdArgs a) {
 // two smaller workgroups per CU (d_h = 256: one, its LDS holds no second).
 struct SplitPlan { int bm, n_split, tiles_per_split; bool pipe, pair; int decode_nb; };
 constexpr int kDecodeMaxTokens = 128;
+// d_h = 256, 257 .. 383 token blocks: two rounds of workgroups, the second at most half full, or,
+// with two shares per block, three rounds of half the depth and the partials.  Microseconds,
+// measured: a tile takes 1.42 (pair kernel) or 1.76, a workgroup 10 or 12 around its tiles,
+// the partials are written and read at about 9 TB/s, the second launch costs 4.  10240 tokens,
+// H = 4, 176 tiles a head (pair kernel): 525 us whole, 426 in two shares; 32 tiles: 111 and 114;
+// 96 tiles (tiles of 32 neurons of 48 sub-networks): 355 and 311; 17 tiles: 83 and 101.
+bool two_shares_256(const Problem& p, bool pair, int64_t base, int T) {
+  if (base <= 256 || base >= 384) return false;
+  const double tile = pair ? 1.42 : 1.76, ends = pair ? 10.0 : 12.0;
+  const double partials = 4.0 + 4.0 * p.N * p.H * p.dh * sizeof(float) / 9e6;
+  return 3 * ((T + 1) / 2 * tile + ends) + partials < 2 * (T * tile + ends);
+}
 SplitPlan plan_split(const Problem& p) {
   SplitPlan s;
   s.pipe = p.dh == kDh && p.E <= kPipeMaxSub;
@@ -1467,6 +1479,7 @@ SplitPlan plan_split(const Problem& p) {
   int want = 1;
   if (s.pipe || p.dh == 256) {   // one workgroup per CU
     if (base <= 128) want = (int)(256 / base);
+    else if (p.dh == 256 && two_shares_256(p, s.pair, base, T)) want = 2;
   } else if (base < 384) {
     want = (int)((512 + base - 1) / base);
   }

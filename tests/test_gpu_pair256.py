@@ -4,13 +4,13 @@ ragged token blocks; 16 sub-networks, the most it takes, and 17).  Oracle parity
 with the per-row bound, and run-to-run bit identity."""
 import pytest
 
+from oracle import mhffn_oracle as orc
 from paper_2512_06989_amd import mhffn
-from tests.helpers import TOL, check_parity, device_inputs, small_workload, to_host
+from tests.helpers import TOL, check_parity, device_inputs, launch_plan, small_workload, to_host
 from tests.test_gpu_forward import oracle_forward, run_forward
 
-pytestmark = pytest.mark.gpu
 
-
+@pytest.mark.gpu
 @pytest.mark.parametrize("N,H,E,de,route_weights", [
     (1, 1, 1, 32, False), (15, 2, 1, 64, False), (16, 1, 3, 32, False), (33, 3, 2, 96, True),
     (127, 2, 16, 32, False), (129, 1, 16, 64, True), (128, 8, 17, 32, False), (200, 2, 4, 704, False),
@@ -27,3 +27,26 @@ def test_pair_forward(N, H, E, de, route_weights):
     again = [mhffn.forward(g["X"], g["W_gate"], g["W_up"], g["W_down"], g[key], w.eps, mode) for _ in range(2)]
     assert torch.equal(again[0], again[1])
     assert (to_host(again[0]) == Y).all()
+
+
+# 257 .. 383 token blocks: two whole rounds of workgroups, or three of half the depth where a head
+# has enough tiles (the pair kernel and the one for more sub-networks)
+UNEVEN = [(1300, 24, 4, 64, 1), (1300, 24, 16, 96, 2), (1281, 24, 4, 416, 2), (1900, 24, 17, 32, 1), (1281, 24, 17, 96, 2),
+          (1280, 24, 48, 64, 1), (2049, 24, 48, 64, 1)]
+
+
+@pytest.mark.parametrize("N,H,E,de,shares", UNEVEN)
+def test_uneven_rounds_are_shared_out(N, H, E, de, shares):
+    assert launch_plan(mhffn.OP_FORWARD, N, H, E, de, dh=256).endswith(" shares=%d" % shares)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,H,E,de", [c[:4] for c in UNEVEN if c[4] == 2])
+def test_uneven_rounds(N, H, E, de):
+    w = small_workload("uneven", N, H, E, de, "bf16", dh=256)
+    d, Y = run_forward(w, seed=N + E)
+    for h in (0, H - 1):                              # heads are independent
+        c = slice(h * 256, (h + 1) * 256)
+        one = [d[k][h:h + 1] for k in ("W_gate", "W_up", "W_down", "W_r")]
+        want = orc.forward(d["X"][:, c], *one, w.eps)
+        check_parity({"Y": Y[:, c]}, {"Y": want}, TOL["bf16"], 256, "uneven rounds, head %d" % h)
