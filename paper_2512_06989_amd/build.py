@@ -5,6 +5,7 @@ for gfx950 with hipcc (cross-compiles without a GPU).
 """
 import concurrent.futures
 import os
+import shutil
 import subprocess
 import sys
 
@@ -42,13 +43,18 @@ def _compile(src):
     return obj, err
 
 
+def _rocm_include():
+    """The headers beside the compiler; HIPCC may be a name on PATH or a link to it."""
+    hipcc = os.path.realpath(shutil.which(HIPCC) or HIPCC)
+    return os.path.join(os.path.dirname(os.path.dirname(hipcc)), "include")
+
+
 def _compile_binding():
     """csrc/binding.cpp with the host compiler, against the headers of the installed torch."""
     import sysconfig
     from torch.utils import cpp_extension
     obj = os.path.join(OBJDIR, "binding.o")
-    rocm = os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include")
-    inc = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"], rocm]
+    inc = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"], _rocm_include()]
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            *["-I" + d for d in inc], "-c", os.path.join(CSRC, "binding.cpp"), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
