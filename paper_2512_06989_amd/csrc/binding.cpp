@@ -212,13 +212,21 @@ void gradients(const Problem& p, PyObject* want, Outputs& out, const Grad (&grad
   }
 }
 
-// Calls the library with the interpreter lock released, as a foreign call would
-template <typename F>
-int unlocked(F&& call) {
+// The interpreter lock, released for as long as it lives
+struct Unlocked {
   PyThreadState* state = PyEval_SaveThread();
-  const int rc = call();
-  PyEval_RestoreThread(state);
-  return rc;
+  Unlocked() = default;
+  ~Unlocked() { PyEval_RestoreThread(state); }
+  Unlocked(const Unlocked&) = delete;
+  Unlocked& operator=(const Unlocked&) = delete;
+};
+// Calls the library with the lock released, as a foreign call would.  The arguments are plain
+// values by then: a tensor without memory of its own (inside torch.func) throws when asked for
+// its address.
+template <typename... P, typename... A>
+int unlocked(int (*call)(P...), A... args) {
+  const Unlocked released;
+  return call(args...);
 }
 
 // forward(X, W_gate, W_up, W_down, route, eps, mode, out, stream, workspace)
@@ -230,10 +238,8 @@ PyObject* forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     p.d.ld_y = rows(y, p.x);
     const Workspace ws(p, MHFFN_OP_FORWARD, a[9], a[8]);
     void* const stream = stream_of(a[8]);
-    const int rc = unlocked([&] {
-      return mhffn_forward(&p.d, data(p.x), data(p.wg), data(p.wu), data(p.wd), data(p.route), data(y),
-                                 ws.ptr(), ws.bytes, stream);
-    });
+    const int rc = unlocked(mhffn_forward, &p.d, data(p.x), data(p.wg), data(p.wu), data(p.wd), data(p.route),
+                            data(y), ws.ptr(), ws.bytes, stream);
     return rc ? status(rc) : THPVariable_Wrap(y);
   });
 }
@@ -246,10 +252,8 @@ PyObject* forward_static(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const at::Tensor y = tensor(a[5]);
     p.d.ld_y = rows(y, p.x);
     void* const stream = stream_of(a[8]);
-    const int rc = unlocked([&] {
-      return mhffn_forward_static(&p.d, data(p.x), data(p.wg), data(p.wu), data(p.wd), data(p.route), data(y),
-                                        stream);
-    });
+    const int rc = unlocked(mhffn_forward_static, &p.d, data(p.x), data(p.wg), data(p.wu), data(p.wd),
+                            data(p.route), data(y), stream);
     return rc ? status(rc) : THPVariable_Wrap(y);
   });
 }
@@ -275,12 +279,10 @@ PyObject* backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     gradients(p, a[8], out, grads, t);
     const Workspace ws(p, MHFFN_OP_BACKWARD, a[9], a[11]);
     void* const stream = stream_of(a[11]);
-    const int rc = unlocked([&] {
-      return mhffn_backward_phases(&p.d, data(p.x), data(p.wg), data(p.wu), data(p.wd), data(p.route), data(dy),
-                                         data(t[0]), data(t[1]), data(t[2]), data(t[3]), data(t[4]), ws.ptr(),
-                                         ws.bytes, stream, events.empty() ? nullptr : events.data(),
-                                         (int)events.size());
-    });
+    const int rc = unlocked(mhffn_backward_phases, &p.d, data(p.x), data(p.wg), data(p.wu), data(p.wd),
+                            data(p.route), data(dy), data(t[0]), data(t[1]), data(t[2]), data(t[3]), data(t[4]),
+                            ws.ptr(), ws.bytes, stream, events.empty() ? nullptr : events.data(),
+                            (int)events.size());
     return rc ? status(rc) : out.release();
   });
 }
@@ -304,11 +306,9 @@ PyObject* module_forward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     p.d.ld_y = rows(t[0], p.x);
     const Workspace ws(p, MHFFN_OP_MODULE_FORWARD, a[10], a[9]);
     void* const stream = stream_of(a[9]);
-    const int rc = unlocked([&] {
-      return mhffn_module_forward(&p.d, data(p.x), data(w_in), data(p.wg), data(p.wu), data(p.wd),
-                                        data(p.route), data(w_out), data(t[0]), data(t[1]), data(t[2]), ws.ptr(),
-                                        ws.bytes, stream);
-    });
+    const int rc = unlocked(mhffn_module_forward, &p.d, data(p.x), data(w_in), data(p.wg), data(p.wu),
+                            data(p.wd), data(p.route), data(w_out), data(t[0]), data(t[1]), data(t[2]),
+                            ws.ptr(), ws.bytes, stream);
     if (rc) return status(rc);
     PyObject* r = PyTuple_New(3);
     if (!r) return nullptr;
@@ -334,12 +334,10 @@ PyObject* module_backward(PyObject*, PyObject* const* a, Py_ssize_t n) {
     gradients(p, a[11], out, grads, t);
     const Workspace ws(p, MHFFN_OP_MODULE_BACKWARD, a[14], a[13]);
     void* const stream = stream_of(a[13]);
-    const int rc = unlocked([&] {
-      return mhffn_module_backward(&p.d, data(p.x), data(w_in), data(p.wg), data(p.wu), data(p.wd),
-                                         data(p.route), data(w_out), data(q), data(s), data(d_o), data(t[0]),
-                                         data(t[1]), data(t[2]), data(t[3]), data(t[4]), data(t[5]), data(t[6]),
-                                         ws.ptr(), ws.bytes, stream);
-    });
+    const int rc = unlocked(mhffn_module_backward, &p.d, data(p.x), data(w_in), data(p.wg), data(p.wu),
+                            data(p.wd), data(p.route), data(w_out), data(q), data(s), data(d_o), data(t[0]),
+                            data(t[1]), data(t[2]), data(t[3]), data(t[4]), data(t[5]), data(t[6]), ws.ptr(),
+                            ws.bytes, stream);
     return rc ? status(rc) : out.release();
   });
 }

@@ -1,5 +1,9 @@
-"""Errors raised while the binding allocates outputs and scratch keep their type: a training loop
-catches torch.OutOfMemoryError to go on with a smaller batch."""
+"""Errors raised inside the native binding are Python exceptions of the type torch gives them: a
+training loop catches torch.OutOfMemoryError to go on with a smaller batch, and tensors without
+memory of their own (those of torch.func) are refused with torch's own message."""
+import subprocess
+import sys
+
 import pytest
 import torch
 from torch.utils._python_dispatch import TorchDispatchMode
@@ -52,6 +56,39 @@ def test_an_aten_error_reads_as_torch_raises_it():
     with pytest.raises(RuntimeError) as got:
         mhffn.forward(X, *W, torch.zeros(2, 128, 3, dtype=torch.bfloat16))
     assert str(got.value) == str(want.value)   # (no C++ backtrace)
+
+
+WRAPPED = """
+import types
+import torch
+from paper_2512_06989_amd import mhffn
+X = torch.zeros(8, 256, dtype=torch.bfloat16)
+W = [torch.zeros(2, 3, 64, 128, dtype=torch.bfloat16) for _ in range(3)]
+Wr, P = torch.zeros(2, 128, 3, dtype=torch.bfloat16), torch.zeros(256, 256, dtype=torch.bfloat16)
+stream = types.SimpleNamespace(cuda_stream=0)
+ws = torch.zeros(8)
+calls = {"forward": lambda x: mhffn.forward(x, *W, Wr, stream=stream, workspace=ws),
+         "forward_out": lambda x: mhffn.forward(X, *W, Wr, out=x, stream=stream, workspace=ws),
+         "forward_static": lambda x: mhffn.forward_static(x, *W, Wr, X, stream=stream),
+         "backward": lambda x: mhffn.backward(x, *W, Wr, X, stream=stream, workspace=ws),
+         "module_forward": lambda x: mhffn.module_forward(x, P, *W, Wr, P, stream=stream, workspace=ws)[0],
+         "module_backward": lambda x: mhffn.module_backward(x, P, *W, Wr, P, X, X, X, stream=stream, workspace=ws)}
+for name, call in calls.items():
+    for transform in (lambda f: torch.vmap(f)(torch.stack([X, X])), lambda f: torch.func.grad(lambda x: f(x).sum())(X)):
+        try:
+            transform(call)
+            print(name, "passed")
+        except RuntimeError as e:
+            print(name, "storage" in str(e))
+"""
+
+
+def test_tensors_without_memory_are_refused():
+    """(a process of its own: an exception that leaves the binding without the interpreter lock ends it)"""
+    r = subprocess.run([sys.executable, "-W", "ignore", "-c", WRAPPED], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr[-400:]
+    lines = r.stdout.split("\n")[:-1]
+    assert len(lines) == 12 and all(line.endswith(" True") for line in lines), r.stdout
 
 
 @pytest.mark.gpu
