@@ -199,7 +199,10 @@ void gradients(const Problem& p, PyObject* want, Outputs& out, const Grad (&grad
     PyObject* k = PySequence_Fast_GET_ITEM(want, i);
     size_t j = 0;
     while (j < G && !(PyUnicode_Check(k) && PyUnicode_CompareWithASCIIString(k, grads[j].key) == 0)) ++j;
-    require(j < G);
+    if (j == G) {   // not a gradient of this call: what the caller gave under that name, if anything
+      require(PyDict_Contains(out.dict, k) == 1);
+      continue;
+    }
     if (out.has(grads[j].key)) continue;
     out.set(grads[j].key, grads[j].like ? at::empty(grads[j].like->sizes(), grads[j].like->options())
                                         : empty_rows_like(p.x));

@@ -259,7 +259,8 @@ def backward(X, W_gate, W_up, W_down, route, dY, eps=1e-6, route_mode=ROUTE_PARA
     """Fused recompute-based backward.  Returns a dict of the requested gradients.
     `phase_events`: optional list of raw hipEvent_t handles (ints) recorded between
     the phases of the backward (see mhffn_backward_phases)."""
-    r = (_host or _load_host()).backward(X, W_gate, W_up, W_down, route, dY, eps, int(route_mode), tuple(want),
+    want = tuple(want)
+    r = (_host or _load_host()).backward(X, W_gate, W_up, W_down, route, dY, eps, int(route_mode), want,
                                          workspace, dict(out) if out else None, _raw(stream),
                                          tuple(phase_events) if phase_events else None)
     if r is None:
@@ -327,8 +328,9 @@ def module_forward(X, W_in, W_gate, W_up, W_down, W_r, W_out, eps=1e-6, out=None
 def module_backward(X, W_in, W_gate, W_up, W_down, W_r, W_out, Q, S, dO, eps=1e-6,
                     want=MODULE_GRADS, out=None, stream=None, workspace=None):
     """Backward of module_forward from the saved Q and S.  Returns a dict of gradients."""
+    want = tuple(want)
     r = (_host or _load_host()).module_backward(X, W_in, W_gate, W_up, W_down, W_r, W_out, Q, S, dO, eps,
-                                                tuple(want), dict(out) if out else None, _raw(stream), workspace)
+                                                want, dict(out) if out else None, _raw(stream), workspace)
     if r is None:
         _check_params(X, W_gate, W_up, W_down, W_r, ROUTE_PARAMS)
         out, (N, dm) = dict(out or {}), X.shape
@@ -343,7 +345,8 @@ def module_backward(X, W_in, W_gate, W_up, W_down, W_r, W_out, Q, S, dO, eps=1e-
             _require(_rows("dX", out["dX"], X) == d.ld_x or N < 2,
                      "dX must have X's row stride (%d), got %d" % (d.ld_x, out["dX"].stride(0)))
         for k in want:
-            _require(k == "dX" or k in like, "unknown gradient %r" % (k,))
+            if k != "dX" and k not in like and k not in out:
+                raise KeyError(k)
         for k, ref in like.items():
             if out.get(k) is not None:
                 _dense(k, out[k], ref.shape, ref.dtype, ref.device)

@@ -76,3 +76,13 @@ def test_unfused_rejects_y_and_dy_of_different_strides():
     dY = torch.zeros(N, DM + 64, dtype=torch.bfloat16)[:, :DM]
     with pytest.raises(ValueError):
         mhffn.reference_unfused(X, *W, Wr, dY=dY, out={"Y": torch.zeros(N, DM, dtype=torch.bfloat16)})
+
+
+@pytest.mark.parametrize("call", ["backward", "module_backward"])
+def test_an_unknown_gradient_is_named_whatever_holds_the_names(call):
+    X, W, Wr = _args()
+    P = torch.zeros(DM, DM, dtype=torch.bfloat16)
+    args = {"backward": (X, *W, Wr, X), "module_backward": (X, P, *W, Wr, P, X, X, X)}[call]
+    for want in (("dX", "dW"), ["dX", "dW"], (k for k in ("dX", "dW"))):
+        with pytest.raises(KeyError, match="dW"):
+            getattr(mhffn, call)(*args, want=want)
