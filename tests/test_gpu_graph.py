@@ -83,3 +83,39 @@ def test_first_call_may_be_captured_after_init():
     assert torch.equal(Y1, Y0)
     for k in names:
         assert torch.equal(G1[k], G0[k]), k
+
+
+@pytest.mark.parametrize("dtype,N,H,dh,E,de", [
+    ("f32", 300, 2, 128, 6, 64), ("f32", 70, 1, 72, 3, 40), ("bf16", 300, 2, 256, 6, 96), ("bf16", 96, 4, 128, 8, 64)])
+def test_module_replays_with_scratch_from_the_capture(dtype, N, H, dh, E, de):
+    """Outputs and scratch come from the graph's own pool (shared sub-networks, few-row products,
+    split contractions, both on the capturing stream and with it given)."""
+    import torch
+    mhffn.init()
+    w = small_workload("graph_module", N, H, E, de, dtype, dh=dh, backward=True)
+    g = device_inputs(inputs.make_module_inputs(w, seed=N, with_dy=True), dtype)
+    a = [g[k] for k in ("X", "W_in", "W_gate", "W_up", "W_down", "W_r", "W_out")]
+
+    def run(stream=None):
+        O, Q, S = mhffn.module_forward(*a, w.eps, stream=stream)
+        return [O, Q, S, *mhffn.module_backward(*a, Q, S, g["dY"], w.eps, stream=stream).values()]
+
+    want = run()
+    torch.cuda.synchronize()
+    for given in (False, True):
+        graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            with torch.cuda.graph(graph, stream=side):
+                got = run(side if given else None)
+        torch.cuda.current_stream().wait_stream(side)
+        for rep in range(3):
+            for t in got:
+                t.fill_(7.0)
+            scratch = torch.randn(1 << 20, device="cuda").sum()    # eager work between the replays
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            for x, y in zip(got, want):
+                assert torch.equal(x, y), (given, rep)
+            del scratch
