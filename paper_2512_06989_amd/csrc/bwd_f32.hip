@@ -314,7 +314,8 @@ __global__ __launch_bounds__(64 * NW, DHP <= 64 ? 3 : DHP <= 128 ? 2 : 1) void b
 // The K, U, V rows are resident as operands (tokens on the MFMA rows here, neurons on the
 // columns); blocks of 16 tokens of q and dY pass through two LDS buffers.  From d_h = 192 on
 // the V rows lie in LDS instead: operands and accumulators of three matrices would take 384 of
-// a lane's 512 registers at d_h = 256, and what is left is too few (it spills).
+// a lane's 512 registers at d_h = 256.  With V in LDS 428 bytes per lane still spill there, 25
+// reloads beside the 384 products of a block; at 192 nothing does.
 // ---------------------------------------------------------------------------
 constexpr int kWgtWaves = 4;
 constexpr bool wgt_v_in_lds(int dhp) { return dhp >= 192; }
@@ -366,8 +367,9 @@ __global__ __launch_bounds__(64 * kWgtWaves, DHP <= 128 ? 2 : 1) void bwd_f32_wg
   const float* Xh = a.X + (size_t)h * dh;
   const float* Yh = a.dY + (size_t)h * dh;
   const float* Rrow = a.Rws + ((size_t)h * E + e) * N;
-  // (no read-ahead: the resident operands and accumulators fill the registers, and the other
-  // workgroup of the CU computes meanwhile)
+  // (no read-ahead: the resident operands and accumulators fill the registers.  Up to d_h = 128
+  // the other workgroups of the CU compute meanwhile; at 192 and 256 there is none, and every
+  // block waits for its loads)
   auto stage = [&](int64_t b, float* buf) {
     const int64_t t0 = b * kF32Rows;
     f32x4 xreg[CPT], yreg[CPT];

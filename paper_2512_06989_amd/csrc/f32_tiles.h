@@ -84,10 +84,12 @@ struct F32Op3 { f32x4 a, b, c; };
 __device__ __forceinline__ f32x4 lds_f32x4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 
 // How many workgroups share one unit of work (the tiles of a token block, the tokens of a
-// neuron group) so that the chip is evenly loaded.  Up to four workgroups live on a CU, so
-// the time is that of the CU with the most workgroups, ceil(items * s / 256), times the
-// steps of one, plus what a split costs (partials written and read back).  `step_cost` and
-// `split_cost` (per split) in the same unit.
+// neuron group) so that the chip is evenly loaded.  The time is taken as that of the CU with the
+// most workgroups, ceil(items * s / 256), times the steps of one, plus what a split costs
+// (partials written and read back), `step_cost` and `split_cost` (per split) in the same unit.
+// How many of a CU's workgroups run at once is not in the rule: by registers (head width 64 / 96,
+// 128 / 192, 256) five / three / two of the forward's, four / two / one of the token-major
+// sweep's, three / two / one of the weight-major sweep's.
 inline int f32_plan_splits(int64_t items, int64_t steps, double step_cost, double split_cost, double fixed_cost,
                            int max_splits) {
   int best = 1;

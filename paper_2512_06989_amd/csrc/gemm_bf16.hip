@@ -344,8 +344,8 @@ __global__ void gemm_bf16_reduce_kernel(TunedGemmArgs a) {
 // 128-byte (transposed weights: 64-byte) pieces of rows: fetched in operand layout, 8 bytes
 // per lane from 32 rows, A held the address unit for 64 cycles a load.  What a CU then takes
 // is the 27 bytes per clock it can load (128 rows in one workgroup: 30 us, in four: 8.4).
-// 16 x 2048 x 2048: 8 us against 19.8 + 4.0 us of the tiled kernel, whose 256-row tiles
-// fill 32 CUs and whose split contraction needs a second launch.
+// 16 x 2048 x 2048: 7.8 us against 9.9 of the tiled kernel (64 x 128 tiles, the contraction
+// split and summed by a second launch); 128 rows: 8.7 against 15.1.
 // ---------------------------------------------------------------------------
 constexpr int kSkinnyWaves = 16, kSkinnyRows = 32, kSkinnyCols = 32;
 constexpr int kSkinnyWaveLds = 2 * 4096;   // a slice of B and one of A
@@ -498,8 +498,14 @@ int launch_form(const TunedGemmArgs& a, int shape, hipStream_t stream) {
 }  // namespace
 
 // Where the few-rows kernel is the faster one: a round of its workgroups (one per CU) takes
-// about 520 clocks per 64-wide slice of k and 2000 around them (4.4 us at K = 1024, 7 us at K =
-// 2048).  300 rows at K = 2048 and 700 at K = 1024 is where the tiled kernel takes over.
+// about 520 clocks per 64-wide slice of k and 2000 around them.  It is chosen for up to 512 rows
+// at d_model = 1024, 160 at 1536, 128 at 2048, 45 .. 96 at 2560 and not at all from 3072 on.
+// Microseconds, few rows | tiled with its sum: d_model = 1024, 128 rows 5.0 | 9.1, 512 9.1 | 10.1,
+// 513 11.5 | 10.0; 1536, 160 rows 6.5 | 13.0; 2048, 1 row 7.1 | 8.6, 128 8.7 | 15.1, 320 18.8 |
+// 15.5; 2560, 1 row 10.0 | 9.4, 64 10.7 | 12.9, 128 16.9 | 14.6; 3072, 1 row 10.7 | 9.8; 5120, 1
+// row 20.6 | 14.9.  The tiled kernel gets some sizes too early: 2048, 129 .. 256 rows 12.4 ..
+// 13.8 | 14.6 .. 15.2; 1536, 192 .. 320 rows 10.0 .. 11.2 | 13.7 .. 14.8; 3072 and 4096, 64 rows
+// 12.6 | 14.7 and 15.2 | 17.1.
 bool skinny_takes(int64_t M, int64_t N, int64_t K) {
   if (N % kSkinnyCols != 0 || K % kSkinnyK != 0) return false;
   const int64_t wgs = ((M + kSkinnyRows - 1) / kSkinnyRows) * (N / kSkinnyCols);
