@@ -1474,7 +1474,8 @@ SplitPlan plan_split(const Problem& p) {
   }
   s.bm = (!s.pipe && p.N <= 128) ? 64 : 256;
   if (p.dh == 256) s.bm = 128;   // 4 waves of up to 512 registers (see launch_fwd_bf16)
-  const int64_t base = ((p.N + s.bm - 1) / s.bm) * p.H;
+  // (an empty batch is planned too, for its LDS: as one token block)
+  const int64_t base = (p.N > s.bm ? (p.N + s.bm - 1) / s.bm : 1) * p.H;
   const int T = p.E * (p.de / kBI);
   int want = 1;
   if (s.pipe || p.dh == 256) {   // one workgroup per CU

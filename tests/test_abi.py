@@ -192,3 +192,17 @@ def test_most_sub_networks_of_the_fp32_forward(d_head, most):
     shape = dict(dtype=mhffn.F32, n_tokens=0, d_head=d_head, d_sub=1)
     assert fwd(desc(n_sub=most, **shape)) == 0
     assert fwd(desc(n_sub=most + 1, **shape)) == 3
+
+
+@pytest.mark.parametrize("dtype,d_head,n_sub", [(mhffn.BF16, 64, 3), (mhffn.BF16, 64, 96), (mhffn.BF16, 128, 3),
+                                                (mhffn.BF16, 128, 80), (mhffn.BF16, 256, 3), (mhffn.BF16, 256, 40),
+                                                (mhffn.F32, 64, 3), (mhffn.F32, 256, 3)])
+def test_empty_batches_of_every_head_width(dtype, d_head, n_sub):
+    """(a plan for no tokens must not divide by them)"""
+    lib, d = mhffn.load(), desc(n_tokens=0, dtype=dtype, d_head=d_head, n_sub=n_sub)
+    for op in range(6):
+        mhffn.workspace_bytes(d, op)
+    assert fwd(d) == 0 and lib.mhffn_forward_static(ctypes.byref(d), *([FAKE] * 6), None) == 0
+    assert lib.mhffn_module_forward(ctypes.byref(d), *([FAKE] * 10), None, 0, None) == 0
+    none = [FAKE] * 6 + [None] * 5     # no gradient asked for: nothing to zero (6: no GPU to ask for errors)
+    assert lib.mhffn_backward(ctypes.byref(d), *none, None, 0, None) in (0, 6)
