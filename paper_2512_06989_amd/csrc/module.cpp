@@ -82,7 +82,8 @@ int launch_module_forward(const Problem& p, int dtype, const void* X, const void
   if (p.N == 0) return 0;
   const int64_t dm = (int64_t)p.H * p.dh;
   const Problem q = inner(p);
-  void* gws = static_cast<unsigned char*>(ws) + align256(fused_fwd_ws(p, dtype));
+  // (fp32 may come without scratch, and its products use none)
+  void* gws = dtype == 1 ? static_cast<unsigned char*>(ws) + align256(fused_fwd_ws(p, dtype)) : nullptr;
   // Q[l][j] = sum_i X[l][i] W_in[i][j]
   int e = product_nn(dtype, X, p.ldx, W_in, dm, Q, dm, p.N, dm, dm, gws, stream);
   if (e) return e;
