@@ -1443,17 +1443,25 @@ __global__ void fwd_bf16_reduce_kernel(FwdArgs a) {
 // two smaller workgroups per CU (d_h = 256: one, its LDS holds no second).
 struct SplitPlan { int bm, n_split, tiles_per_split; bool pipe, pair; int decode_nb; };
 constexpr int kDecodeMaxTokens = 128;
-// d_h = 256, 257 .. 383 token blocks: two rounds of workgroups, the second at most half full, or,
-// with two shares per block, three rounds of half the depth and the partials.  Microseconds,
-// measured: a tile takes 1.42 (pair kernel) or 1.76, a workgroup 10 or 12 around its tiles,
-// the partials are written and read at about 9 TB/s, the second launch costs 4.  10240 tokens,
-// H = 4, 176 tiles a head (pair kernel): 525 us whole, 426 in two shares; 32 tiles: 111 and 114;
-// 96 tiles (tiles of 32 neurons of 48 sub-networks): 355 and 311; 17 tiles: 83 and 101.
-bool two_shares_256(const Problem& p, bool pair, int64_t base, int T) {
-  if (base <= 256 || base >= 384) return false;
+// Shares per token block at d_h = 256 for 129 .. 383 blocks, which as whole blocks take one round
+// of workgroups or two, the last at most half full: more shares make more, shorter rounds (164
+// blocks in three shares: two rounds of a third) and partials.  Microseconds, measured: a tile
+// takes 1.42 (pair kernel) or 1.76, a workgroup 10 or 12 around its tiles, the partials are
+// written and read at about 9 TB/s, the second launch costs 4.  Whole | shared: pair kernel, 164
+// blocks (H = 4), 176 tiles a head 262 | 205 in three shares, 12 tiles 28 | 46; 200 blocks, 176
+// tiles 262 | 283 in two; 320 blocks, 176 tiles 516 | 418 in two, 32 tiles 111 | 114; the other
+// kernel, 164 blocks, 96 tiles 177 | 159 in three, 40 tiles 80 | 88; 320 blocks, 96 tiles 354 | 310.
+// At most as many shares as the scratch is asked for (fwd_bf16_workspace_bytes).
+int shares_256(const Problem& p, bool pair, int64_t base, int T) {
   const double tile = pair ? 1.42 : 1.76, ends = pair ? 10.0 : 12.0;
-  const double partials = 4.0 + 4.0 * p.N * p.H * p.dh * sizeof(float) / 9e6;
-  return 3 * ((T + 1) / 2 * tile + ends) + partials < 2 * (T * tile + ends);
+  const double partial = 2.0 * p.N * p.H * p.dh * sizeof(float) / 9e6;
+  int best = 1;
+  double best_us = 0;
+  for (int s = 1; s <= (512 + base - 1) / base; ++s) {
+    const double us = (double)((base * s + 255) / 256) * ((T + s - 1) / s * tile + ends) + (s > 1 ? 4.0 + s * partial : 0.0);
+    if (s == 1 || us < best_us) { best = s; best_us = us; }
+  }
+  return best;
 }
 SplitPlan plan_split(const Problem& p) {
   SplitPlan s;
@@ -1480,7 +1488,7 @@ SplitPlan plan_split(const Problem& p) {
   int want = 1;
   if (s.pipe || p.dh == 256) {   // one workgroup per CU
     if (base <= 128) want = (int)(256 / base);
-    else if (p.dh == 256 && two_shares_256(p, s.pair, base, T)) want = 2;
+    else if (p.dh == 256 && base < 384) want = shares_256(p, s.pair, base, T);
   } else if (base < 384) {
     want = (int)((512 + base - 1) / base);
   }

@@ -29,15 +29,16 @@ def test_pair_forward(N, H, E, de, route_weights):
     assert (to_host(again[0]) == Y).all()
 
 
-# 257 .. 383 token blocks: two whole rounds of workgroups, or three of half the depth where a head
+# 129 .. 383 token blocks: one or two whole rounds of workgroups, or more of less depth where a head
 # has enough tiles (the pair kernel and the one for more sub-networks)
-UNEVEN = [(1300, 24, 4, 64, 1), (1300, 24, 16, 96, 2), (1281, 24, 4, 416, 2), (1900, 24, 17, 32, 1), (1281, 24, 17, 96, 2),
+UNEVEN = [(800, 20, 4, 96, 1), (800, 20, 5, 416, 3), (1000, 20, 17, 96, 3), (1000, 25, 17, 96, 1), (1000, 25, 5, 416, 1),
+          (1300, 24, 4, 64, 1), (1300, 24, 16, 96, 2), (1281, 24, 4, 416, 2), (1900, 24, 17, 32, 1), (1281, 24, 17, 96, 2),
           (1280, 24, 48, 64, 1), (2049, 24, 48, 64, 1)]
 
 
 @pytest.mark.parametrize("N,H,E,de,shares", UNEVEN)
 def test_uneven_rounds_are_shared_out(N, H, E, de, shares):
-    assert launch_plan(mhffn.OP_FORWARD, N, H, E, de, dh=256).endswith(" shares=%d" % shares)
+    assert launch_plan(mhffn.OP_FORWARD, N, H, E, de, dh=256).endswith(" shares=%d" % shares), launch_plan(mhffn.OP_FORWARD, N, H, E, de, dh=256)
 
 
 @pytest.mark.gpu
