@@ -2578,22 +2578,29 @@ bool tok_direct_staging(const Problem& p) {
 
 // Shares of the sub-networks per token block: few tokens leave CUs without a workgroup, or the
 // last round of workgroups mostly empty.  Microseconds, measured: a step of 32 neurons takes
-// about 2.1 (d_h = 64, two workgroups on a CU: 1.1), a workgroup 20 (14) before and after its
-// steps; a share's partial dX is written and read back at about 4 TB/s; the launch that adds
-// them up costs about 10.
+// about 2.1 (d_h = 64, two workgroups on a CU: 1.1; d_h = 256: 1.85, tiles through registers
+// 2.6), a workgroup 20 (14) before and after its steps; a share's partial dX is written and read
+// back at about 4 TB/s.  The launch that adds them up costs about 10 at d_h = 64, 5 + 1 per share
+// at 128 and, its few waves waiting for one share's partial after the other, 4 + 2.5 per share at
+// 256 (2 less where it also takes the routing derivative off the blocks).  Whole | shared, 128 tokens, H = 4, R given, the
+// token-major part alone: d_h = 256, E = 7, d_e = 32 26.5 | 30.7 in seven shares, E = 13 38.5 | 52.2
+// in thirteen and 36.2 in three, E = 30, d_e = 64 125 | 52 in six; d_h = 128, E = 7, d_e = 32 21.2 |
+// 20.3 in four, E = 30, d_e = 64 108 | 36 in ten; d_h = 64 73 | 24 in eight.
 struct TokShares { int shares, subs; };
 TokShares plan_tok_shares(const Problem& p) {
   const int bm = tok_block_tokens(p.dh);
   const int64_t items = ((p.N + bm - 1) / bm) * p.H;
   const int slots = p.dh == 64 ? 512 : 256;      // workgroups that run at once
-  const double sub_us = (p.dh == 64 ? 1.1 : 2.1) * (p.de / 32), ends_us = p.dh == 64 ? 14.0 : 20.0;
-  const double part_us = 2.0 * p.N * p.H * p.dh * sizeof(float) / 4e6;
+  const double tile_us = p.dh == 64 ? 1.1 : p.dh == 128 ? 2.1 : tok_direct_staging(p) ? 1.85 : 2.6;
+  const double sub_us = tile_us * (p.de / 32), ends_us = p.dh == 64 ? 14.0 : 20.0;
+  const double sum_us = p.dh == 64 ? 10.0 : p.dh == 128 ? 5.0 : p.route_mode == 0 ? 2.0 : 4.0;
+  const double share_us = (p.dh == 64 ? 0.0 : p.dh == 128 ? 1.0 : 2.5) + 2.0 * p.N * p.H * p.dh * sizeof(float) / 4e6;
   TokShares best{1, p.E};
   double best_us = 0;
   for (int s = 1; s <= 16 && s <= p.E; ++s) {
     const int subs = (p.E + s - 1) / s;
     if ((p.E + subs - 1) / subs != s) continue;  // s workgroups would not all have a sub-network
-    const double us = (double)((items * s + slots - 1) / slots) * (subs * sub_us + ends_us) + (s > 1 ? 10.0 + s * part_us : 0.0);
+    const double us = (double)((items * s + slots - 1) / slots) * (subs * sub_us + ends_us) + (s > 1 ? sum_us + s * share_us : 0.0);
     if (s == 1 || us < best_us) { best = {s, subs}; best_us = us; }
   }
   return best;

@@ -13,8 +13,9 @@ CASES = [
     (300, 2, 128, 90, 32, False),                 # register-staged tiles (E > 88)
     (129, 2, 64, 5, 96, False), (128, 1, 64, 33, 32, True),
     (127, 2, 256, 3, 64, False), (130, 1, 256, 40, 32, True),    # (E > 32: register-staged)
-    (1, 1, 128, 8, 64, False), (127, 2, 256, 6, 96, False), (1, 2, 256, 12, 64, True)]
-ONE_SHARE = [CASES[0], CASES[6]]                  # too little work to share out
+    (1, 1, 128, 8, 64, False), (127, 2, 256, 6, 96, False), (1, 2, 256, 12, 64, True),
+    (128, 4, 256, 7, 32, True), (128, 4, 256, 13, 32, True)]
+ONE_SHARE = [CASES[0], CASES[6], CASES[11]]       # too little work to share out
 
 
 @pytest.mark.parametrize("N,H,dh,E,de,route_weights", CASES)
