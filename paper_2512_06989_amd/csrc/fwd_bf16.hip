@@ -21,6 +21,7 @@
 #include "mhffn_device.h"
 #include "mhffn_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace mhffn {
@@ -52,6 +53,21 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 #define MHFFN_SB() __builtin_amdgcn_sched_barrier(0)
 
+// Work list of fwd_bf16_flow_kernel (flow_shares below plans it): token blocks 0 .. n_full - 1 are
+// whole (256 tokens, all tiles of the head, Y stored); the blocks behind them are units of
+// unit_tokens (256 or 128) tokens whose tiles are shared out, `equal` shares of up to share_tiles
+// tiles and, if rest_tiles, one of those.  More than one share: fp32 partial outputs
+// P[share][unit][token][128].
+struct FlowShares {
+  uint32_t n_full, n_units;
+  uint32_t tiles;                // whole blocks per head
+  uint32_t unit0, unit_tiles;    // unit i is token tile (unit0 + i) % unit_tiles of head (unit0 + i) / unit_tiles
+  uint32_t unit_tokens, equal, share_tiles, rest_tiles;
+  __host__ __device__ uint32_t shares() const { return equal + (rest_tiles > 0); }
+  __host__ __device__ size_t partial_floats() const { return shares() > 1 ? (size_t)shares() * n_units * unit_tokens * 128 : 0; }
+  uint32_t grid() const { return (n_full + n_units * shares() + 7) / 8 * 8; }
+};
+
 struct FwdArgs {
   const uint16_t* X;
   const uint16_t* Wg;
@@ -64,6 +80,7 @@ struct FwdArgs {
   int H, E, de, dh, route_mode;
   int n_split, tiles_per_split;
   float eps;
+  FlowShares flow;   // fwd_bf16_flow_kernel only
 };
 
 template <int DH, int TB, int NW>
@@ -398,19 +415,49 @@ __global__ __launch_bounds__(64 * kPipeWaves) void fwd_bf16_flow_kernel(FwdArgs 
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 31, g = lane >> 5;
-  const int64_t item = xcd_work_item(blockIdx.x, a.n_items);
-  if (item >= a.n_items) return;  // whole workgroup leaves together
-  const int split = (int)(item % a.n_split);
-  const int64_t ht = item / a.n_split;
-  const int h = (int)(ht / a.n_tiles);
-  const int64_t tile_tok0 = (ht % a.n_tiles) * BM;
+  // Workgroups go to the XCDs round robin and are started in order: every XCD takes its eighth of
+  // the whole blocks, then of the equal shares, then of the rests, so that the short ones are last.
+  const FlowShares& fs = a.flow;
+  const int tiles_per_sub = a.de / kBI;
+  const uint32_t xcd = blockIdx.x & 7;
+  uint32_t widx = blockIdx.x >> 3, unit = 0;
+  int64_t tile_tok0;
+  int h, share = 0, bm = BM, t_begin = 0, T = a.E * tiles_per_sub;
+  // (whole blocks beside units: a multiple of 256)
+  const uint32_t n_equal = fs.n_units * fs.equal;
+  const uint32_t px_full = (fs.n_full >> 3) + (xcd < (fs.n_full & 7)), px_equal = (n_equal >> 3) + (xcd < (n_equal & 7));
+  const bool whole = widx < px_full;
+  if (whole) {
+    const uint32_t blk = xcd * (fs.n_full >> 3) + min(xcd, fs.n_full & 7) + widx;
+    h = (int)(blk / fs.tiles);
+    tile_tok0 = (int64_t)(blk % fs.tiles) * BM;
+  } else {
+    widx -= px_full;
+    if (widx < px_equal) {
+      const uint32_t i = xcd * (n_equal >> 3) + min(xcd, n_equal & 7) + widx;
+      unit = i / fs.equal;
+      share = (int)(i - unit * fs.equal);
+    } else {
+      // (of n % 8 rests the last XCDs take one more, of n % 8 equal shares the first ones: none
+      // takes more than an eighth of all workgroups, rounded up)
+      const uint32_t n_rest = fs.rest_tiles ? fs.n_units : 0, extra = 8 - (n_rest & 7);
+      widx -= px_equal;
+      if (widx >= (n_rest >> 3) + (xcd >= extra)) return;   // whole workgroup leaves together
+      unit = xcd * (n_rest >> 3) + (xcd > extra ? xcd - extra : 0) + widx;
+      share = (int)fs.equal;
+    }
+    bm = (int)fs.unit_tokens;
+    t_begin = share * (int)fs.share_tiles;
+    T = min(T - t_begin, (int)fs.share_tiles);
+    const uint32_t u = fs.unit0 + unit;
+    h = (int)(u / fs.unit_tiles);
+    tile_tok0 = (int64_t)(u % fs.unit_tiles) * bm;
+    if (tile_tok0 >= a.N) return;   // the second half of a head's last, ragged block
+  }
   const int wtok = wave * 32;
   const int E = a.E;
-  const bool active = tile_tok0 + wtok < a.N;
+  const bool active = wtok < bm && tile_tok0 + wtok < a.N;
 
-  const int tiles_per_sub = a.de / kBI;
-  const int t_begin = split * a.tiles_per_split;
-  const int T = min(E * tiles_per_sub, t_begin + a.tiles_per_split) - t_begin;
   const size_t head_off = ((size_t)h * E * a.de + (size_t)t_begin * kBI) * kDh;
   const uint16_t* Kh = a.Wg + head_off;
   const uint16_t* Uh = a.Wu + head_off;
@@ -514,7 +561,7 @@ __global__ __launch_bounds__(64 * kPipeWaves) void fwd_bf16_flow_kernel(FwdArgs 
   } else {
     first_requests();
     const float* R = reinterpret_cast<const float*>(a.route);
-    for (int idx = tid; idx < BM * E; idx += THREADS) {
+    for (int idx = tid; idx < bm * E; idx += THREADS) {
       const int tl = idx / E, e = idx - tl * E;
       const int64_t tok = tile_tok0 + tl;
       Rs[e * BM + tl] = inv_weight((tok < a.N) ? R[((size_t)tok * a.H + h) * E + e] : 0.f);
@@ -735,9 +782,10 @@ __global__ __launch_bounds__(64 * kPipeWaves) void fwd_bf16_flow_kernel(FwdArgs 
   __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the reads issued for a step that never comes
 
   const int64_t tok = tile_tok0 + wtok + r;
-  if (a.n_split > 1) {
+  if (!active) return;
+  if (!whole && fs.shares() > 1) {
     if (tok < a.N) {
-      float* dst = a.P + (((size_t)split * a.N + tok) * a.H + h) * kDh + 4 * g;
+      float* dst = a.P + (((size_t)share * fs.n_units + unit) * bm + wtok + r) * kDh + 4 * g;
 #pragma unroll
       for (int jb = 0; jb < 4; ++jb)
 #pragma unroll
@@ -1411,6 +1459,42 @@ __global__ __launch_bounds__(kDecodeThreads) void fwd_bf16_decode_kernel(FwdArgs
   }
 }
 
+// sum += src[0] + src[stride] + .., in this order: eight loads in flight, also of the last ones (one
+// after the other, 15 partials of 16 x 2048 took 1.3 us more)
+__device__ __forceinline__ void add_partials(f32x4& sum, const float* src, size_t stride, int n) {
+  f32x4 v[8];
+  for (; n >= 8; n -= 8, src += 8 * stride) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = *reinterpret_cast<const f32x4*>(src + i * stride);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sum += v[i];
+  }
+  if (n == 0) return;
+#pragma unroll
+  for (int i = 0; i < 7; ++i) {
+    v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (i < n) v[i] = *reinterpret_cast<const f32x4*>(src + i * stride);
+  }
+#pragma unroll
+  for (int i = 0; i < 7; ++i) sum += v[i];
+}
+
+// Y = bf16(sum over the shares), for the units of fwd_bf16_flow_kernel: thread = 4 columns of one token of a unit
+__global__ void fwd_bf16_flow_reduce_kernel(FwdArgs a) {
+  const FlowShares& fs = a.flow;
+  const uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x, row = idx / (kDh / 4), col = 4 * (idx % (kDh / 4));
+  const uint32_t unit = row / fs.unit_tokens, u = fs.unit0 + unit;
+  if (unit >= fs.n_units) return;
+  const int64_t tok = (int64_t)(u % fs.unit_tiles) * fs.unit_tokens + row % fs.unit_tokens;
+  if (tok >= a.N) return;
+  const size_t stride = (size_t)fs.n_units * fs.unit_tokens * kDh;
+  const float* src = a.P + (size_t)row * kDh + col;
+  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+  add_partials(sum, src, stride, (int)fs.shares());
+  *reinterpret_cast<u32x2*>(a.Y + tok * a.ldy + (int64_t)(u / fs.unit_tiles) * kDh + col) =
+      u32x2{pack_bf16(sum[0], sum[1]), pack_bf16(sum[2], sum[3])};
+}
+
 // Y[tok][col] = bf16(sum_s P[s][tok][col]), fixed order
 __global__ void fwd_bf16_reduce_kernel(FwdArgs a) {
   const int64_t dm = (int64_t)a.H * a.dh;
@@ -1418,16 +1502,7 @@ __global__ void fwd_bf16_reduce_kernel(FwdArgs a) {
   if (idx >= a.N * dm) return;
   f32x4 sum = {0.f, 0.f, 0.f, 0.f};
   const size_t stride = (size_t)a.N * dm;
-  int s = 0;
-  for (; s + 8 <= a.n_split; s += 8) {   // eight loads in flight, summed in the order of s
-    f32x4 v[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = *reinterpret_cast<const f32x4*>(a.P + (size_t)(s + i) * stride + idx);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) sum += v[i];
-  }
-  for (; s < a.n_split; ++s)
-    sum += *reinterpret_cast<const f32x4*>(a.P + (size_t)s * stride + idx);
+  add_partials(sum, a.P + idx, stride, a.n_split);
   const int64_t tok = idx / dm, col = idx % dm;
   u32x2 pk;
   pk[0] = pack_bf16(sum[0], sum[1]);
@@ -1435,12 +1510,9 @@ __global__ void fwd_bf16_reduce_kernel(FwdArgs a) {
   *reinterpret_cast<u32x2*>(a.Y + tok * a.ldy + col) = pk;
 }
 
-// How the intermediate dimension is shared out when the token tiles alone
-// cannot fill the chip (decode / short prefill).  The pipelined kernel (one workgroup of
-// 256 tokens per CU) is split down to about one workgroup per CU: with few tokens it
-// is a weight-streaming kernel, and its deep ring of direct loads is what keeps
-// enough bytes in flight.  The older kernel (more than 64 sub-networks) aims for
-// two smaller workgroups per CU (d_h = 256: one, its LDS holds no second).
+// How the intermediate dimension is shared out when the token tiles alone cannot fill the chip
+// (the pipelined kernel: flow_shares).  The decode kernel takes about one workgroup per CU, the
+// kernel for more than 64 sub-networks two smaller ones (d_h = 256: one, its LDS holds no second).
 struct SplitPlan { int bm, n_split, tiles_per_split; bool pipe, pair; int decode_nb; };
 constexpr int kDecodeMaxTokens = 128;
 // Shares per token block at d_h = 256 for 129 .. 383 blocks, which as whole blocks take one round
@@ -1463,6 +1535,64 @@ int shares_256(const Problem& p, bool pair, int64_t base, int T) {
   }
   return best;
 }
+// Work list of the pipelined kernel.  Blocks of 256 tokens that fill whole rounds of the 256 CUs
+// (LDS holds one workgroup) stay whole; the blocks behind them stay whole too, or are cut in
+// halves of 128 tokens (waves 4-7 then only move tiles: a wave that has its SIMD to itself takes
+// two thirds of the time of two that share it).  Up to 128 blocks, whole or in halves, share their
+// tiles out for fp32 partials, in equal shares or, for the CUs that those leave, one shorter share
+// per unit.  (More blocks run without scratch, as callers of the static entry point rely on.)
+// The time is modelled from measurements (us): a step of 32 neurons takes 0.95 (half a block: 0.62)
+// on a CU, but the chip under its power limit takes no more than 197 (338) of them per us;
+// 11.4 (10.8) around a workgroup's steps; the partials 0.46 per MiB, written and read, and 1.
+// Where the two bounds meet, a tenth more than either.  Whole | this list, forward calls, E d_e / 32
+// tiles, us: 384 blocks, 64 tiles 165 | 153 (128 blocks in halves); 128 blocks, 32 tiles 42 | 33 and
+// 64 blocks 41 | 30 (halves; 36 in four shares); 96 blocks, 264 tiles 257 | 155 in shares of 108, 108
+// and 48, 160 in two equal ones; 32 blocks (300 tokens), 32 tiles 41 | 21 (halves in four shares; 27
+// whole in eight).  Partials of at most 40 MiB: what the static scratch buffer holds.
+FlowShares flow_shares(const Problem& p) {
+  const uint32_t T = (uint32_t)(p.E * (p.de / kBI)), slots = 256;
+  FlowShares f{};
+  f.tiles = p.N > kPipeBM ? (uint32_t)((p.N + kPipeBM - 1) / kPipeBM) : 1;   // (an empty batch is planned too)
+  const uint32_t blocks = f.tiles * (uint32_t)p.H, rounds = blocks / slots;
+  f.n_full = blocks;
+  if (blocks == rounds * slots) return f;
+  double best = 0;
+  for (uint32_t half = 0; half < 2; ++half) {
+    const double step = half ? 0.62 : 0.95, rate = half ? 338 : 197, ends = half ? 10.8 : 11.4;
+    const uint32_t tokens = half ? kPipeBM / 2 : kPipeBM;
+    const uint32_t per_head = rounds ? f.tiles * (half + 1) : p.N > tokens ? (uint32_t)((p.N + tokens - 1) / tokens) : 1;
+    const uint32_t unit0 = rounds * slots * (half + 1), units = per_head * (uint32_t)p.H - unit0;
+    const double rows = rounds ? (double)units * tokens : (double)p.N * p.H;   // (ragged blocks cost less)
+    const double work = rounds * slots * T / 197.0 + rows / tokens * T / rate;
+    const uint32_t most = blocks <= 128 ? std::min((40u << 20) / (tokens * kDh * 4) / units, T / 2) : 1;   // shares
+    auto consider = [&](uint32_t equal, uint32_t share, uint32_t turns) {
+      const uint32_t rest = T > equal * share ? T - equal * share : 0, shares = equal + (rest > 0);
+      if (shares > 1 && shares > most) return;
+      const double path = rounds * T * 0.95 + turns * share * step;
+      const double hi = path > work ? path : work, r = (path > work ? work : path) / hi, r2 = r * r, r4 = r2 * r2;
+      const double us = hi * (1 + 0.09 * r4 * r4) + rounds * 11.4 + turns * ends +
+                        (shares > 1 ? 1 + 0.46 / (1 << 20) * shares * rows * kDh * 4 : 0.0);
+      if (best != 0 && us >= best) return;
+      best = us;
+      const bool cut = shares > 1 || half;
+      f.n_full = cut ? rounds * slots : blocks;
+      f.n_units = cut ? units : 0;
+      f.unit0 = unit0; f.unit_tiles = per_head; f.unit_tokens = tokens;
+      f.equal = equal; f.share_tiles = share; f.rest_tiles = rest;
+    };
+    for (uint32_t s = 1; s == 1 || (s <= most && units * s <= slots); s += 1 + s / 8) {
+      const uint32_t share = (T + s - 1) / s, n = (T + share - 1) / share;
+      consider(n, share, (units * n + slots - 1) / slots);   // (the last share may be shorter)
+      // the CUs that s shares per unit leave take a shorter share of every unit, m each
+      if (units * s >= slots || slots - units * s >= units) continue;   // (m = 1: s + 1 equal ones)
+      const uint32_t left = slots - units * s, m = (units + left - 1) / left;
+      const uint32_t big = (uint32_t)((m * T + (m - 1) * (ends / step)) / (1 + m * s)) + 1;
+      if (big * s + 2 > T || T - big * s > big) continue;
+      consider(s, big, 1);
+    }
+  }
+  return f;
+}
 SplitPlan plan_split(const Problem& p) {
   SplitPlan s;
   s.pipe = p.dh == kDh && p.E <= kPipeMaxSub;
@@ -1480,15 +1610,18 @@ SplitPlan plan_split(const Problem& p) {
     s.n_split = (T + s.tiles_per_split - 1) / s.tiles_per_split;
     return s;
   }
+  s.n_split = 1;
+  s.tiles_per_split = 0;
   s.bm = (!s.pipe && p.N <= 128) ? 64 : 256;
+  if (s.pipe) return s;          // flow_shares
   if (p.dh == 256) s.bm = 128;   // 4 waves of up to 512 registers (see launch_fwd_bf16)
   // (an empty batch is planned too, for its LDS: as one token block)
   const int64_t base = (p.N > s.bm ? (p.N + s.bm - 1) / s.bm : 1) * p.H;
   const int T = p.E * (p.de / kBI);
   int want = 1;
-  if (s.pipe || p.dh == 256) {   // one workgroup per CU
+  if (p.dh == 256) {   // one workgroup per CU
     if (base <= 128) want = (int)(256 / base);
-    else if (p.dh == 256 && base < 384) want = shares_256(p, s.pair, base, T);
+    else if (base < 384) want = shares_256(p, s.pair, base, T);
   } else if (base < 384) {
     want = (int)((512 + base - 1) / base);
   }
@@ -1518,21 +1651,16 @@ int launch_variant(const Problem& p, FwdArgs a, const SplitPlan& sp, hipStream_t
   return (int)hipGetLastError();
 }
 
-int launch_pipe(const Problem& p, FwdArgs a, const SplitPlan& sp, hipStream_t stream) {
-  a.n_tiles = (p.N + kPipeBM - 1) / kPipeBM;
-  a.n_split = sp.n_split;
-  a.tiles_per_split = sp.tiles_per_split;
-  a.n_items = a.n_tiles * p.H * sp.n_split;
+int launch_pipe(const Problem& p, FwdArgs a, hipStream_t stream) {
+  a.flow = flow_shares(p);
   const size_t lds = (size_t)3 * kPipeRing + (size_t)kPipeMaxSub * kPipeBM * sizeof(float);   // 1/r: 64 rows
   if (hipError_t e0 = LdsLimit<&fwd_bf16_flow_kernel, (int)kLdsBytesPerWorkgroup>::ensure(); e0 != hipSuccess)
     return (int)e0;
-  hipLaunchKernelGGL(fwd_bf16_flow_kernel, dim3((unsigned)xcd_grid_size(a.n_items)),
-                     dim3(64 * kPipeWaves), lds, stream, a);
+  hipLaunchKernelGGL(fwd_bf16_flow_kernel, dim3(a.flow.grid()), dim3(64 * kPipeWaves), lds, stream, a);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || sp.n_split == 1) return (int)e;
-  const int64_t n4 = p.N * p.H * kDh / 4;
-  hipLaunchKernelGGL(fwd_bf16_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0,
-                     stream, a);
+  if (e != hipSuccess || a.flow.shares() <= 1) return (int)e;
+  const uint32_t n4 = a.flow.n_units * a.flow.unit_tokens * (kDh / 4);
+  hipLaunchKernelGGL(fwd_bf16_flow_reduce_kernel, dim3((n4 + 255) / 256), dim3(256), 0, stream, a);
   return (int)hipGetLastError();
 }
 
@@ -1575,6 +1703,7 @@ int launch_decode(const Problem& p, FwdArgs a, const SplitPlan& sp, hipStream_t 
 size_t fwd_bf16_workspace_bytes(const Problem& p) {
   if (p.N == 0) return 0;
   const SplitPlan sp = plan_split(p);
+  if (sp.pipe && !sp.decode_nb) return flow_shares(p).partial_floats() * sizeof(float);
   int64_t splits = sp.n_split;
   if (p.dh == 256) {
     // The scratch asked for at this width is that of shares for two workgroups per CU, although
@@ -1610,7 +1739,7 @@ int launch_fwd_bf16(const Problem& p, const void* X, const void* Wg, const void*
   if (sp.decode_nb == 1) return launch_decode<1>(p, a, sp, st);
   if (sp.decode_nb == 2) return launch_decode<2>(p, a, sp, st);
   if (sp.decode_nb == 4) return launch_decode<4>(p, a, sp, st);
-  if (sp.pipe) return launch_pipe(p, a, sp, st);
+  if (sp.pipe) return launch_pipe(p, a, st);
   if (p.dh == 64) {
     if (sp.bm == 64) return launch_variant<64, 1, 2>(p, a, sp, st);
     return launch_variant<64, 1, 8>(p, a, sp, st);
@@ -1627,8 +1756,13 @@ int launch_fwd_bf16(const Problem& p, const void* X, const void* Wg, const void*
 
 std::string fwd_bf16_plan(const Problem& p) {
   const SplitPlan sp = plan_split(p);
+  if (sp.pipe && !sp.decode_nb) {
+    const FlowShares f = flow_shares(p);
+    return "flow whole=" + std::to_string(f.n_full) + " units=" + std::to_string(f.n_units) + "x" + std::to_string(f.unit_tokens) +
+           " tiles=" + std::to_string(f.equal) + "x" + std::to_string(f.share_tiles) + "+" + std::to_string(f.rest_tiles) +
+           " shares=" + std::to_string(f.n_units ? f.shares() : 1);
+  }
   const std::string kernel = sp.decode_nb ? "decode" + std::to_string(32 * sp.decode_nb)
-                             : sp.pipe    ? "flow"
                              : sp.pair    ? "pair256"
                                           : "tiles" + std::to_string(sp.bm);
   return kernel + " shares=" + std::to_string(sp.n_split);
