@@ -444,6 +444,86 @@ int launch_skinny(const TunedGemmArgs& a, hipStream_t stream) {
   return (int)hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// Up to 16 rows: a workgroup owns 16 columns of C, so that d_model = 2048 fills 128 CUs and not
+// 64.  Same idea otherwise: wave w takes the 64-wide k slices w, w + 16, .., every load in flight
+// before the first is waited for, the waves' partial tiles added up through LDS in wave order.
+// 16x16x32 products: MFMA rows are the columns of C, MFMA columns the rows of A, whose operand
+// is 16 bytes per lane of 16 rows as it lies in memory (no LDS); so is the weights' in row form.
+// Transposed weights pass through the wave's LDS slice ([32 k][16 n] per product) for the
+// transposing read.  Bound: one memory latency, and the 128-byte lines of the transposed weights,
+// of which a workgroup uses a quarter (neighbours share them in one L2; read past the L1 they
+// cost 3 us more).  Kernel above | this one: 1 x 1024 x 1024 4.9 | 4.0 us a product, 1 x 2048 x
+// 2048 7.3 | 6.3, 16 x 2048 x 2048 7.6 | 7.0; row form 1 x 2048 x 2048 0.7 less, 16 rows 0.2 more.
+// ---------------------------------------------------------------------------
+constexpr int kFewCols = 16, kFewTile = 1024;   // LDS of one product's transposed weights
+constexpr int kFewRowsTr = 16, kFewRows = 8;    // rows up to which it is the faster one, by the weights' form
+template <bool B_TR>
+__global__ __launch_bounds__(64 * kSkinnyWaves) void gemm_bf16_few_kernel(TunedGemmArgs a) {
+  constexpr int NW = kSkinnyWaves, SL = kSkinnySlices;
+  __shared__ __attribute__((aligned(16))) unsigned char smem[NW * SL * 2 * kFewTile];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int i16 = lane & 15, gq = lane >> 4;
+  const int64_t item = xcd_work_item(blockIdx.x, a.n_items);
+  if (item >= a.n_items) return;
+  const int64_t n0 = item * kFewCols;
+  const int KT = (int)(a.K / kSkinnyK);
+  unsigned char* btile = smem + wave * (SL * 2 * kFewTile);
+  const uint16_t* bsrc = B_TR ? a.B + (int64_t)(lane >> 1) * a.ldb + n0 + 8 * (lane & 1) : a.B + (n0 + i16) * a.ldb + 8 * gq;
+  const uint16_t* asrc = a.A + i16 * a.lda + 8 * gq;
+  f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  for (int s0 = wave; s0 < KT; s0 += NW * SL) {
+    u32x4 w[SL][2], x[SL][2];
+#pragma unroll
+    for (int s = 0; s < SL; ++s) {
+      const int sl = s0 + NW * s;
+      if (sl >= KT) continue;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int64_t k0 = (int64_t)sl * kSkinnyK + 32 * t;
+        w[s][t] = *reinterpret_cast<const u32x4*>(B_TR ? bsrc + k0 * a.ldb : bsrc + k0);
+        x[s][t] = u32x4{0, 0, 0, 0};
+        if (i16 < a.M) x[s][t] = *reinterpret_cast<const u32x4*>(asrc + k0);
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < SL; ++s) {
+      if (s0 + NW * s >= KT) continue;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        bf16x8 wf;
+        if constexpr (B_TR) {   // (the wave's own slice: its reads follow its stores in the same queue)
+          unsigned char* tile = btile + (2 * s + t) * kFewTile;
+          *reinterpret_cast<u32x4*>(tile + lane * 16) = w[s][t];
+          const unsigned char* p = tile + (8 * gq + (i16 >> 2)) * 32 + (i16 & 3) * 8;
+          wf = join_tr(lds_read_tr16(p), lds_read_tr16(p + 4 * 32));
+        } else {
+          wf = __builtin_bit_cast(bf16x8, w[s][t]);
+        }
+        acc = mfma16(wf, __builtin_bit_cast(bf16x8, x[s][t]), acc);
+      }
+    }
+  }
+  __syncthreads();
+  f32x4* red = reinterpret_cast<f32x4*>(smem);   // [wave][lane]
+  red[tid] = acc;
+  __syncthreads();
+  if (tid >= 64) return;
+  f32x4 sum = red[lane];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) sum += red[w * 64 + lane];
+  if (i16 < a.M)
+    *reinterpret_cast<u32x2*>(a.C + i16 * a.ldc + n0 + 4 * gq) = u32x2{pack_bf16(sum[0], sum[1]), pack_bf16(sum[2], sum[3])};
+}
+
+template <bool B_TR>
+int launch_few(TunedGemmArgs a, hipStream_t stream) {
+  a.n_items = a.N / kFewCols;
+  hipLaunchKernelGGL(gemm_bf16_few_kernel<B_TR>, dim3((unsigned)xcd_grid_size(a.n_items)), dim3(64 * kSkinnyWaves), 0, stream, a);
+  return (int)hipGetLastError();
+}
+
 // Tile shape and split of the contraction, from what was measured (clocks of a CU at 2.2 GHz):
 // a slice of k costs a workgroup kSliceClocks (the smaller shapes share the CU, so two of them
 // take as long as one after the other); a workgroup starts in about 4000 and stores its tile at
@@ -554,8 +634,10 @@ int launch_gemm_bf16(bool a_tr, bool b_tr, const void* A, int64_t lda, const voi
   a.slices_per_split = plan.slices_per_split;
   a.P = static_cast<float*>(ws);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (!a_tr && skinny_takes(M, N, K) && !accumulate)
+  if (!a_tr && skinny_takes(M, N, K) && !accumulate) {
+    if (M <= (b_tr ? kFewRowsTr : kFewRows)) return b_tr ? launch_few<true>(a, st) : launch_few<false>(a, st);
     return b_tr ? launch_skinny<true>(a, st) : launch_skinny<false>(a, st);
+  }
   if (a.splits > 1 && !ws) return -1;
   if (!a_tr && b_tr) return launch_form<false, true>(a, plan.shape, st);
   if (!a_tr && !b_tr) return launch_form<false, false>(a, plan.shape, st);
