@@ -393,6 +393,11 @@ __global__ __launch_bounds__(64 * NW, NW == 2 ? 2 : 1) void fwd_bf16_kernel(FwdA
 //     operand address an immediate offset from a loop-invariant per-lane register.
 // One barrier per step: it publishes the tiles requested one step ago and retires the K/U
 // stage of tile i+1 and the V stage of tile i-1.
+// Around the steps nothing overlaps (one workgroup per CU), so rows of X and Y move whole, through
+// LDS, partial outputs lie as the registers hold them, and no wait is wider than its data: 11.4 us
+// (a wave in operand layout touches 32 lines a load) -> about 8.  16384 tokens, H = 6, E = 16: 153 ->
+// 147 us; 6650 tokens, H = 4, 35 tiles 34 -> 31; given weights, one load in flight per thread ->
+// eight: 252 tokens, H = 2, E = 6 13.3 -> 11.1.
 // ---------------------------------------------------------------------------
 constexpr int kPipeStages = 4;
 constexpr int kPipeTile = kBI * kDh * 2;            // 8 KB, rows of 256 B, chunks swizzled
@@ -472,18 +477,30 @@ __global__ __launch_bounds__(64 * kPipeWaves) void fwd_bf16_flow_kernel(FwdArgs 
                       smem + ring * kPipeRing + stage * kPipeTile + wave_u * 1024);
   };
 
+  // this wave's token rows, through LDS that will hold 1/R; they are asked for ahead of the tiles
+  unsigned char* const rows_lds = smem + 3 * kPipeRing + wave_u * (32 * kDh * 2);
+  auto request_rows = [&]() {
+    if (active) wave_request_rows<kDh>(a.X + (tile_tok0 + wtok) * a.ldx + h * kDh, a.ldx, a.N - tile_tok0 - wtok, rows_lds, lane);
+  };
   bf16x8 q[8];
-  {
-    const int64_t tok = tile_tok0 + wtok + r;
-    const bool valid = tok < a.N;
-    const uint16_t* src = a.X + (valid ? tok : 0) * a.ldx + h * kDh + 8 * g;
+  auto read_rows = [&]() {
+    // (the requests of the tiles, eight, may stay in flight)
+    if (T >= 3) __builtin_amdgcn_s_waitcnt(0x0F78);   // vmcnt(8)
+    else __builtin_amdgcn_s_waitcnt(0x0F70);
+    const unsigned rows_addr = lds_addr_of(rows_lds);
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      bf16x8 v = *reinterpret_cast<const bf16x8*>(src + 16 * ks);
-      if (!valid) v = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-      q[ks] = v;
-    }
-  }
+    for (int ks = 0; ks < 8; ++ks) q[ks] = lds_read_b128_untracked<0>(rows_addr + tile_off(r, 2 * ks + g));
+#pragma unroll
+    for (int ks = 0; ks < 8; ks += 2) lds_wait<0>(q[ks], q[ks + 1]);
+    if (tile_tok0 + wtok + r >= a.N)
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) q[ks] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
+  };
+  auto lds_barrier = [&]() {   // this wave's LDS traffic has landed; loads may stay in flight
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
   // first requests: K/U tiles 0..2 and V tiles 0, 1 (stage 3 of every ring is the scratch of
   // the gating phase; K/U tile 3 follows it)
   auto first_requests = [&]() {
@@ -508,6 +525,7 @@ __global__ __launch_bounds__(64 * kPipeWaves) void fwd_bf16_flow_kernel(FwdArgs 
       wv[it] = u32x4{0, 0, 0, 0};
       if (c < kDh * E / 8) wv[it] = *reinterpret_cast<const u32x4*>(Wr + 8 * c);
     }
+    request_rows();
     first_requests();
     // (rows E.. of the operand keep whatever the memory held: a row of the product depends on
     // its own row of the operand only, and rows E.. are masked below)
@@ -524,7 +542,8 @@ __global__ __launch_bounds__(64 * kPipeWaves) void fwd_bf16_flow_kernel(FwdArgs 
         }
       }
     }
-    __syncthreads();
+    read_rows();
+    lds_barrier();   // W_r staged; the rows are in registers, their LDS is free
     if (active) {
       f32x16 acc[2] = {f32x16{0}, f32x16{0}};
       bf16x8 af[2][8];
@@ -532,7 +551,9 @@ __global__ __launch_bounds__(64 * kPipeWaves) void fwd_bf16_flow_kernel(FwdArgs 
       for (int eb = 0; eb < 2; ++eb)
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks)
-          af[eb][ks] = *reinterpret_cast<const bf16x8*>(smem + wr_off(32 * (eb < EB ? eb : 0) + r, 2 * ks + g));
+          af[eb][ks] = lds_read_b128_untracked<0>(lds_addr_of(smem) + wr_off(32 * (eb < EB ? eb : 0) + r, 2 * ks + g));
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) lds_wait<0>(af[0][ks], af[1][ks]);
 #pragma unroll
       for (int ks = 0; ks < 8; ++ks) {
         acc[0] = mfma32(af[0][ks], q[ks], acc[0]);
@@ -559,12 +580,30 @@ __global__ __launch_bounds__(64 * kPipeWaves) void fwd_bf16_flow_kernel(FwdArgs 
       }
     }
   } else {
-    first_requests();
     const float* R = reinterpret_cast<const float*>(a.route);
-    for (int idx = tid; idx < bm * E; idx += THREADS) {
-      const int tl = idx / E, e = idx - tl * E;
-      const int64_t tok = tile_tok0 + tl;
-      Rs[e * BM + tl] = inv_weight((tok < a.N) ? R[((size_t)tok * a.H + h) * E + e] : 0.f);
+    constexpr int kBatch = 8;   // loads in flight per thread (one after the other: 1 us each)
+    float rv[kBatch];
+    auto load_r = [&](int idx0) {
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        const int idx = idx0 + i * THREADS + tid, tl = idx / E, e = idx - tl * E;
+        const int64_t tok = tile_tok0 + tl;
+        rv[i] = 0.f;
+        if (idx < bm * E && tok < a.N) rv[i] = R[((size_t)tok * a.H + h) * E + e];
+      }
+    };
+    load_r(0);
+    request_rows();
+    first_requests();
+    read_rows();
+    lds_barrier();   // the rows are in registers, their LDS is free
+    for (int idx0 = 0; idx0 < bm * E; idx0 += kBatch * THREADS) {
+      if (idx0 > 0) load_r(idx0);
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        const int idx = idx0 + i * THREADS + tid, tl = idx / E;
+        if (idx < bm * E) Rs[(idx - tl * E) * BM + tl] = inv_weight(rv[i]);
+      }
     }
   }
   __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0): the first tiles have landed
@@ -781,34 +820,18 @@ __global__ __launch_bounds__(64 * kPipeWaves) void fwd_bf16_flow_kernel(FwdArgs 
   }
   __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the reads issued for a step that never comes
 
-  const int64_t tok = tile_tok0 + wtok + r;
   if (!active) return;
   if (!whole && fs.shares() > 1) {
-    if (tok < a.N) {
-      float* dst = a.P + (((size_t)share * fs.n_units + unit) * bm + wtok + r) * kDh + 4 * g;
+    // as they lie in the registers: [share][unit][wave][quad 4 jb + vq][lane]
+    f32x4* dst = reinterpret_cast<f32x4*>(a.P) + (((size_t)share * fs.n_units + unit) * (bm / 32) + wave_u) * 1024 + lane;
 #pragma unroll
-      for (int jb = 0; jb < 4; ++jb)
+    for (int jb = 0; jb < 4; ++jb)
 #pragma unroll
-        for (int vq = 0; vq < 4; ++vq) {
-          f32x4 o = {O[jb][4 * vq], O[jb][4 * vq + 1], O[jb][4 * vq + 2], O[jb][4 * vq + 3]};
-          *reinterpret_cast<f32x4*>(dst + 32 * jb + 8 * vq) = o;
-        }
-    }
+      for (int vq = 0; vq < 4; ++vq)
+        dst[(4 * jb + vq) * 64] = f32x4{O[jb][4 * vq], O[jb][4 * vq + 1], O[jb][4 * vq + 2], O[jb][4 * vq + 3]};
     return;
   }
-  if (tok < a.N) {
-    uint16_t* dst = a.Y + tok * a.ldy + h * kDh + 4 * g;
-#pragma unroll
-    for (int jb = 0; jb < 4; ++jb) {
-#pragma unroll
-      for (int vq = 0; vq < 4; ++vq) {
-        u32x2 pkw;
-        pkw[0] = pack_bf16(O[jb][4 * vq], O[jb][4 * vq + 1]);
-        pkw[1] = pack_bf16(O[jb][4 * vq + 2], O[jb][4 * vq + 3]);
-        *reinterpret_cast<u32x2*>(dst + 32 * jb + 8 * vq) = pkw;
-      }
-    }
-  }
+  wave_store_rows<kDh>(O, a.Y + (tile_tok0 + wtok) * a.ldy + h * kDh, a.ldy, a.N - tile_tok0 - wtok, smem + wave_u * (32 * kDh * 2), lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -1479,20 +1502,25 @@ __device__ __forceinline__ void add_partials(f32x4& sum, const float* src, size_
   for (int i = 0; i < 7; ++i) sum += v[i];
 }
 
-// Y = bf16(sum over the shares), for the units of fwd_bf16_flow_kernel: thread = 4 columns of one token of a unit
-__global__ void fwd_bf16_flow_reduce_kernel(FwdArgs a) {
+// Y = bf16(sum over the shares), for the units of fwd_bf16_flow_kernel: a workgroup takes 32 columns
+// (blockIdx.y) of a wave's 32 tokens, a thread four of one token
+__global__ __launch_bounds__(256) void fwd_bf16_flow_reduce_kernel(FwdArgs a) {
+  constexpr int kRow = 64 + 16;   // bytes of LDS per token
+  __shared__ __attribute__((aligned(16))) unsigned char rows[32 * kRow];
   const FlowShares& fs = a.flow;
-  const uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x, row = idx / (kDh / 4), col = 4 * (idx % (kDh / 4));
-  const uint32_t unit = row / fs.unit_tokens, u = fs.unit0 + unit;
-  if (unit >= fs.n_units) return;
-  const int64_t tok = (int64_t)(u % fs.unit_tiles) * fs.unit_tokens + row % fs.unit_tokens;
-  if (tok >= a.N) return;
-  const size_t stride = (size_t)fs.n_units * fs.unit_tokens * kDh;
-  const float* src = a.P + (size_t)row * kDh + col;
+  const uint32_t waves = fs.unit_tokens / 32, unit = blockIdx.x / waves, u = fs.unit0 + unit;
+  const int64_t tok0 = (int64_t)(u % fs.unit_tiles) * fs.unit_tokens + 32 * (blockIdx.x % waves);
+  if (tok0 >= a.N) return;
+  const int tid = threadIdx.x, lane = tid & 63;
   f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-  add_partials(sum, src, stride, (int)fs.shares());
-  *reinterpret_cast<u32x2*>(a.Y + tok * a.ldy + (int64_t)(u / fs.unit_tiles) * kDh + col) =
+  add_partials(sum, a.P + ((size_t)blockIdx.x * 1024 + blockIdx.y * 256 + tid) * 4, (size_t)fs.n_units * fs.unit_tokens * kDh, (int)fs.shares());
+  *reinterpret_cast<u32x2*>(rows + (lane & 31) * kRow + 16 * (tid >> 6) + 8 * (lane >> 5)) =
       u32x2{pack_bf16(sum[0], sum[1]), pack_bf16(sum[2], sum[3])};
+  __syncthreads();
+  const int row = tid >> 2, chunk = tid & 3;
+  if (tid < 128 && tok0 + row < a.N)
+    *reinterpret_cast<u32x4*>(a.Y + (tok0 + row) * a.ldy + (int64_t)(u / fs.unit_tiles) * kDh + 32 * blockIdx.y + 8 * chunk) =
+        *reinterpret_cast<const u32x4*>(rows + row * kRow + 16 * chunk);
 }
 
 // Y[tok][col] = bf16(sum_s P[s][tok][col]), fixed order
@@ -1659,8 +1687,7 @@ int launch_pipe(const Problem& p, FwdArgs a, hipStream_t stream) {
   hipLaunchKernelGGL(fwd_bf16_flow_kernel, dim3(a.flow.grid()), dim3(64 * kPipeWaves), lds, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.flow.shares() <= 1) return (int)e;
-  const uint32_t n4 = a.flow.n_units * a.flow.unit_tokens * (kDh / 4);
-  hipLaunchKernelGGL(fwd_bf16_flow_reduce_kernel, dim3((n4 + 255) / 256), dim3(256), 0, stream, a);
+  hipLaunchKernelGGL(fwd_bf16_flow_reduce_kernel, dim3(a.flow.n_units * a.flow.unit_tokens / 32, 4), dim3(256), 0, stream, a);
   return (int)hipGetLastError();
 }
 

@@ -187,6 +187,45 @@ __device__ __forceinline__ unsigned lds_addr_of(const void* p) {
   return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
 }
 
+// Rows of DH bf16 between memory and a wave's operand layout, through wave-private LDS (32 rows,
+// 64 DH bytes): in operand layout a load or store touches 32 rows, 16 or 32 bytes of each, and
+// the address unit takes a 128-byte line a clock; here a wave moves whole rows.
+//
+// Request: lane l fetches the chunk that the swizzle maps to its place.  Rows past the last one
+// repeat it.  `src` points at column 0 of row 0.  Completion is counted by vmcnt (DH / 16 loads).
+template <int DH>
+__device__ __forceinline__ void wave_request_rows(const uint16_t* src, int64_t ld, int64_t rows, unsigned char* lds, int lane) {
+  constexpr int CPR = DH / 8, RPL = 64 / CPR;
+  const int last = rows < 32 ? (int)rows - 1 : 31;
+#pragma unroll
+  for (int i = 0; i < 32 / RPL; ++i) {
+    const int row = RPL * i + lane / CPR;
+    const int chunk = (tile_off_dh<DH>(row, lane % CPR) - row * 2 * DH) >> 4;   // (an involution within a row)
+    global_to_lds_16B(src + min(row, last) * ld + chunk * 8, lds + i * 1024);
+  }
+}
+// Store: acc[jb] holds columns 32 jb + 8 vq + 4 g + i of row lane % 32 in its registers 4 vq + i.
+template <int DH>
+__device__ __forceinline__ void wave_store_rows(const f32x16 (&acc)[DH / 32], uint16_t* dst, int64_t ld, int64_t rows,
+                                                unsigned char* lds, int lane) {
+  constexpr int CPR = DH / 8, RPL = 64 / CPR;
+  const int r = lane & 31, g = lane >> 5;
+#pragma unroll
+  for (int jb = 0; jb < DH / 32; ++jb)
+#pragma unroll
+    for (int vq = 0; vq < 4; ++vq) {
+      const u32x2 pk = {pack_bf16(acc[jb][4 * vq], acc[jb][4 * vq + 1]), pack_bf16(acc[jb][4 * vq + 2], acc[jb][4 * vq + 3])};
+      *reinterpret_cast<u32x2*>(lds + tile_off_dh<DH>(r, 4 * jb + vq) + 8 * g) = pk;
+    }
+  __builtin_amdgcn_wave_barrier();   // (one wave: its reads follow its writes in the same queue)
+#pragma unroll
+  for (int i = 0; i < 32 / RPL; ++i) {
+    const int row = RPL * i + lane / CPR, chunk = lane % CPR;
+    const u32x4 v = *reinterpret_cast<const u32x4*>(lds + tile_off_dh<DH>(row, chunk));
+    if (row < rows) *reinterpret_cast<u32x4*>(dst + row * ld + chunk * 8) = v;
+  }
+}
+
 // XCD-aware work distribution.  Workgroups are handed to the 8 XCDs round
 // robin by blockIdx, and every XCD has a private L2.  The head-major work list
 // (item = head * n_tiles + tile) is cut into 8 contiguous chunks, one per XCD,
