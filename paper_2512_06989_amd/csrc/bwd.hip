@@ -18,9 +18,10 @@
 //       workgroups; the derivative and the sum of the partial dX then run in
 //       bwd_finish.hip.  1536 tokens, H = 16, E = 22, d_e = 384 (96 blocks on 256 CUs):
 //       0.489 ms as one workgroup per block, 0.30 + 0.01 ms as two.  What a workgroup does
-//       before and after its steps is 30 us of 450 at the 1.3B shape (it was 60 with a
-//       device-wide fence, two gating passes and a load behind every store of dp: 1.80 ->
-//       1.67 ms for the kernel).
+//       before and after its steps is 24 us of 408 at the 1.3B shape, 6 of them the rows of X and dY
+//       (all CUs read theirs at the same time), 16 at E = 7.  It was 30 and 20 with rows in operand
+//       layout, r_e read back from memory and a comparison per sub-network; a device-wide fence
+//       and a load behind every store of dp made it 60.
 //   bwd_wgt16_kernel (appendix algorithm "Backward (dK,dU,dV)")
 //       one wave = 16 neurons of one head, K/U/V rows resident in registers as
 //       MFMA operands, loop over all tokens:
@@ -109,10 +110,12 @@ struct BwdArgs {
   // [wsplit][3][8 * (gpx - full_px) groups][128 rows][128]
   int gpx, full_px, n_groups;
   // token-major kernel with the sub-networks of a token block shared out over `shares`
-  // workgroups (few tokens): partial dX [shares][N][H*dh] fp32 and 1 / (Z + eps) [H][N]
+  // workgroups (few tokens): partial dX fp32, [shares][token blocks][waves] of 32 x d_h as the
+  // registers hold them, and 1 / (Z + eps) [H][N]
   float* XPws;
   float* Zws;
   int shares, subs_per_share;
+  int keep_r;   // token-major kernel: LDS holds a second copy of the gating weights
   int64_t N, ldx, ldy, n_tiles, n_items;
   int H, E, de, dh, route_mode, n_split;
   float eps;
@@ -157,7 +160,8 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
   constexpr bool kAllLoad = (CHUNKS % THREADS == 0);   // else the upper threads carry none
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];   // (the one-wave pipeline XORs address bits)
   unsigned char* stage_base = smem;
-  float* DRs = reinterpret_cast<float*>(smem + kTokStages * kTokStageBytes);  // [E][BM]: r_e, then dr_e
+  // [E][BM]: r_e, then dr_e; with a.keep_r [E][BM] more: r_e to the end
+  float* DRs = reinterpret_cast<float*>(smem + kTokStages * kTokStageBytes);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 31, g = lane >> 5;
@@ -213,10 +217,11 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
   unsigned char* scratch = stage_base + (DMA ? 2 * kTokStageBytes : 0);
 
   // W_r of the head, 16 bytes per thread and round, requested ahead of everything else
-  constexpr int kWrRounds = (DH * (DH == 256 ? 64 : kTokMaxSub) / 8 + THREADS - 1) / THREADS;
+  constexpr int kMaxSub = DH == 256 ? 64 : DMA ? 88 : kTokMaxSub, kMaxEB = (kMaxSub + 31) / 32;
+  constexpr int kWrRounds = (DH * kMaxSub / 8 + THREADS - 1) / THREADS;
   u32x4 wr[kWrRounds];
   const uint16_t* Wr = reinterpret_cast<const uint16_t*>(a.route) + (size_t)h * DH * E;
-  auto load_wr = [&]() {
+  auto load_wr = [&](int tid) {
 #pragma unroll
     for (int i = 0; i < kWrRounds; ++i) {
       const int c = tid + THREADS * i;
@@ -225,7 +230,7 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
     }
   };
   // element (j, e) of what load_wr fetched goes to LDS byte at(j, e)
-  auto store_wr = [&](unsigned char* dst, auto at) {
+  auto store_wr = [&](int tid, unsigned char* dst, auto at) {
 #pragma unroll
     for (int i = 0; i < kWrRounds; ++i) {
       const int c = tid + THREADS * i;
@@ -239,27 +244,40 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
       }
     }
   };
-  if (a.route_mode == 0) load_wr();
-
+  // Token rows of X and dY: whole rows through this wave's part of LDS, ahead of everything that
+  // LDS holds later (in operand layout, 32 rows a load, they took 3.3 us of the 20 around a
+  // workgroup's steps; 6.3 at d_h = 256)
+  static_assert(TB == 1, "one block of 32 tokens per wave");
+  constexpr int kRowsBytes = 64 * DH;
+  const int64_t rows = N - tile_tok0 - wtok;        // of this wave's 32, may be <= 0
+  unsigned char* const rows_lds = smem + wave_u * (2 * kRowsBytes);
   bf16x8 q[TB][KS], dy[TB][KS];
   int64_t tok[TB];
   bool valid[TB];
-#pragma unroll
-  for (int tb = 0; tb < TB; ++tb) {
-    tok[tb] = tile_tok0 + wtok + 32 * tb + r;
-    valid[tb] = tok[tb] < N;
-    const int64_t t = valid[tb] ? tok[tb] : 0;
-    const uint16_t* sx = a.X + t * a.ldx + h * DH + 8 * g;
-    const uint16_t* sy = a.dY + t * a.ldy + h * DH + 8 * g;
+  tok[0] = tile_tok0 + wtok + r;
+  valid[0] = r < rows;
+  if (a.route_mode == 0) load_wr(tid);
+  if (rows > 0) {
+    wave_request_rows<DH>(a.X + (tile_tok0 + wtok) * a.ldx + h * DH, a.ldx, rows, rows_lds, lane);
+    wave_request_rows<DH>(a.dY + (tile_tok0 + wtok) * a.ldy + h * DH, a.ldy, rows, rows_lds + kRowsBytes, lane);
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+  asm volatile("" ::: "memory");
+  {
+    const unsigned rows_addr = lds_addr_of(rows_lds);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      bf16x8 vx = *reinterpret_cast<const bf16x8*>(sx + 16 * ks);
-      bf16x8 vy = *reinterpret_cast<const bf16x8*>(sy + 16 * ks);
-      if (!valid[tb]) { vx = bf16x8{0, 0, 0, 0, 0, 0, 0, 0}; vy = vx; }
-      q[tb][ks] = vx;
-      dy[tb][ks] = vy;
+      q[0][ks] = lds_read_b128_untracked<0>(rows_addr + tile_off_dh<DH>(r, 2 * ks + g));
+      dy[0][ks] = lds_read_b128_untracked<kRowsBytes>(rows_addr + tile_off_dh<DH>(r, 2 * ks + g));
     }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) lds_wait<0>(q[0][ks], dy[0][ks]);
+    if (!valid[0])
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) q[0][ks] = dy[0][ks] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
   }
+  __builtin_amdgcn_s_barrier();         // every wave's rows are in registers: LDS is free
+  asm volatile("" ::: "memory");
   if constexpr (DMA) {
     dma(0, 0);
     if (T > 1) dma(1, 1);
@@ -273,46 +291,60 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
     const int EB = (E + 31) >> 5;
     // W_r^T as [32*EB][DH] bf16, swizzled rows (rows E.. keep whatever the memory held: a row
     // of the product depends on its own row of the operand only, and rows E.. are masked below)
-    store_wr(scratch, [&](int j, int e) { return btile_off<DH>(e, j >> 3) + (j & 7) * 2; });
+    store_wr(tid, scratch, [&](int j, int e) { return btile_off<DH>(e, j >> 3) + (j & 7) * 2; });
     __syncthreads();
-    float zsum[TB];
+    float sg[kMaxEB][16], zsum = 0.f;
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb) zsum[tb] = 0.f;
-    // sigmoid(p_e) to LDS, then r_e = sigmoid(p_e) / (Z + eps) in its place; every lane comes
-    // back to its own elements
-    for (int eb = 0; eb < EB; ++eb) {
+    for (int eb = 0; eb < kMaxEB; ++eb) {
+      if (eb >= EB) break;
+      f32x16 acc = {0};
 #pragma unroll
-      for (int tb = 0; tb < TB; ++tb) {
-        f32x16 acc = {0};
+      for (int ks = 0; ks < KS; ++ks) {
+        const bf16x8 af = *reinterpret_cast<const bf16x8*>(scratch + btile_off<DH>(32 * eb + r, 2 * ks + g));
+        acc = mfma32(af, q[0][ks], acc);
+      }
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          const bf16x8 af = *reinterpret_cast<const bf16x8*>(scratch + btile_off<DH>(32 * eb + r, 2 * ks + g));
-          acc = mfma32(af, q[tb][ks], acc);
-        }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int e = 32 * eb + 8 * (v / 4) + 4 * g + (v % 4);
-          const float s = (e < E) ? sigmoid_fast(acc[v]) : 0.f;
-          zsum[tb] += s;
-          if (e < E) DRs[e * BM + wtok + 32 * tb + r] = s;
-        }
+      for (int v = 0; v < 16; ++v) {
+        const int e = 32 * eb + 8 * (v / 4) + 4 * g + (v % 4);
+        sg[eb][v] = (e < E) ? sigmoid_fast(acc[v]) : 0.f;
+        zsum += sg[eb][v];
       }
     }
     if constexpr (DMA) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), ahead of the stores of R
+    inv[0] = 1.0f / (zsum + __shfl_xor(zsum, 32) + a.eps);
+    // r_e to LDS, where it waits until sub-network e has been swept (and a copy that stays), and, for
+    // this workgroup's share, to the workspace.  Eight sub-networks at a time: a comparison per
+    // element costs more than the element.
+    float* dr_lane = DRs + wtok + r;
+    const int copy = a.keep_r ? E * BM : 0;
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb) {
-      const float z = zsum[tb] + __shfl_xor(zsum[tb], 32);
-      inv[tb] = 1.0f / (z + a.eps);
-      for (int eb = 0; eb < EB; ++eb)
+    for (int eb = 0; eb < kMaxEB; ++eb) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int e = 32 * eb + 8 * (v / 4) + 4 * g + (v % 4);
-          if (e < E) {
-            const float rv = DRs[e * BM + wtok + 32 * tb + r] * inv[tb];
-            DRs[e * BM + wtok + 32 * tb + r] = rv;   // until sub-network e has been swept
-            if (valid[tb] && e >= e_begin && e < e_end) Rh[(size_t)e * N + tok[tb]] = rv;
-          }
+      for (int o = 0; o < 4; ++o) {
+        const int e8 = 32 * eb + 8 * o, e4 = e8 + 4 * g;
+        if (e8 >= E) break;
+        float rv[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) rv[i] = sg[eb][4 * o + i] * inv[0];
+        if (e8 + 8 <= E) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) dr_lane[(e4 + i) * BM] = dr_lane[(e4 + i) * BM + copy] = rv[i];
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (e4 + i < E) dr_lane[(e4 + i) * BM] = dr_lane[(e4 + i) * BM + copy] = rv[i];
         }
+        if (!valid[0]) continue;
+        float* out = Rh + (size_t)e4 * N + tok[0];
+        if (e8 >= e_begin && e8 + 8 <= e_end) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) out[i * N] = rv[i];
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (e4 + i >= e_begin && e4 + i < e_end) out[i * N] = rv[i];
+        }
+      }
     }
   } else {
     const float* R = reinterpret_cast<const float*>(a.route);
@@ -365,6 +397,7 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
   for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
     for (int jb = 0; jb < JB; ++jb) dXa[tb][jb] = f32x16{0};
+  const bool whole = a.shares == 1;
 
   float rw[TB], drp[TB];
 #pragma unroll
@@ -708,6 +741,8 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
     };
     step(0, std::true_type{});
     for (int t = 1; t < T; ++t) step(t, std::false_type{});
+    if (whole && a.route_mode == 0) load_wr(tid);   // on its way under the last products
+    MHFFN_SB();
     run_stream(IC0{}, ICT{}, sto0 + prev * kTokStageBytes, 0u);
     close_half(false, false, 0u);
     if (!late) bare_barrier();
@@ -848,7 +883,13 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
   }
 
   // ---- derivative through the gating weights ------------------------------------
-  const bool whole = a.shares == 1;
+  // (the lane's coordinates anew: kept across the loop they cost registers that it does not have)
+  {
+  const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  const int r = lane & 31, g = lane >> 5, wtok = 32 * wave_u;
+  const int64_t rows = N - tile_tok0 - wtok;
+  const bool valid[1] = {r < rows};
+  const int64_t tok[1] = {tile_tok0 + wtok + r};
   if (!whole && a.route_mode == 0) {
     // a share leaves its dr_e; the sum over all sub-networks is taken by bwd_finish.hip
 #pragma unroll
@@ -858,53 +899,50 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
         if (share == 0 && g == 0) a.Zws[(size_t)h * N + tok[tb]] = inv[tb];
       }
   } else if (a.route_mode == 0) {
-    // stage W_r[h] as rows j, columns e (zero padded to 32*EB), for the A operand
+    // stage W_r[h] as rows j, columns e, for the A operand (columns E.. are masked when read)
     const int EB = (E + 31) >> 5;
     const int wr_stride = 64 * EB + 16;  // bytes per row; +16 keeps rows off the same banks
-    load_wr();
-    // (weights r_e come back from the workspace in batches: a load behind every store of dp
-    // would be waited for alone)
+    if constexpr (!PHASED) load_wr(64 * wave_u + lane);
+    // (where LDS has no room for a second copy, the weights r_e come back from the workspace, in
+    // batches: a load behind every store of dp would be waited for alone)
     constexpr int kBatch = 24;
-    float rr[TB][kBatch], dot[TB];
-    auto load_r = [&](int tb, int e0) {
+    float rr[kBatch], dd[kBatch], dot = 0.f;
+    float* drcol = DRs + wtok + r;
+    // lanes g = 0 and g = 1 of a token split the sub-networks between them: e0 + 2 i + g (past the
+    // last one, its values once more, unused)
+    auto load_r = [&](int e0) {
 #pragma unroll
-      for (int i = 0; i < kBatch; ++i) {
-        const int e = e0 + 2 * i;
-        rr[tb][i] = (valid[tb] && e < E) ? Rh[(size_t)e * N + tok[tb]] : 0.f;
+      for (int i = 0; i < kBatch; ++i) dd[i] = drcol[min(e0 + 2 * i + g, E - 1) * BM];
+      if (a.keep_r) {
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) rr[i] = drcol[(E + min(e0 + 2 * i + g, E - 1)) * BM];
+      } else {
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) rr[i] = valid[0] ? Rh[(size_t)min(e0 + 2 * i + g, E - 1) * N + tok[0]] : 0.f;
       }
     };
-    // lanes g = 0 and g = 1 of a token split the sub-networks between them
+    for (int e0 = 0; e0 < E; e0 += 2 * kBatch) {
+      load_r(e0);
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb) {
-      const float* drcol = DRs + wtok + 32 * tb + r;
-      dot[tb] = 0.f;
-      for (int e0 = g; e0 < E; e0 += 2 * kBatch) {
-        load_r(tb, e0);
-#pragma unroll
-        for (int i = 0; i < kBatch; ++i)
-          if (e0 + 2 * i < E) dot[tb] = fmaf(drcol[(e0 + 2 * i) * BM], rr[tb][i], dot[tb]);
+      for (int i = 0; i < kBatch; ++i) {
+        const float d = fmaf(dd[i], rr[i], dot);
+        dot = e0 + 2 * i + g < E ? d : dot;
       }
-      dot[tb] += __shfl_xor(dot[tb], 32);
     }
-    store_wr(stage_base, [&](int j, int e) { return j * wr_stride + e * 2; });
-    const int epad = 32 * EB - E;   // zeros
-    for (int idx = tid; idx < DH * epad; idx += THREADS)
-      *reinterpret_cast<uint16_t*>(stage_base + (idx / epad) * wr_stride + (E + idx % epad) * 2) = 0;
+    dot += __shfl_xor(dot, 32);
+    store_wr(64 * wave_u + lane, stage_base, [&](int j, int e) { return j * wr_stride + e * 2; });
+    const float zpe = 1.0f / inv[0];
+    for (int e0 = 0; e0 < E; e0 += 2 * kBatch) {
+      if (E > 2 * kBatch) load_r(e0);   // else they are still there
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb) {
-      float* drcol = DRs + wtok + 32 * tb + r;
-      const float zpe = 1.0f / inv[tb];
-      for (int e0 = g; e0 < E; e0 += 2 * kBatch) {
-        if (E > 2 * kBatch) load_r(tb, e0);   // else they are still there
-#pragma unroll
-        for (int i = 0; i < kBatch; ++i) {
-          const int e = e0 + 2 * i;
-          if (e < E) {
-            const float s = rr[tb][i] * zpe;
-            const float dp = valid[tb] ? (drcol[e * BM] - dot[tb]) * inv[tb] * s * (1.0f - s) : 0.f;
-            if (valid[tb]) DPh[(size_t)e * N + tok[tb]] = dp;
-            drcol[e * BM] = dp;
-          }
+      for (int i = 0; i < kBatch; ++i) {
+        if (e0 + 2 * i >= E) break;
+        const int e = e0 + 2 * i + g;
+        const float s = rr[i] * zpe;
+        const float dp = valid[0] ? (dd[i] - dot) * inv[0] * s * (1.0f - s) : 0.f;
+        if (e < E) {
+          if (valid[0]) DPh[(size_t)e * N + tok[0]] = dp;
+          drcol[e * BM] = dp;
         }
       }
     }
@@ -922,11 +960,17 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
           pk[i] = pack_bf16(d0, d1);
         }
         const bf16x8 bp = __builtin_bit_cast(bf16x8, pk);
+        u32x4 in;   // columns that exist (the others hold whatever the memory held)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int e0 = 16 * ks + 8 * g + 2 * i;
+          in[i] = e0 + 1 < E ? 0xFFFFFFFFu : e0 < E ? 0xFFFFu : 0u;
+        }
 #pragma unroll
         for (int jb = 0; jb < JB; ++jb) {
-          const bf16x8 aw = *reinterpret_cast<const bf16x8*>(stage_base + (32 * jb + r) * wr_stride +
-                                                             (16 * ks + 8 * g) * 2);
-          dXa[tb][jb] = mfma32(aw, bp, dXa[tb][jb]);
+          u32x4 aw = *reinterpret_cast<const u32x4*>(stage_base + (32 * jb + r) * wr_stride + (16 * ks + 8 * g) * 2);
+          aw &= in;
+          dXa[tb][jb] = mfma32(__builtin_bit_cast(bf16x8, aw), bp, dXa[tb][jb]);
         }
       }
     }
@@ -944,31 +988,21 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
     }
   }
 
-  if (a.dX) {
+  if (!a.dX) return;
+  if (!whole) {
+    // as they lie in the registers: [share][block][wave][quad 4 jb + vq][lane]
+    if (rows <= 0) return;
+    f32x4* dst = reinterpret_cast<f32x4*>(a.XPws) + (((size_t)share * a.H * a.n_tiles + ht) * NW + wave_u) * (8 * DH) + lane;
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb) {
-      if (valid[tb] && !whole) {
-        float* dst = a.XPws + (((size_t)share * N + tok[tb]) * a.H + h) * DH + 4 * g;
+    for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
-        for (int jb = 0; jb < JB; ++jb)
-#pragma unroll
-          for (int vq = 0; vq < 4; ++vq)
-            *reinterpret_cast<f32x4*>(dst + 32 * jb + 8 * vq) =
-                f32x4{dXa[tb][jb][4 * vq], dXa[tb][jb][4 * vq + 1], dXa[tb][jb][4 * vq + 2], dXa[tb][jb][4 * vq + 3]};
-      } else if (valid[tb]) {
-        uint16_t* dst = a.dX + tok[tb] * a.ldx + h * DH + 4 * g;
-#pragma unroll
-        for (int jb = 0; jb < JB; ++jb) {
-#pragma unroll
-          for (int vq = 0; vq < 4; ++vq) {
-            u32x2 pk;
-            pk[0] = pack_bf16(dXa[tb][jb][4 * vq], dXa[tb][jb][4 * vq + 1]);
-            pk[1] = pack_bf16(dXa[tb][jb][4 * vq + 2], dXa[tb][jb][4 * vq + 3]);
-            *reinterpret_cast<u32x2*>(dst + 32 * jb + 8 * vq) = pk;
-          }
-        }
-      }
-    }
+      for (int vq = 0; vq < 4; ++vq)
+        dst[(4 * jb + vq) * 64] =
+            f32x4{dXa[0][jb][4 * vq], dXa[0][jb][4 * vq + 1], dXa[0][jb][4 * vq + 2], dXa[0][jb][4 * vq + 3]};
+    return;
+  }
+  __syncthreads();   // W_r has been read: LDS is free
+  wave_store_rows<DH>(dXa[0], a.dX + (tile_tok0 + wtok) * a.ldx + h * DH, a.ldx, rows, smem + wave_u * kRowsBytes, lane);
   }
 }
 
@@ -2565,15 +2599,24 @@ constexpr int kFullLds = (int)kLdsBytesPerWorkgroup;
 
 constexpr int tok_block_tokens(int dh) { return dh == 128 ? 256 : 128; }
 
-// LDS of the token-major kernel: the weight stages and dr_e of every token of the block
+// LDS of the token-major kernel: the weight stages, dr_e of every token of the block and, where the
+// workgroups that share a CU (d_h = 64: two) have room for it, r_e; at the start, the block's rows of
+// X and dY
+size_t tok_steps_lds(const Problem& p, bool dma, int copies) {
+  return (size_t)tok_stages(dma) * tok_stage_bytes(p.dh) + (size_t)copies * p.E * tok_block_tokens(p.dh) * sizeof(float);
+}
+bool tok_keeps_r(const Problem& p, bool dma) {
+  return tok_steps_lds(p, dma, 2) <= kLdsBytesPerWorkgroup / (p.dh == 64 ? 2 : 1);
+}
 size_t tok_lds_bytes(const Problem& p, bool dma) {
-  return (size_t)tok_stages(dma) * tok_stage_bytes(p.dh) +
-         (size_t)p.E * tok_block_tokens(p.dh) * sizeof(float);
+  const size_t steps = tok_steps_lds(p, dma, tok_keeps_r(p, dma) ? 2 : 1);
+  const size_t rows = (size_t)tok_block_tokens(p.dh) * p.dh * 4;
+  return steps > rows ? steps : rows;
 }
 // direct staging (three stages) where it fits: d_h = 128 with up to 88 sub-networks, d_h = 256
 // (stages of 48 KB) with up to 32
 bool tok_direct_staging(const Problem& p) {
-  return (p.dh == 128 || p.dh == 256) && tok_lds_bytes(p, true) <= kLdsBytesPerWorkgroup;
+  return (p.dh == 128 || p.dh == 256) && tok_steps_lds(p, true, 1) <= kLdsBytesPerWorkgroup;
 }
 
 // Shares of the sub-networks per token block: few tokens leave CUs without a workgroup, or the
@@ -2607,7 +2650,8 @@ TokShares plan_tok_shares(const Problem& p) {
 }
 size_t tok_share_bytes(const Problem& p) {
   const int s = plan_tok_shares(p).shares;
-  return s > 1 ? (size_t)s * p.N * p.H * p.dh * sizeof(float) : 0;
+  const int64_t bm = tok_block_tokens(p.dh);
+  return s > 1 ? (size_t)s * ((p.N + bm - 1) / bm * bm) * p.H * p.dh * sizeof(float) : 0;
 }
 
 template <int DH, int TB, int NW, bool DMA = false, bool PHASED = false, bool PIPE = false>
@@ -2617,13 +2661,14 @@ int launch_tok(const Problem& p, BwdArgs a, hipStream_t stream) {
   a.n_tiles = (p.N + BM - 1) / BM;
   a.n_items = a.n_tiles * p.H * a.shares;
   const size_t lds = tok_lds_bytes(p, DMA);
+  a.keep_r = tok_keeps_r(p, DMA);
   if (hipError_t e = LdsLimit<&bwd_tok_kernel<DH, TB, NW, DMA, PHASED, PIPE>, kFullLds>::ensure(); e != hipSuccess)
     return (int)e;
   hipLaunchKernelGGL((bwd_tok_kernel<DH, TB, NW, DMA, PHASED, PIPE>), dim3((unsigned)xcd_grid_size(a.n_items)),
                      dim3(64 * NW), lds, stream, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.shares == 1) return (int)e;
-  const BwdFinish f{a.XPws, a.Rws, a.DPws, a.Zws, a.route, a.dX, p.N, p.ldx, p.H, p.dh, p.E, a.shares, p.route_mode == 0};
+  const BwdFinish f{a.XPws, a.Rws, a.DPws, a.Zws, a.route, a.dX, p.N, p.ldx, p.H, p.dh, p.E, a.shares, p.route_mode == 0, BM};
   return launch_bwd_tok_finish(1, f, stream);
 }
 

@@ -18,8 +18,8 @@ namespace {
 __device__ __forceinline__ float wide(float v) { return v; }
 __device__ __forceinline__ float wide(uint16_t v) { return bf16_bits_to_f32(v); }
 __device__ __forceinline__ void store4(float* p, f32x4 v) { *reinterpret_cast<f32x4*>(p) = v; }
-__device__ __forceinline__ void store4(uint16_t* p, f32x4 v) {
-  *reinterpret_cast<u32x2*>(p) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+__device__ __forceinline__ void store8(uint16_t* p, f32x4 v, f32x4 w) {
+  *reinterpret_cast<u32x4*>(p) = u32x4{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3])};
 }
 
 template <typename T, int DHP>
@@ -39,8 +39,14 @@ __global__ __launch_bounds__(256) void bwd_tok_finish_kernel(BwdFinish a) {
   f32x4 acc[JG][4];
   if (a.dX) {
     // (all quads of a share in flight at once: there are few waves, and this is what they wait for)
-    const size_t stride = (size_t)a.N * a.H * dh;
-    const float* src = a.P + ((size_t)t * a.H + h) * dh + 16 * gq;
+    // bf16: columns 64 J + 16 gq + 4 v .. of token t are quad 8 J + 4 (gq / 2) + 2 (gq % 2) + v / 2,
+    // lane half v % 2, of the [quad][lane] tile of its 32 tokens
+    constexpr bool kTiles = sizeof(T) == 2;
+    constexpr int kStepJ = kTiles ? 8 * 256 : 64;
+    const int64_t bt = a.block_tokens, tiles = (a.N + bt - 1) / bt * (bt / 32);
+    const size_t stride = kTiles ? (size_t)a.H * tiles * 32 * DHP : (size_t)a.N * a.H * dh;
+    const float* src = kTiles ? a.P + ((size_t)h * tiles + t / 32) * 32 * DHP + (4 * (gq >> 1) + 2 * (gq & 1)) * 256 + (t % 32) * 4
+                              : a.P + ((size_t)t * a.H + h) * dh + 16 * gq;
     f32x4 sum[JG][4];   // [J][v]
 #pragma unroll
     for (int J = 0; J < JG; ++J)
@@ -52,7 +58,8 @@ __global__ __launch_bounds__(256) void bwd_tok_finish_kernel(BwdFinish a) {
       for (int J = 0; J < JG; ++J)
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-          if (64 * J + 16 * gq + 4 * v < dh) sum[J][v] += *reinterpret_cast<const f32x4*>(src + 64 * J + 4 * v);
+          if (kTiles || 64 * J + 16 * gq + 4 * v < dh)
+            sum[J][v] += *reinterpret_cast<const f32x4*>(src + kStepJ * J + (kTiles ? (v >> 1) * 256 + (v & 1) * 128 : 4 * v));
     }
 #pragma unroll
     for (int J = 0; J < JG; ++J)
@@ -98,7 +105,12 @@ __global__ __launch_bounds__(256) void bwd_tok_finish_kernel(BwdFinish a) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int col = 64 * J + 16 * gq + 4 * v;
-        if (col < dh) store4(dst + col, f32x4{acc[J][0][v], acc[J][1][v], acc[J][2][v], acc[J][3][v]});
+        auto quad = [&](int k) { return f32x4{acc[J][0][k], acc[J][1][k], acc[J][2][k], acc[J][3][k]}; };
+        if constexpr (sizeof(T) == 2) {
+          if (v % 2 == 0) store8(dst + col, quad(v), quad(v | 1));
+        } else {
+          if (col < dh) store4(dst + col, quad(v));
+        }
       }
   }
 }
