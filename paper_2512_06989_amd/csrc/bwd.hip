@@ -109,12 +109,13 @@ struct BwdArgs {
   // others share the tokens out over `wsplit` workgroups each and leave fp32 partials
   // [wsplit][3][8 * (gpx - full_px) groups][128 rows][128]
   int gpx, full_px, n_groups;
-  // token-major kernel with the sub-networks of a token block shared out over `shares`
-  // workgroups (few tokens): partial dX fp32, [shares][token blocks][waves] of 32 x d_h as the
-  // registers hold them, and 1 / (Z + eps) [H][N]
+  // token-major kernel: token blocks 0 .. n_full - 1 are whole, the sub-networks of the n_units
+  // behind them are shared out over workgroups: partial dX fp32, [shares][units][waves] of 32 x d_h
+  // as the registers hold them, and 1 / (Z + eps) [H][N]
   float* XPws;
   float* Zws;
-  int shares, subs_per_share;
+  uint32_t n_full, n_units, equal, rest_subs;   // work list (list_item): shares of subs_per_share, one of rest_subs
+  int subs_per_share;
   int keep_r;   // token-major kernel: LDS holds a second copy of the gating weights
   int64_t N, ldx, ldy, n_tiles, n_items;
   int H, E, de, dh, route_mode, n_split;
@@ -165,12 +166,13 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 31, g = lane >> 5;
-  const int64_t item = xcd_work_item(blockIdx.x, a.n_items);
-  if (item >= a.n_items) return;
-  const int share = (int)(item % a.shares);       // the shares of a token block sit next to each other
-  const int64_t ht = item / a.shares;
-  const int h = (int)(ht / a.n_tiles);
-  const int64_t tile_tok0 = (ht % a.n_tiles) * BM;
+  const ListItem item = list_item(blockIdx.x, a.n_full, a.n_units, a.equal, a.rest_subs > 0);
+  if (!item.found) return;
+  const bool whole = item.whole;
+  const int share = (int)item.share;
+  const uint32_t block = item.index + (whole ? 0 : a.n_full), blocks_per_head = (uint32_t)a.n_tiles;
+  const int h = (int)(block / blocks_per_head);
+  const int64_t tile_tok0 = (int64_t)(block % blocks_per_head) * BM;
   const int wtok = wave * 32 * TB;
   const int E = a.E;
   const int64_t N = a.N;
@@ -178,7 +180,7 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
   float* DPh = a.DPws + (size_t)h * E * N;
 
   const int tiles_per_sub = a.de / 32;
-  const int e_begin = share * a.subs_per_share, e_end = min(E, e_begin + a.subs_per_share);
+  const int e_begin = share * a.subs_per_share, e_end = whole ? E : min(E, e_begin + a.subs_per_share);
   const int T = (e_end - e_begin) * tiles_per_sub;   // this workgroup's tiles
   float* DRw = DRs + e_begin * BM;                   // dr of its sub-networks
   const size_t head_off = ((size_t)h * E + e_begin) * a.de * DH;
@@ -397,7 +399,6 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
   for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
     for (int jb = 0; jb < JB; ++jb) dXa[tb][jb] = f32x16{0};
-  const bool whole = a.shares == 1;
 
   float rw[TB], drp[TB];
 #pragma unroll
@@ -951,15 +952,19 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
     for (int tb = 0; tb < TB; ++tb) {
       for (int ks = 0; ks < 2 * EB; ++ks) {
         if (16 * ks >= E) break;
-        u32x4 pk;
+        // dp as the sum of two bf16 operands: what one rounding leaves goes into the second product, so
+        // that dX does not depend on whether its block was shared out (there dp stays in fp32)
+        u32x4 pk, lo;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int e0 = 16 * ks + 8 * g + 2 * i;
           const float d0 = (e0 < E) ? DRs[e0 * BM + wtok + 32 * tb + r] : 0.f;
           const float d1 = (e0 + 1 < E) ? DRs[(e0 + 1) * BM + wtok + 32 * tb + r] : 0.f;
           pk[i] = pack_bf16(d0, d1);
+          const float h0 = bf16_bits_to_f32((uint16_t)pk[i]), h1 = bf16_bits_to_f32((uint16_t)(pk[i] >> 16));
+          lo[i] = pack_bf16(fabsf(h0) < INFINITY ? d0 - h0 : 0.f, fabsf(h1) < INFINITY ? d1 - h1 : 0.f);
         }
-        const bf16x8 bp = __builtin_bit_cast(bf16x8, pk);
+        const bf16x8 bp = __builtin_bit_cast(bf16x8, pk), bl = __builtin_bit_cast(bf16x8, lo);
         u32x4 in;   // columns that exist (the others hold whatever the memory held)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -971,6 +976,7 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
           u32x4 aw = *reinterpret_cast<const u32x4*>(stage_base + (32 * jb + r) * wr_stride + (16 * ks + 8 * g) * 2);
           aw &= in;
           dXa[tb][jb] = mfma32(__builtin_bit_cast(bf16x8, aw), bp, dXa[tb][jb]);
+          dXa[tb][jb] = mfma32(__builtin_bit_cast(bf16x8, aw), bl, dXa[tb][jb]);
         }
       }
     }
@@ -990,9 +996,9 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
 
   if (!a.dX) return;
   if (!whole) {
-    // as they lie in the registers: [share][block][wave][quad 4 jb + vq][lane]
+    // as they lie in the registers: [share][unit][wave][quad 4 jb + vq][lane]
     if (rows <= 0) return;
-    f32x4* dst = reinterpret_cast<f32x4*>(a.XPws) + (((size_t)share * a.H * a.n_tiles + ht) * NW + wave_u) * (8 * DH) + lane;
+    f32x4* dst = reinterpret_cast<f32x4*>(a.XPws) + (((size_t)share * a.n_units + item.index) * NW + wave_u) * (8 * DH) + lane;
 #pragma unroll
     for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
@@ -2619,39 +2625,51 @@ bool tok_direct_staging(const Problem& p) {
   return (p.dh == 128 || p.dh == 256) && tok_steps_lds(p, true, 1) <= kLdsBytesPerWorkgroup;
 }
 
-// Shares of the sub-networks per token block: few tokens leave CUs without a workgroup, or the
-// last round of workgroups mostly empty.  Microseconds, measured: a step of 32 neurons takes
-// about 2.1 (d_h = 64, two workgroups on a CU: 1.1; d_h = 256: 1.85, tiles through registers
-// 2.6), a workgroup 20 (14) before and after its steps; a share's partial dX is written and read
-// back at about 4 TB/s.  The launch that adds them up costs about 10 at d_h = 64, 5 + 1 per share
-// at 128 and, its few waves waiting for one share's partial after the other, 4 + 2.5 per share at
-// 256 (2 less where it also takes the routing derivative off the blocks).  Whole | shared, 128 tokens, H = 4, R given, the
-// token-major part alone: d_h = 256, E = 7, d_e = 32 26.5 | 30.7 in seven shares, E = 13 38.5 | 52.2
-// in thirteen and 36.2 in three, E = 30, d_e = 64 125 | 52 in six; d_h = 128, E = 7, d_e = 32 21.2 |
-// 20.3 in four, E = 30, d_e = 64 108 | 36 in ten; d_h = 64 73 | 24 in eight.
-struct TokShares { int shares, subs; };
-TokShares plan_tok_shares(const Problem& p) {
-  const int bm = tok_block_tokens(p.dh);
-  const int64_t items = ((p.N + bm - 1) / bm) * p.H;
-  const int slots = p.dh == 64 ? 512 : 256;      // workgroups that run at once
-  const double tile_us = p.dh == 64 ? 1.1 : p.dh == 128 ? 2.1 : tok_direct_staging(p) ? 1.85 : 2.6;
-  const double sub_us = tile_us * (p.de / 32), ends_us = p.dh == 64 ? 14.0 : 20.0;
+// Work list of the token-major kernel.  Blocks that fill whole rounds of workgroups stay whole (they
+// leave no partials); the blocks behind them stay whole too or share their sub-networks out, in equal
+// shares or, for the CUs that those leave, with one shorter share each.  Microseconds, measured: a
+// step of 32 neurons takes 1.6 on a CU (d_h = 64: 1.0, 256: 1.8, tiles through registers 2.6), but the
+// chip under its power limit does no more than 114 of them per us (352, 114, 98); 18 (12, 20) around
+// a workgroup's steps.  A share's partial dX is written and read back at about 5 TB/s; the launch that
+// adds them up costs 5 + 1 per share (d_h = 64: 10, 256: 4 + 2.5, 2 less where it also takes the
+// routing derivative off the blocks).
+struct TokList {
+  uint32_t n_full, n_units, equal, subs, rest;
+  uint32_t shares() const { return equal + (rest > 0); }
+};
+TokList plan_tok(const Problem& p) {
+  const uint32_t bm = (uint32_t)tok_block_tokens(p.dh), E = (uint32_t)p.E, slots = p.dh == 64 ? 512 : 256;
+  const uint32_t blocks = (uint32_t)((p.N + bm - 1) / bm) * (uint32_t)p.H, units = blocks % slots;
+  TokList best{blocks, 0, 0, E, 0};
+  if (units == 0) return best;
+  const bool regs = p.dh == 256 && !tok_direct_staging(p);
+  const double step = p.dh == 64 ? 1.0 : p.dh == 128 ? 1.6 : regs ? 2.6 : 1.8, rate = p.dh == 64 ? 352 : regs ? 98 : 114;
+  const double sub = step * (p.de / 32), ends = p.dh == 64 ? 12 : p.dh == 128 ? 18 : 20;
+  const double work = (double)units * E * (p.de / 32) / rate;
   const double sum_us = p.dh == 64 ? 10.0 : p.dh == 128 ? 5.0 : p.route_mode == 0 ? 2.0 : 4.0;
-  const double share_us = (p.dh == 64 ? 0.0 : p.dh == 128 ? 1.0 : 2.5) + 2.0 * p.N * p.H * p.dh * sizeof(float) / 4e6;
-  TokShares best{1, p.E};
+  const double share_us = (p.dh == 64 ? 0.0 : p.dh == 128 ? 1.0 : 2.5) + 2.0 * units * bm * p.dh * sizeof(float) / 5e6;
   double best_us = 0;
-  for (int s = 1; s <= 16 && s <= p.E; ++s) {
-    const int subs = (p.E + s - 1) / s;
-    if ((p.E + subs - 1) / subs != s) continue;  // s workgroups would not all have a sub-network
-    const double us = (double)((items * s + slots - 1) / slots) * (subs * sub_us + ends_us) + (s > 1 ? sum_us + s * share_us : 0.0);
-    if (s == 1 || us < best_us) { best = {s, subs}; best_us = us; }
+  auto consider = [&](uint32_t equal, uint32_t subs, uint32_t turns) {
+    const uint32_t rest = E > equal * subs ? E - equal * subs : 0, shares = equal + (rest > 0);
+    const double path = turns * subs * sub, hi = path > work ? path : work, r = (path > work ? work : path) / hi, r2 = r * r, r4 = r2 * r2;
+    const double us = hi * (1 + 0.09 * r4 * r4) + turns * ends + (shares > 1 ? sum_us + shares * share_us : 0.0);
+    if (best_us != 0 && us >= best_us) return;
+    best_us = us;
+    best = shares > 1 ? TokList{blocks - units, units, equal, subs, rest} : TokList{blocks, 0, 0, E, 0};
+  };
+  for (uint32_t s = 1; s <= 16 && s <= E; ++s) {
+    const uint32_t subs = (E + s - 1) / s;
+    if ((E + subs - 1) / subs == s) consider(s, subs, (units * s + slots - 1) / slots);
+    if (units * s >= slots || slots - units * s >= units) continue;   // (one each: s + 1 equal shares)
+    const uint32_t left = slots - units * s, m = (units + left - 1) / left;
+    const uint32_t big = (uint32_t)((m * E * sub + (m - 1) * ends) / ((1 + m * s) * sub)) + 1;
+    if (big * s < E && E - big * s <= big) consider(s, big, 1);
   }
   return best;
 }
 size_t tok_share_bytes(const Problem& p) {
-  const int s = plan_tok_shares(p).shares;
-  const int64_t bm = tok_block_tokens(p.dh);
-  return s > 1 ? (size_t)s * ((p.N + bm - 1) / bm * bm) * p.H * p.dh * sizeof(float) : 0;
+  const TokList l = plan_tok(p);
+  return l.n_units ? (size_t)l.shares() * l.n_units * tok_block_tokens(p.dh) * p.dh * sizeof(float) : 0;
 }
 
 template <int DH, int TB, int NW, bool DMA = false, bool PHASED = false, bool PIPE = false>
@@ -2659,16 +2677,17 @@ int launch_tok(const Problem& p, BwdArgs a, hipStream_t stream) {
   constexpr int BM = 32 * TB * NW;
   static_assert(BM == tok_block_tokens(DH), "bwd_bf16_lds_bytes assumes this block size");
   a.n_tiles = (p.N + BM - 1) / BM;
-  a.n_items = a.n_tiles * p.H * a.shares;
   const size_t lds = tok_lds_bytes(p, DMA);
   a.keep_r = tok_keeps_r(p, DMA);
   if (hipError_t e = LdsLimit<&bwd_tok_kernel<DH, TB, NW, DMA, PHASED, PIPE>, kFullLds>::ensure(); e != hipSuccess)
     return (int)e;
-  hipLaunchKernelGGL((bwd_tok_kernel<DH, TB, NW, DMA, PHASED, PIPE>), dim3((unsigned)xcd_grid_size(a.n_items)),
+  const uint32_t shares = a.equal + (a.rest_subs > 0);
+  hipLaunchKernelGGL((bwd_tok_kernel<DH, TB, NW, DMA, PHASED, PIPE>), dim3(list_grid(a.n_full, a.n_units, shares)),
                      dim3(64 * NW), lds, stream, a);
   const hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.shares == 1) return (int)e;
-  const BwdFinish f{a.XPws, a.Rws, a.DPws, a.Zws, a.route, a.dX, p.N, p.ldx, p.H, p.dh, p.E, a.shares, p.route_mode == 0, BM};
+  if (e != hipSuccess || a.n_units == 0) return (int)e;
+  const BwdFinish f{a.XPws, a.Rws, a.DPws, a.Zws, a.route, a.dX, p.N, p.ldx, p.H, p.dh, p.E, (int)shares, p.route_mode == 0,
+                    BM, a.n_full, a.n_units};
   return launch_bwd_tok_finish(1, f, stream);
 }
 
@@ -2764,11 +2783,16 @@ int bwd_bf16_max_sub(const Problem& p) { return p.dh == 256 ? 64 : kRouteMaxSub;
 
 size_t bwd_bf16_lds_bytes(const Problem& p) { return tok_lds_bytes(p, tok_direct_staging(p)); }
 
+std::string tok_list_text(const TokList& l) {   // "1", or "equal[+1] units"
+  if (l.n_units == 0) return "1";
+  return std::to_string(l.equal) + (l.rest ? "+1" : "") + " of " + std::to_string(l.n_units);
+}
+
 std::string bwd_plan(const Problem& p, int dtype) {
   if (dtype != 1) return bwd_f32_plan(p);
   const bool runs = p.dh == kDh || wgt256_takes(p);   // token segments of the last round's groups only
   return std::string("tok ") + (tok_direct_staging(p) ? "direct" : "registers") + " shares=" +
-         std::to_string(plan_tok_shares(p).shares) + "; wgt segs=" +
+         tok_list_text(plan_tok(p)) + "; wgt segs=" +
          std::to_string(runs ? plan_wgt16(p).segs : plan_wgt_split(p).segs) + "; route parts=" +
          std::to_string(route_splits(p.N, p.H));
 }
@@ -2837,11 +2861,12 @@ int launch_bwd(const Problem& p, int dtype, const void* X, const void* Wg, const
   a.WRws = reinterpret_cast<float*>(static_cast<unsigned char*>(ws) + 2 * nhe);
   unsigned char* rest = static_cast<unsigned char*>(ws) + 2 * nhe +
                         align256((size_t)p.H * kRouteParts * p.dh * p.E * sizeof(float));
-  const TokShares ts = plan_tok_shares(p);
-  a.shares = ts.shares;
-  a.subs_per_share = ts.subs;
+  const TokList list = plan_tok(p);
+  a.n_full = list.n_full; a.n_units = list.n_units;
+  a.equal = list.equal; a.rest_subs = list.rest;
+  a.subs_per_share = (int)list.subs;
   a.Zws = reinterpret_cast<float*>(rest);
-  if (ts.shares > 1) rest += align256((size_t)p.N * p.H * sizeof(float));
+  if (list.n_units) rest += align256((size_t)p.N * p.H * sizeof(float));
   a.XPws = a.WPws = reinterpret_cast<float*>(rest);
   a.wsplit = 1;
   a.blocks_per_seg = (p.N + 31) / 32;

@@ -598,7 +598,8 @@ int launch_tok(const Problem& p, BwdF32Args a, hipStream_t stream) {
                      tok_lds_bytes(p, NW), stream, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.shares == 1) return (int)e;
-  const BwdFinish f{a.XPws, a.Rws, a.DPws, a.Zws, a.route, a.dX, p.N, p.ldx, p.H, p.dh, p.E, a.shares, p.route_mode == 0, 16};
+  const BwdFinish f{a.XPws, a.Rws, a.DPws, a.Zws, a.route, a.dX, p.N, p.ldx, p.H, p.dh, p.E, a.shares, p.route_mode == 0, 16,
+                    0, (uint32_t)((p.N + 15) / 16 * p.H)};
   return launch_bwd_tok_finish(0, f, stream);
 }
 

@@ -27,11 +27,13 @@ __global__ __launch_bounds__(256) void bwd_tok_finish_kernel(BwdFinish a) {
   constexpr int JG = f32_col_groups(DHP);
   const int lane = threadIdx.x & 63;
   const int i16 = lane & 15, gq = lane >> 4;
-  const int64_t blocks = (a.N + 15) / 16;
-  const int64_t item = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (item >= blocks * a.H) return;
-  const int h = (int)(item / blocks);
-  const int64_t tok = (item % blocks) * 16 + i16;
+  const uint32_t waves = (uint32_t)a.block_tokens / 16, per_head = (uint32_t)((a.N + a.block_tokens - 1) / a.block_tokens);
+  const uint32_t item = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (item >= a.n_units * waves) return;
+  const uint32_t unit = item / waves, block = a.first_unit + unit;
+  const int h = (int)(block / per_head);
+  const int64_t tok0 = (int64_t)(block % per_head) * a.block_tokens + 16 * (item % waves), tok = tok0 + i16;
+  if (tok0 >= a.N) return;
   const bool ok = tok < a.N;
   const int64_t t = ok ? tok : a.N - 1;
   const int dh = a.dh, E = a.E;
@@ -43,9 +45,8 @@ __global__ __launch_bounds__(256) void bwd_tok_finish_kernel(BwdFinish a) {
     // lane half v % 2, of the [quad][lane] tile of its 32 tokens
     constexpr bool kTiles = sizeof(T) == 2;
     constexpr int kStepJ = kTiles ? 8 * 256 : 64;
-    const int64_t bt = a.block_tokens, tiles = (a.N + bt - 1) / bt * (bt / 32);
-    const size_t stride = kTiles ? (size_t)a.H * tiles * 32 * DHP : (size_t)a.N * a.H * dh;
-    const float* src = kTiles ? a.P + ((size_t)h * tiles + t / 32) * 32 * DHP + (4 * (gq >> 1) + 2 * (gq & 1)) * 256 + (t % 32) * 4
+    const size_t stride = kTiles ? (size_t)a.n_units * a.block_tokens * DHP : (size_t)a.N * a.H * dh;
+    const float* src = kTiles ? a.P + ((size_t)item / 2) * 32 * DHP + (4 * (gq >> 1) + 2 * (gq & 1)) * 256 + (16 * (item & 1) + i16) * 4
                               : a.P + ((size_t)t * a.H + h) * dh + 16 * gq;
     f32x4 sum[JG][4];   // [J][v]
 #pragma unroll
@@ -117,7 +118,7 @@ __global__ __launch_bounds__(256) void bwd_tok_finish_kernel(BwdFinish a) {
 
 template <typename T>
 int launch(const BwdFinish& a, hipStream_t stream) {
-  const dim3 grid((unsigned)(((a.N + 15) / 16 * a.H + 3) / 4)), block(256);
+  const dim3 grid((a.n_units * (uint32_t)(a.block_tokens / 16) + 3) / 4), block(256);
   switch (64 * ((a.dh + 63) / 64)) {
     case 64: hipLaunchKernelGGL((bwd_tok_finish_kernel<T, 64>), grid, block, 0, stream, a); break;
     case 128: hipLaunchKernelGGL((bwd_tok_finish_kernel<T, 128>), grid, block, 0, stream, a); break;

@@ -65,7 +65,6 @@ struct FlowShares {
   uint32_t unit_tokens, equal, share_tiles, rest_tiles;
   __host__ __device__ uint32_t shares() const { return equal + (rest_tiles > 0); }
   __host__ __device__ size_t partial_floats() const { return shares() > 1 ? (size_t)shares() * n_units * unit_tokens * 128 : 0; }
-  uint32_t grid() const { return (n_full + n_units * shares() + 7) / 8 * 8; }
 };
 
 struct FwdArgs {
@@ -420,37 +419,18 @@ __global__ __launch_bounds__(64 * kPipeWaves) void fwd_bf16_flow_kernel(FwdArgs 
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 31, g = lane >> 5;
-  // Workgroups go to the XCDs round robin and are started in order: every XCD takes its eighth of
-  // the whole blocks, then of the equal shares, then of the rests, so that the short ones are last.
   const FlowShares& fs = a.flow;
-  const int tiles_per_sub = a.de / kBI;
-  const uint32_t xcd = blockIdx.x & 7;
-  uint32_t widx = blockIdx.x >> 3, unit = 0;
+  const ListItem item = list_item(blockIdx.x, fs.n_full, fs.n_units, fs.equal, fs.rest_tiles > 0);
+  if (!item.found) return;  // whole workgroup leaves together
+  const bool whole = item.whole;
+  const uint32_t unit = item.index;
+  const int tiles_per_sub = a.de / kBI, share = (int)item.share;
   int64_t tile_tok0;
-  int h, share = 0, bm = BM, t_begin = 0, T = a.E * tiles_per_sub;
-  // (whole blocks beside units: a multiple of 256)
-  const uint32_t n_equal = fs.n_units * fs.equal;
-  const uint32_t px_full = (fs.n_full >> 3) + (xcd < (fs.n_full & 7)), px_equal = (n_equal >> 3) + (xcd < (n_equal & 7));
-  const bool whole = widx < px_full;
+  int h, bm = BM, t_begin = 0, T = a.E * tiles_per_sub;
   if (whole) {
-    const uint32_t blk = xcd * (fs.n_full >> 3) + min(xcd, fs.n_full & 7) + widx;
-    h = (int)(blk / fs.tiles);
-    tile_tok0 = (int64_t)(blk % fs.tiles) * BM;
+    h = (int)(item.index / fs.tiles);
+    tile_tok0 = (int64_t)(item.index % fs.tiles) * BM;
   } else {
-    widx -= px_full;
-    if (widx < px_equal) {
-      const uint32_t i = xcd * (n_equal >> 3) + min(xcd, n_equal & 7) + widx;
-      unit = i / fs.equal;
-      share = (int)(i - unit * fs.equal);
-    } else {
-      // (of n % 8 rests the last XCDs take one more, of n % 8 equal shares the first ones: none
-      // takes more than an eighth of all workgroups, rounded up)
-      const uint32_t n_rest = fs.rest_tiles ? fs.n_units : 0, extra = 8 - (n_rest & 7);
-      widx -= px_equal;
-      if (widx >= (n_rest >> 3) + (xcd >= extra)) return;   // whole workgroup leaves together
-      unit = xcd * (n_rest >> 3) + (xcd > extra ? xcd - extra : 0) + widx;
-      share = (int)fs.equal;
-    }
     bm = (int)fs.unit_tokens;
     t_begin = share * (int)fs.share_tiles;
     T = min(T - t_begin, (int)fs.share_tiles);
@@ -1684,7 +1664,7 @@ int launch_pipe(const Problem& p, FwdArgs a, hipStream_t stream) {
   const size_t lds = (size_t)3 * kPipeRing + (size_t)kPipeMaxSub * kPipeBM * sizeof(float);   // 1/r: 64 rows
   if (hipError_t e0 = LdsLimit<&fwd_bf16_flow_kernel, (int)kLdsBytesPerWorkgroup>::ensure(); e0 != hipSuccess)
     return (int)e0;
-  hipLaunchKernelGGL(fwd_bf16_flow_kernel, dim3(a.flow.grid()), dim3(64 * kPipeWaves), lds, stream, a);
+  hipLaunchKernelGGL(fwd_bf16_flow_kernel, dim3(list_grid(a.flow.n_full, a.flow.n_units, a.flow.shares())), dim3(64 * kPipeWaves), lds, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.flow.shares() <= 1) return (int)e;
   hipLaunchKernelGGL(fwd_bf16_flow_reduce_kernel, dim3(a.flow.n_units * a.flow.unit_tokens / 32, 4), dim3(256), 0, stream, a);

@@ -239,6 +239,31 @@ __host__ __device__ __forceinline__ int64_t xcd_grid_size(int64_t n_items) {
   return 8 * ((n_items + 7) / 8);
 }
 
+// Work list of `n_full` whole token blocks (a multiple of 256 beside units) and of n_units units in
+// `equal` shares and, if `rest`, one shorter share each.  Workgroups go to the XCDs round robin and
+// are started in order: every XCD takes its eighth of the whole blocks, then of the equal shares
+// (the shares of a unit side by side), then of the short ones.  Of n % 8 short ones the last XCDs
+// take one more, of n % 8 equal ones the first: none takes more than an eighth of all, rounded up.
+struct ListItem { bool found, whole; uint32_t index, share; };
+__device__ __forceinline__ ListItem list_item(uint32_t bid, uint32_t n_full, uint32_t n_units, uint32_t equal, bool rest) {
+  const uint32_t xcd = bid & 7, n_equal = n_units * equal;
+  uint32_t widx = bid >> 3;
+  const uint32_t px_full = (n_full >> 3) + (xcd < (n_full & 7)), px_equal = (n_equal >> 3) + (xcd < (n_equal & 7));
+  if (widx < px_full) return {true, true, xcd * (n_full >> 3) + min(xcd, n_full & 7) + widx, 0};
+  widx -= px_full;
+  if (widx < px_equal) {
+    const uint32_t i = xcd * (n_equal >> 3) + min(xcd, n_equal & 7) + widx;
+    return {true, false, i / equal, i % equal};
+  }
+  widx -= px_equal;
+  const uint32_t n_rest = rest ? n_units : 0, extra = 8 - (n_rest & 7);
+  const bool found = widx < (n_rest >> 3) + (xcd >= extra);
+  return {found, false, xcd * (n_rest >> 3) + (xcd > extra ? xcd - extra : 0) + widx, equal};
+}
+__host__ __device__ __forceinline__ uint32_t list_grid(uint32_t n_full, uint32_t n_units, uint32_t shares) {
+  return (n_full + n_units * shares + 7) / 8 * 8;
+}
+
 // Host side.  A kernel's dynamic-LDS limit is an attribute of the kernel on one device:
 // raise it the first time the kernel is launched on each device.  `done` is the launcher's
 // own bit mask of devices (one static per kernel instantiation); concurrent first launches

@@ -57,8 +57,8 @@ int launch_bwd_f32(const Problem& p, const void* X, const void* Wg, const void* 
 
 // Last step of a token-major backward that shared its sub-networks out (bwd_finish.hip)
 struct BwdFinish {
-  const float* P;      // partial dX: fp32 path [shares][N][H*dh]; bf16 path [shares][head][block of
-                       // block_tokens][32 tokens], each as a wave's registers hold it (bwd.hip)
+  const float* P;      // partial dX: fp32 path [shares][N][H*dh]; bf16 path [shares][unit][32 tokens],
+                       // each as a wave's registers hold it (bwd.hip)
   const float* R;      // [H][E][N] gating weights
   float* DP;           // [H][E][N] dr_e in, dp_e out (params mode)
   const float* Zinv;   // [H][N] 1 / (Z + eps) (params mode)
@@ -67,7 +67,9 @@ struct BwdFinish {
   int64_t N, ldx;
   int H, dh, E, shares;
   bool params;
+  // units: token blocks of block_tokens, head by head, from block first_unit on
   int block_tokens;
+  uint32_t first_unit, n_units;
 };
 int launch_bwd_tok_finish(int dtype, const BwdFinish& a, void* stream);
 
