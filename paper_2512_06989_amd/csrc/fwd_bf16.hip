@@ -1601,6 +1601,33 @@ FlowShares flow_shares(const Problem& p) {
   }
   return f;
 }
+// Shares that two smaller workgroups per CU ask for (any d_h, fewer than 384 blocks).
+int shares_two_per_cu(int64_t base, int64_t T) {
+  int64_t want = base < 384 ? (512 + base - 1) / base : 1;
+  if (want > T / 2) want = T / 2 > 0 ? T / 2 : 1;
+  const int64_t per = (T + want - 1) / want;
+  return (int)((T + per - 1) / per);
+}
+// Shares per block of 256 tokens at d_h = 64, where the plan above takes any.  A CU holds two
+// workgroups: a tile takes one 0.88 us, two 1.62, and c workgroups on the fullest CU c / 2 rounds of
+// that; 10 around the tiles, the partials (written and read) 0.2 per MiB, the second launch 3.  Plan
+// of two workgroups per CU | this one, us: 256 blocks, 40 tiles 57.2 | 45.8 (whole); 192 blocks, 320
+// tiles 292 | 238 (four shares, not three); 64 blocks, 84 tiles 39.3 | 37.4 (four, not eight); 320
+// blocks, 84 tiles 130 | 125 (three, not two).  No more scratch than that plan's or the static buffer's.
+int shares_64(const Problem& p, int64_t base, int64_t T) {
+  const int asked = shares_two_per_cu(base, T);
+  if (asked == 1) return 1;
+  const double mib = (double)p.N * p.H * p.dh * sizeof(float) / (1 << 20);
+  int best = 1;
+  double best_us = 0;
+  for (int s = 1; s <= 32 && s <= T / 2; ++s) {
+    if (s > 1 && s > asked && s * mib > 40) break;
+    const int64_t c = (base * s + 255) / 256;
+    const double us = (double)((T + s - 1) / s) * ((c / 2) * 1.62 + (c & 1) * 0.88) + ((c + 1) / 2) * 10.0 + (s > 1 ? 3 + 0.2 * s * mib : 0.0);
+    if (s == 1 || us < best_us) { best = s; best_us = us; }
+  }
+  return best;
+}
 SplitPlan plan_split(const Problem& p) {
   SplitPlan s;
   s.pipe = p.dh == kDh && p.E <= kPipeMaxSub;
@@ -1630,8 +1657,10 @@ SplitPlan plan_split(const Problem& p) {
   if (p.dh == 256) {   // one workgroup per CU
     if (base <= 128) want = (int)(256 / base);
     else if (base < 384) want = shares_256(p, s.pair, base, T);
-  } else if (base < 384) {
-    want = (int)((512 + base - 1) / base);
+  } else if (p.dh == 64 && s.bm == 256) {
+    want = shares_64(p, base, T);
+  } else {
+    want = shares_two_per_cu(base, T);
   }
   if (want > T / 2) want = T / 2 > 0 ? T / 2 : 1;   // at least two tiles per split
   s.tiles_per_split = (T + want - 1) / want;
@@ -1712,15 +1741,11 @@ size_t fwd_bf16_workspace_bytes(const Problem& p) {
   const SplitPlan sp = plan_split(p);
   if (sp.pipe && !sp.decode_nb) return flow_shares(p).partial_floats() * sizeof(float);
   int64_t splits = sp.n_split;
-  if (p.dh == 256) {
-    // The scratch asked for at this width is that of shares for two workgroups per CU, although
-    // the launch takes no more than half of them: which problems exceed the static scratch buffer
-    // (and are refused by the entry point that has no other) is part of the interface.
-    const int64_t base = ((p.N + sp.bm - 1) / sp.bm) * p.H;
-    const int64_t T = (int64_t)p.E * (p.de / kBI);
-    int64_t want = base < 384 ? (512 + base - 1) / base : 1;
-    if (want > T / 2) want = T / 2 > 0 ? T / 2 : 1;
-    const int64_t per = (T + want - 1) / want, asked = (T + per - 1) / per;
+  if (p.dh != kDh) {
+    // The scratch asked for at these widths is that of shares for two workgroups per CU, although
+    // the launch may take fewer: which problems exceed the static scratch buffer (and are refused
+    // by the entry point that has no other) is part of the interface.
+    const int64_t asked = shares_two_per_cu(((p.N + sp.bm - 1) / sp.bm) * p.H, (int64_t)p.E * (p.de / kBI));
     splits = splits > asked ? splits : asked;
   }
   return splits > 1 ? (size_t)splits * p.N * p.H * p.dh * sizeof(float) : 0;
