@@ -1416,8 +1416,9 @@ __global__ void bwd_wgt16_reduce_kernel(BwdArgs a, size_t crows) {
   }
 }
 
-// Tokens are shared out only when that shortens the kernel by a fifth or more: its time goes in
-// rounds of 256 workgroups (one per CU), so S segments cost ceil(groups * S / 256) / S rounds.
+// Token segments per neuron group.  d_h = 256, the generic kernel: only when that shortens it by a fifth
+// or more; its time goes in rounds of 256 workgroups (one per CU), so S segments cost
+// ceil(groups * S / 256) / S rounds.
 struct WgtSplit { int segs; int64_t blocks_per_seg; };
 // waves per workgroup and workgroups the chip holds at once, per head width
 constexpr int wgt_waves(int dh) { return dh == kDh ? kW16Waves : 4; }
@@ -1428,9 +1429,23 @@ WgtSplit plan_wgt_split(const Problem& p) {
   const int64_t groups = (int64_t)p.H * (((int64_t)p.E * p.de / 16 + waves - 1) / waves);
   auto rounds = [&](int64_t S) { return (double)((groups * S + slots - 1) / slots) / (double)S; };
   int best = 1;
-  for (int S = 2; S <= 8; ++S)
-    if (nb / S >= 16 && rounds(S) < 0.9 * rounds(best)) best = S;   // more segments only for a clear gain
-  if (rounds(best) > 0.8 * rounds(1)) best = 1;
+  if (p.dh == 64) {
+    // A CU holds three workgroups; a block of 32 tokens takes one, two, three of them 0.6, 0.9, 1.35 us,
+    // 6 around the blocks, the partials 0.22 per MiB and 4 for the launch that adds them up.  One
+    // segment | the best, us: 672 groups, 512 blocks 672 | 623 (three), 157 blocks 212 | 212; 160
+    // groups, 250 blocks 157 | 91 (three; 97 in four, which rounds of 768 workgroups suggest).
+    const double mib = 3.0 * p.H * p.E * p.de * p.dh * sizeof(float) / (1 << 20), turn[3] = {0, 0.6, 0.9};
+    double best_us = 0;
+    for (int S = 1; S <= 8 && (S == 1 || nb / S >= 16); ++S) {
+      const int64_t c = (groups * S + 255) / 256;
+      const double us = (double)((nb + S - 1) / S) * ((c / 3) * 1.35 + turn[c % 3]) + ((c + 2) / 3) * 6.0 + (S > 1 ? 4 + 0.22 * S * mib : 0.0);
+      if (S == 1 || us < best_us) { best = S; best_us = us; }
+    }
+  } else {
+    for (int S = 2; S <= 8; ++S)
+      if (nb / S >= 16 && rounds(S) < 0.9 * rounds(best)) best = S;   // more segments only for a clear gain
+    if (rounds(best) > 0.8 * rounds(1)) best = 1;
+  }
   WgtSplit w;
   w.blocks_per_seg = (nb + best - 1) / best;
   w.segs = (int)((nb + w.blocks_per_seg - 1) / w.blocks_per_seg);

@@ -1,0 +1,36 @@
+"""Weight-major backward at d_h = 64: token segments per neuron group by what the fullest CU gets, from
+one to eight, with a shorter last segment and a ragged last block.  Weight gradients of the heads at
+both ends against the oracle, and run-to-run bit identity."""
+import pytest
+
+from oracle import mhffn_oracle as orc
+from paper_2512_06989_amd import inputs, mhffn
+from tests.helpers import TOL, check_parity, device_inputs, launch_plan, small_workload, to_host
+
+WANT = ("dW_gate", "dW_up", "dW_down")
+CASES = [(363, 1, 1, 32, 1), (1013, 1, 1, 32, 2), (1840, 1, 1, 32, 3), (2139, 1, 1, 32, 4),
+         (2807, 1, 1, 32, 5), (3075, 1, 1, 32, 6), (3610, 1, 1, 32, 7), (4723, 1, 1, 32, 8)]
+
+
+@pytest.mark.parametrize("N,H,E,de,segs", CASES)
+def test_plan(N, H, E, de, segs):
+    assert "; wgt segs=%d;" % segs in launch_plan(mhffn.OP_BACKWARD, N, H, E, de, dh=64)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,H,E,de,segs", CASES)
+def test_weight_gradients(N, H, E, de, segs):
+    import torch
+    w = small_workload("segments64", N, H, E, de, "bf16", dh=64, backward=True)
+    d = inputs.make_inputs(w, seed=N + E, with_dy=True)
+    g = device_inputs(d, "bf16")
+    a = [g[k] for k in ("X", "W_gate", "W_up", "W_down", "W_r", "dY")]
+    got = mhffn.backward(*a, w.eps, want=WANT)
+    again = mhffn.backward(*a, w.eps, want=WANT)
+    for k in WANT:
+        assert torch.equal(got[k], again[k]), k
+    for h in (0, H - 1):                              # heads are independent
+        c, hs = slice(h * 64, (h + 1) * 64), slice(h, h + 1)
+        one = [d[k][hs] for k in ("W_gate", "W_up", "W_down", "W_r")]
+        want = orc.backward(d["X"][:, c], *one, d["dY"][:, c], w.eps)
+        check_parity({k: to_host(got[k])[hs] for k in WANT}, want, TOL["bf16"], 64, "segments, head %d" % h)
