@@ -5,10 +5,9 @@
 //   dX   = sum_shares partial + dp W_r^T
 // A wave takes 16 tokens of one head.  The lane group gq of a token walks the sub-networks
 // 4 k + gq, which is how the fp32 product dp W_r^T (f32_tiles.h) wants its operand, so nothing
-// passes through LDS.  Bound: reading the partials, by few waves that wait for memory (two shares
-// of 1536 x 2048, 384 workgroups, weights given: 10 us, 3.8 TB/s with what L2 still holds; a
-// quad of one share at a time took twice that.  Two shares of 5000 x 1024 at d_h = 64 with the
-// routing derivative: 24 us for 41 MB).
+// passes through LDS.  Bound: reading the partials, by few waves that wait for memory, so all quads of a
+// share are in flight at once.  bf16 partials lie as the token-major kernel's registers held them
+// (256 bytes a load, not 64 bytes of each of 16 rows).
 #include "f32_tiles.h"
 #include "mhffn_internal.h"
 

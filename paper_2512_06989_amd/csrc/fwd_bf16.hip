@@ -79,7 +79,9 @@ struct FwdArgs {
   int H, E, de, dh, route_mode;
   int n_split, tiles_per_split;
   float eps;
-  FlowShares flow;   // fwd_bf16_flow_kernel only
+};
+struct FlowArgs : FwdArgs {   // fwd_bf16_flow_kernel (small launches pay for longer arguments)
+  FlowShares flow;
 };
 
 template <int DH, int TB, int NW>
@@ -411,7 +413,7 @@ __device__ __forceinline__ void lds_wait4(T0& a, T1& b, T2& c, T3& d) {
   asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "n"(N));
 }
 
-__global__ __launch_bounds__(64 * kPipeWaves) void fwd_bf16_flow_kernel(FwdArgs a) {
+__global__ __launch_bounds__(64 * kPipeWaves) void fwd_bf16_flow_kernel(FlowArgs a) {
   constexpr int BM = kPipeBM;
   constexpr int THREADS = 64 * kPipeWaves;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -1484,7 +1486,7 @@ __device__ __forceinline__ void add_partials(f32x4& sum, const float* src, size_
 
 // Y = bf16(sum over the shares), for the units of fwd_bf16_flow_kernel: a workgroup takes 32 columns
 // (blockIdx.y) of a wave's 32 tokens, a thread four of one token
-__global__ __launch_bounds__(256) void fwd_bf16_flow_reduce_kernel(FwdArgs a) {
+__global__ __launch_bounds__(256) void fwd_bf16_flow_reduce_kernel(FlowArgs a) {
   constexpr int kRow = 64 + 16;   // bytes of LDS per token
   __shared__ __attribute__((aligned(16))) unsigned char rows[32 * kRow];
   const FlowShares& fs = a.flow;
@@ -1511,7 +1513,8 @@ __global__ void fwd_bf16_reduce_kernel(FwdArgs a) {
   f32x4 sum = {0.f, 0.f, 0.f, 0.f};
   const size_t stride = (size_t)a.N * dm;
   add_partials(sum, a.P + idx, stride, a.n_split);
-  const int64_t tok = idx / dm, col = idx % dm;
+  // (shared blocks are few: an output has at most 2^31 elements)
+  const int64_t tok = (uint32_t)idx / (uint32_t)dm, col = (uint32_t)idx % (uint32_t)dm;
   u32x2 pk;
   pk[0] = pack_bf16(sum[0], sum[1]);
   pk[1] = pack_bf16(sum[2], sum[3]);
@@ -1688,7 +1691,9 @@ int launch_variant(const Problem& p, FwdArgs a, const SplitPlan& sp, hipStream_t
   return (int)hipGetLastError();
 }
 
-int launch_pipe(const Problem& p, FwdArgs a, hipStream_t stream) {
+int launch_pipe(const Problem& p, const FwdArgs& base, hipStream_t stream) {
+  FlowArgs a;
+  static_cast<FwdArgs&>(a) = base;
   a.flow = flow_shares(p);
   const size_t lds = (size_t)3 * kPipeRing + (size_t)kPipeMaxSub * kPipeBM * sizeof(float);   // 1/r: 64 rows
   if (hipError_t e0 = LdsLimit<&fwd_bf16_flow_kernel, (int)kLdsBytesPerWorkgroup>::ensure(); e0 != hipSuccess)
