@@ -7,7 +7,8 @@
 // 4 k + gq, which is how the fp32 product dp W_r^T (f32_tiles.h) wants its operand, so nothing
 // passes through LDS.  Bound: reading the partials, by few waves that wait for memory, so all quads of a
 // share are in flight at once.  bf16 partials lie as the token-major kernel's registers held them
-// (256 bytes a load, not 64 bytes of each of 16 rows).
+// (256 bytes a load, not 64 bytes of each of 16 rows): three shares of 1536 x 2048, 384 workgroups,
+// weights given, 9.7 us; two took 10.6 as rows.
 #include "f32_tiles.h"
 #include "mhffn_internal.h"
 
