@@ -157,7 +157,7 @@ int mhffn_forward(const mhffn_desc* desc, const void* X, const void* W_gate,
  * use there, or by mhffn_init).  fp32 uses no scratch here: no fp32 problem is refused
  * for its size and calls on different streams are independent.  A bf16 problem whose mhffn_workspace_bytes exceeds
  * that size returns MHFFN_ERR_STATIC_SCRATCH and launches nothing (d_head = 128
- * with up to 64 sub-networks never needs more, whatever the token
+ * with up to 64 sub-networks never needs more than 32 MiB, whatever the token
  * count; the kernels of the other shapes can need up to 64 MiB at a few hundred
  * to a few thousand tokens and are then refused).  All bf16 calls on one GPU share the buffer: it keeps the last call's
  * partial sums (each call overwrites what it reads, nothing has to start at

@@ -1557,9 +1557,11 @@ int shares_256(const Problem& p, bool pair, int64_t base, int T) {
 // 11.4 (10.8) around a workgroup's steps; the partials 0.46 per MiB, written and read, and 1.
 // Where the two bounds meet, a tenth more than either.  Whole | this list, forward calls, E d_e / 32
 // tiles, us: 384 blocks, 64 tiles 165 | 153 (128 blocks in halves); 128 blocks, 32 tiles 42 | 33 and
-// 64 blocks 41 | 30 (halves; 36 in four shares); 96 blocks, 264 tiles 257 | 155 in shares of 108, 108
-// and 48, 160 in two equal ones; 32 blocks (300 tokens), 32 tiles 41 | 21 (halves in four shares; 27
-// whole in eight).  Partials of at most 40 MiB: what the static scratch buffer holds.
+// 64 blocks 41 | 30 (halves; 36 in four shares); 96 blocks, 264 tiles 259 | 160 in two shares; 32 blocks
+// (300 tokens), 32 tiles 41 | 21 (halves in four shares; 27 whole in eight).  Partials of at most
+// 32 MiB: the interface promises it, and callers hold workspaces of that size (what it costs: the 96
+// blocks would take 151 in shares of 109, 109 and 46, which leave 36 MiB).
+constexpr uint32_t kFlowScratch = 32u << 20;
 FlowShares flow_shares(const Problem& p) {
   const uint32_t T = (uint32_t)(p.E * (p.de / kBI)), slots = 256;
   FlowShares f{};
@@ -1575,7 +1577,7 @@ FlowShares flow_shares(const Problem& p) {
     const uint32_t unit0 = rounds * slots * (half + 1), units = per_head * (uint32_t)p.H - unit0;
     const double rows = rounds ? (double)units * tokens : (double)p.N * p.H;   // (ragged blocks cost less)
     const double work = rounds * slots * T / 197.0 + rows / tokens * T / rate;
-    const uint32_t most = blocks <= 128 ? std::min((40u << 20) / (tokens * kDh * 4) / units, T / 2) : 1;   // shares
+    const uint32_t most = blocks <= 128 ? std::min(kFlowScratch / (tokens * kDh * 4) / units, T / 2) : 1;   // shares
     auto consider = [&](uint32_t equal, uint32_t share, uint32_t turns) {
       const uint32_t rest = T > equal * share ? T - equal * share : 0, shares = equal + (rest > 0);
       if (shares > 1 && shares > most) return;
