@@ -2654,8 +2654,10 @@ struct TokList {
 };
 TokList plan_tok(const Problem& p) {
   const uint32_t bm = (uint32_t)tok_block_tokens(p.dh), E = (uint32_t)p.E, slots = p.dh == 64 ? 512 : 256;
-  const uint32_t blocks = (uint32_t)((p.N + bm - 1) / bm) * (uint32_t)p.H, units = blocks % slots;
-  TokList best{blocks, 0, 0, E, 0};
+  const int64_t blocks = (p.N + bm - 1) / bm * p.H;   // (a plan is asked for whatever the sizes)
+  const uint32_t units = (uint32_t)(blocks % slots);
+  const TokList none{(uint32_t)blocks, 0, 0, E, 0};
+  TokList best = none;
   if (units == 0) return best;
   const bool regs = p.dh == 256 && !tok_direct_staging(p);
   const double step = p.dh == 64 ? 1.0 : p.dh == 128 ? 1.6 : regs ? 2.6 : 1.8, rate = p.dh == 64 ? 352 : regs ? 98 : 114;
@@ -2670,7 +2672,7 @@ TokList plan_tok(const Problem& p) {
     const double us = hi * (1 + 0.09 * r4 * r4) + turns * ends + (shares > 1 ? sum_us + shares * share_us : 0.0);
     if (best_us != 0 && us >= best_us) return;
     best_us = us;
-    best = shares > 1 ? TokList{blocks - units, units, equal, subs, rest} : TokList{blocks, 0, 0, E, 0};
+    best = shares > 1 ? TokList{(uint32_t)(blocks - units), units, equal, subs, rest} : none;
   };
   for (uint32_t s = 1; s <= 16 && s <= E; ++s) {
     const uint32_t subs = (E + s - 1) / s;

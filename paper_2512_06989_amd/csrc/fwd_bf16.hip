@@ -1565,17 +1565,21 @@ constexpr uint32_t kFlowScratch = 32u << 20;
 FlowShares flow_shares(const Problem& p) {
   const uint32_t T = (uint32_t)(p.E * (p.de / kBI)), slots = 256;
   FlowShares f{};
-  f.tiles = p.N > kPipeBM ? (uint32_t)((p.N + kPipeBM - 1) / kPipeBM) : 1;   // (an empty batch is planned too)
-  const uint32_t blocks = f.tiles * (uint32_t)p.H, rounds = blocks / slots;
-  f.n_full = blocks;
-  if (blocks == rounds * slots) return f;
+  // (64 bits and floating point: a plan is asked for whatever the sizes)
+  const int64_t tiles = p.N > kPipeBM ? (p.N + kPipeBM - 1) / kPipeBM : 1;   // (an empty batch is planned too)
+  const int64_t blocks = tiles * p.H, full = blocks / slots * slots;
+  const double rounds = (double)(full / slots);
+  f.tiles = (uint32_t)tiles;
+  f.n_full = (uint32_t)blocks;
+  if (blocks == full) return f;
   double best = 0;
   for (uint32_t half = 0; half < 2; ++half) {
     const double step = half ? 0.62 : 0.95, rate = half ? 338 : 197, ends = half ? 10.8 : 11.4;
     const uint32_t tokens = half ? kPipeBM / 2 : kPipeBM;
-    const uint32_t per_head = rounds ? f.tiles * (half + 1) : p.N > tokens ? (uint32_t)((p.N + tokens - 1) / tokens) : 1;
-    const uint32_t unit0 = rounds * slots * (half + 1), units = per_head * (uint32_t)p.H - unit0;
-    const double rows = rounds ? (double)units * tokens : (double)p.N * p.H;   // (ragged blocks cost less)
+    const int64_t per_head = full ? tiles * (half + 1) : p.N > tokens ? (p.N + tokens - 1) / tokens : 1;
+    const int64_t unit0 = full * (half + 1);
+    const uint32_t units = (uint32_t)(per_head * p.H - unit0);
+    const double rows = full ? (double)units * tokens : (double)p.N * p.H;   // (ragged blocks cost less)
     const double work = rounds * slots * T / 197.0 + rows / tokens * T / rate;
     const uint32_t most = blocks <= 128 ? std::min(kFlowScratch / (tokens * kDh * 4) / units, T / 2) : 1;   // shares
     auto consider = [&](uint32_t equal, uint32_t share, uint32_t turns) {
@@ -1588,9 +1592,9 @@ FlowShares flow_shares(const Problem& p) {
       if (best != 0 && us >= best) return;
       best = us;
       const bool cut = shares > 1 || half;
-      f.n_full = cut ? rounds * slots : blocks;
+      f.n_full = (uint32_t)(cut ? full : blocks);
       f.n_units = cut ? units : 0;
-      f.unit0 = unit0; f.unit_tiles = per_head; f.unit_tokens = tokens;
+      f.unit0 = (uint32_t)unit0; f.unit_tiles = (uint32_t)per_head; f.unit_tokens = tokens;
       f.equal = equal; f.share_tiles = share; f.rest_tiles = rest;
     };
     for (uint32_t s = 1; s == 1 || (s <= most && units * s <= slots); s += 1 + s / 8) {

@@ -47,6 +47,12 @@ def test_scratch_never_exceeds_what_the_interface_states():
         assert mhffn.workspace_bytes(d, mhffn.OP_FORWARD) <= 32 << 20
 
 
+def test_plan_of_many_long_rounds():
+    """8256 blocks of 2^19 tiles: their product has 33 bits.  The plan is that of half the tiles."""
+    a, b = (launch_plan(mhffn.OP_FORWARD, 256 * 8256, 1, 64, de) for de in (1 << 17, 1 << 18))
+    assert a.split(" tiles=")[0] == b.split(" tiles=")[0] == "flow whole=8256 units=0x256", (a, b)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("N,H,E,de,route_weights,plan", CASES)
 def test_flow_forward(N, H, E, de, route_weights, plan):
