@@ -17,6 +17,13 @@ def test_plan(N, H, E, de, segs):
     assert "; wgt segs=%d;" % segs in launch_plan(mhffn.OP_BACKWARD, N, H, E, de, dh=64)
 
 
+@pytest.mark.parametrize("N,H,E,de,segs", [
+    (31102, 25, 49, 448, 1), (32212, 23, 54, 480, 1),   # two segments: 804 and 874 MiB for nothing
+    (5000, 16, 14, 192, 1), (16384, 16, 14, 192, 3)])   # 33 MiB a segment: 14 % in the second case
+def test_scratch_is_taken_for_a_gain_only(N, H, E, de, segs):
+    test_plan(N, H, E, de, segs)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("N,H,E,de,segs", CASES)
 def test_weight_gradients(N, H, E, de, segs):
