@@ -1436,13 +1436,15 @@ WgtSplit plan_wgt_split(const Problem& p) {
     // segment | the best, us: 672 groups, 512 blocks 712 | 613 (three), 157 blocks 212 | 211; 160
     // groups, 250 blocks 157 | 91 (three; 97 in four, which rounds of 768 workgroups suggest).
     // Segments have to gain more than the model can be wrong by (2 %, less for the first 4 MiB of
-    // partials) and 1 % for every 100 MiB that the caller has to hold, a quarter at most: 8575
-    // groups, 972 blocks 14590 | 14649 in two for 804 MiB, which the model alone takes to be 0.3 % faster.
+    // partials) and 0.5 % for every 100 MiB that the caller has to hold, a quarter at most.  Refused:
+    // 8575 groups, 972 blocks 14590 | 14649 (two, 804 MiB, modelled gain 0.3 %), whole backwards of
+    // 1788 groups, 879 blocks 5088 | 5083 (two, 167 MiB, 2.6 %); taken: 1088 groups, 217 blocks 856 |
+    // 838 (two, 102 MiB, 2.9 %), 2100 groups, 848 blocks 5983 | 5825 (four, 394 MiB, 4.3 %; two now).
     const double mib = 3.0 * p.H * p.E * p.de * p.dh * sizeof(float) / (1 << 20), turn[3] = {0, 0.6, 0.9};
     double best_us = 0;
     for (int S = 1; S <= 8 && (S == 1 || nb / S >= 16); ++S) {
       const int64_t c = (groups * S + 255) / 256;
-      const double scratch = S > 1 ? S * mib : 0.0, margin = std::min(0.25, std::min(0.02, 0.005 * scratch) + 1e-4 * scratch);
+      const double scratch = S > 1 ? S * mib : 0.0, margin = std::min(0.25, std::min(0.02, 0.005 * scratch) + 5e-5 * scratch);
       const double us = (double)((nb + S - 1) / S) * ((c / 3) * 1.35 + turn[c % 3]) + ((c + 2) / 3) * 6.0 + (S > 1 ? 4 + 0.22 * scratch : 0.0);
       if (S == 1 || us * (1 + margin) < best_us) { best = S; best_us = us * (1 + margin); }
     }

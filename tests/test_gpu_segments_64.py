@@ -19,7 +19,8 @@ def test_plan(N, H, E, de, segs):
 
 @pytest.mark.parametrize("N,H,E,de,segs", [
     (31102, 25, 49, 448, 1), (32212, 23, 54, 480, 1),   # two segments: 804 and 874 MiB for nothing
-    (5000, 16, 14, 192, 1), (16384, 16, 14, 192, 3)])   # 33 MiB a segment: 14 % in the second case
+    (28119, 12, 33, 288, 1), (26753, 21, 33, 160, 1),   # 167 and 162 MiB for less than the model's error
+    (5000, 16, 14, 192, 1), (16384, 16, 14, 192, 3), (6940, 17, 16, 256, 2)])
 def test_scratch_is_taken_for_a_gain_only(N, H, E, de, segs):
     test_plan(N, H, E, de, segs)
 
