@@ -1417,20 +1417,24 @@ __global__ void bwd_wgt16_reduce_kernel(BwdArgs a, size_t crows) {
   }
 }
 
-// Token segments per neuron group.  d_h = 256, the generic kernel: only when that shortens it by a fifth
-// or more; its time goes in rounds of 256 workgroups (one per CU), so S segments cost
-// ceil(groups * S / 256) / S rounds.
+// Token segments per neuron group.  The generic kernel: only when that shortens it by a fifth or
+// more; its time goes in rounds of the workgroups that the chip holds (of four waves: two per CU at
+// d_h = 64, by its 200 registers, one at 256), so S segments cost ceil(groups S / slots) / S rounds.
+// d_h = 64, dense strides: one segment | three, which this rule takes and rounds of three per CU do
+// not, 672 groups, 157 blocks 292 | 254 us, 512 blocks 786 | 688; 160 groups, 250 blocks 97 in three
+// (113 in four).
 struct WgtSplit { int segs; int64_t blocks_per_seg; };
-// waves per workgroup and workgroups the chip holds at once, per head width
-constexpr int wgt_waves(int dh) { return dh == kDh ? kW16Waves : 4; }
-constexpr int wgt_slots(int dh) { return dh == 64 ? 768 : 256; }
+constexpr int wgt_waves(int dh) { return dh == kDh ? kW16Waves : 4; }   // per workgroup
+constexpr int kW64PerCu = 3;                                              // workgroups of bwd_wgt64_kernel on a CU
+constexpr int wgt_dh_per_cu(int dh) { return dh == 64 ? 2 : 1; }          // and of bwd_wgt_dh_kernel
+bool wgt64_takes(const Problem& p) { return p.dh == 64 && p.ldx < ((int64_t)1 << 24) && p.ldy < ((int64_t)1 << 24); }
 WgtSplit plan_wgt_split(const Problem& p) {
   const int64_t nb = (p.N + 31) / 32;
-  const int waves = wgt_waves(p.dh), slots = wgt_slots(p.dh);
+  const int waves = wgt_waves(p.dh), slots = 256 * wgt_dh_per_cu(p.dh);
   const int64_t groups = (int64_t)p.H * (((int64_t)p.E * p.de / 16 + waves - 1) / waves);
   auto rounds = [&](int64_t S) { return (double)((groups * S + slots - 1) / slots) / (double)S; };
   int best = 1;
-  if (p.dh == 64) {
+  if (wgt64_takes(p)) {
     // A CU holds three workgroups; a block of 32 tokens takes one, two, three of them 0.6, 0.9, 1.35 us,
     // 6 around the blocks, the partials 0.22 per MiB and 4 for the launch that adds them up.  One
     // segment | the best, us: 672 groups, 512 blocks 712 | 613 (three), 157 blocks 212 | 211; 160
@@ -1440,12 +1444,12 @@ WgtSplit plan_wgt_split(const Problem& p) {
     // 8575 groups, 972 blocks 14590 | 14649 (two, 804 MiB, modelled gain 0.3 %), whole backwards of
     // 1788 groups, 879 blocks 5088 | 5083 (two, 167 MiB, 2.6 %); taken: 1088 groups, 217 blocks 856 |
     // 838 (two, 102 MiB, 2.9 %), 2100 groups, 848 blocks 5983 | 5825 (four, 394 MiB, 4.3 %; two now).
-    const double mib = 3.0 * p.H * p.E * p.de * p.dh * sizeof(float) / (1 << 20), turn[3] = {0, 0.6, 0.9};
+    const double mib = 3.0 * p.H * p.E * p.de * p.dh * sizeof(float) / (1 << 20), turn[kW64PerCu] = {0, 0.6, 0.9};
     double best_us = 0;
     for (int S = 1; S <= 8 && (S == 1 || nb / S >= 16); ++S) {
       const int64_t c = (groups * S + 255) / 256;
       const double scratch = S > 1 ? S * mib : 0.0, margin = std::min(0.25, std::min(0.02, 0.005 * scratch) + 5e-5 * scratch);
-      const double us = (double)((nb + S - 1) / S) * ((c / 3) * 1.35 + turn[c % 3]) + ((c + 2) / 3) * 6.0 + (S > 1 ? 4 + 0.22 * scratch : 0.0);
+      const double us = (double)((nb + S - 1) / S) * ((c / kW64PerCu) * 1.35 + turn[c % kW64PerCu]) + ((c + kW64PerCu - 1) / kW64PerCu) * 6.0 + (S > 1 ? 4 + 0.22 * scratch : 0.0);
       if (S == 1 || us * (1 + margin) < best_us) { best = S; best_us = us * (1 + margin); }
     }
   } else {
@@ -1550,7 +1554,7 @@ constexpr int dh_pending(int c, int na, int ntot) {
 }
 
 template <int DH, int NW>
-__global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_wgt_dh_kernel(BwdArgs a) {
+__global__ __launch_bounds__(64 * NW, wgt_dh_per_cu(DH)) void bwd_wgt_dh_kernel(BwdArgs a) {
   constexpr int THREADS = 64 * NW;
   constexpr int KS = DH / 32;              // contraction steps of the 16x16x32 products over d_h
   constexpr int JB = DH / 16;              // 16-row output tiles over d_h
@@ -1828,7 +1832,7 @@ constexpr int w6_pending(int c) {
   return n;
 }
 
-__global__ __launch_bounds__(kW6Threads, 3) void bwd_wgt64_kernel(BwdArgs a) {
+__global__ __launch_bounds__(kW6Threads, kW64PerCu) void bwd_wgt64_kernel(BwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int cn = lane & 15, gq = lane >> 4;
@@ -2761,7 +2765,8 @@ int launch_wgt_dh(const Problem& p, BwdArgs a, hipStream_t stream) {
 }
 
 int launch_wgt64(const Problem& p, BwdArgs a, hipStream_t stream) {
-  static_assert(kW6Waves == wgt_waves(kW6Dh) && 3 * 256 == wgt_slots(kW6Dh), "plan_wgt_split assumes this launch shape");
+  static_assert(kW6Waves == 4 && kW6Waves == wgt_waves(kW6Dh) && kW64PerCu * kW6LdsBytes <= (int)kLdsBytesPerWorkgroup,
+                "plan_wgt_split assumes this launch shape");
   const int nblk = p.E * p.de / 16;
   const int wg_per_head = (nblk + kW6Waves - 1) / kW6Waves;
   const WgtSplit wsp = plan_wgt_split(p);
@@ -2911,7 +2916,7 @@ int launch_bwd(const Problem& p, int dtype, const void* X, const void* Wg, const
   if (rc) return rc;
   if (mark(1) != hipSuccess) return (int)hipErrorInvalidHandle;
   if (dWg || dWu || dWd) {
-    if (p.dh == 64 && p.ldx < ((int64_t)1 << 24) && p.ldy < ((int64_t)1 << 24)) rc = launch_wgt64(p, a, stream);
+    if (wgt64_takes(p)) rc = launch_wgt64(p, a, stream);
     else if (p.dh == 64) rc = launch_wgt_dh<64, 4>(p, a, stream);
     else if (p.dh == 256 && !wgt256_takes(p)) rc = launch_wgt_dh<256, 4>(p, a, stream);
     else rc = launch_wgt16(p, a, stream);   // d_h = 128 and 256

@@ -77,9 +77,9 @@ def small_workload(name, N, H, E, de, dtype, dh=128, w_std=0.05, route_scale=4.0
                            route_scale=route_scale, backward=backward)
 
 
-def launch_plan(op, N, H, E, de, dtype="bf16", dh=128, route_weights=False):
+def launch_plan(op, N, H, E, de, dtype="bf16", dh=128, route_weights=False, ld=(0, 0)):
     """What a call of this shape launches (mhffn_plan_text): kernels, tile shapes, shares."""
-    d = mhffn.Desc(N, H, dh, E, de, 0, 0, mhffn.BF16 if dtype == "bf16" else mhffn.F32,
+    d = mhffn.Desc(N, H, dh, E, de, ld[0], ld[1], mhffn.BF16 if dtype == "bf16" else mhffn.F32,
                    mhffn.ROUTE_WEIGHTS if route_weights else mhffn.ROUTE_PARAMS, 1e-6)
     text = ctypes.create_string_buffer(256)
     rc = mhffn.load().mhffn_plan_text(ctypes.byref(d), ctypes.c_int(op), text, ctypes.c_size_t(256))

@@ -25,6 +25,15 @@ def test_scratch_is_taken_for_a_gain_only(N, H, E, de, segs):
     test_plan(N, H, E, de, segs)
 
 
+@pytest.mark.parametrize("N,H,E,de,dense,wide", [(8000, 10, 8, 128, 3, 3), (5000, 16, 14, 192, 1, 3),
+                                                 (2013, 9, 12, 224, 2, 1), (20460, 6, 11, 160, 3, 3)])
+def test_generic_kernel_is_planned_with_its_own_occupancy(N, H, E, de, dense, wide):
+    """Row strides from 2^24 on take the kernel of which a CU holds two workgroups."""
+    test_plan(N, H, E, de, dense)
+    for ld in ((1 << 24, 0), (0, 1 << 24)):
+        assert "; wgt segs=%d;" % wide in launch_plan(mhffn.OP_BACKWARD, N, H, E, de, dh=64, ld=ld)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("N,H,E,de,segs", CASES)
 def test_weight_gradients(N, H, E, de, segs):
