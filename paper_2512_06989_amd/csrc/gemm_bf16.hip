@@ -457,7 +457,8 @@ int launch_skinny(const TunedGemmArgs& a, hipStream_t stream) {
 // 2048 7.3 | 6.3, 16 x 2048 x 2048 7.6 | 7.0; row form 1 x 2048 x 2048 0.7 less, 16 rows 0.2 more.
 // ---------------------------------------------------------------------------
 constexpr int kFewCols = 16, kFewTile = 1024;   // LDS of one product's transposed weights
-constexpr int kFewRowsTr = 16, kFewRows = 8;    // rows up to which it is the faster one, by the weights' form
+// rows up to which it is the faster one, by the weights' form
+bool few_takes(bool b_tr, int64_t M) { return M <= (b_tr ? 16 : 8); }
 template <bool B_TR>
 __global__ __launch_bounds__(64 * kSkinnyWaves) void gemm_bf16_few_kernel(TunedGemmArgs a) {
   constexpr int NW = kSkinnyWaves, SL = kSkinnySlices;
@@ -613,6 +614,10 @@ std::string gemm_bf16_plan(bool a_tr, int64_t M, int64_t N, int64_t K) {
          std::to_string(plan.splits);
 }
 
+int gemm_bf16_few_columns(bool b_tr, int64_t M, int64_t N, int64_t K) {
+  return !skinny_takes(M, N, K) ? 0 : few_takes(b_tr, M) ? kFewCols : kSkinnyCols;
+}
+
 size_t gemm_bf16_workspace_bytes(int64_t M, int64_t N, int64_t K) {
   const int s0 = plan_tiles(false, M, N, K).splits, s1 = plan_tiles(true, M, N, K).splits;
   const int splits = s0 > s1 ? s0 : s1;
@@ -635,7 +640,7 @@ int launch_gemm_bf16(bool a_tr, bool b_tr, const void* A, int64_t lda, const voi
   a.P = static_cast<float*>(ws);
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (!a_tr && skinny_takes(M, N, K) && !accumulate) {
-    if (M <= (b_tr ? kFewRowsTr : kFewRows)) return b_tr ? launch_few<true>(a, st) : launch_few<false>(a, st);
+    if (few_takes(b_tr, M)) return b_tr ? launch_few<true>(a, st) : launch_few<false>(a, st);
     return b_tr ? launch_skinny<true>(a, st) : launch_skinny<false>(a, st);
   }
   if (a.splits > 1 && !ws) return -1;

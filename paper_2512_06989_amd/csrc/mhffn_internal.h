@@ -124,6 +124,8 @@ std::string fwd_f32_plan(const Problem& p);
 std::string bwd_plan(const Problem& p, int dtype);
 std::string bwd_f32_plan(const Problem& p);
 std::string gemm_bf16_plan(bool a_tr, int64_t M, int64_t N, int64_t K);
+// columns of C per workgroup of the few-rows kernel that an unaccumulated product takes (0: none)
+int gemm_bf16_few_columns(bool b_tr, int64_t M, int64_t N, int64_t K);
 std::string module_plan(const Problem& p, int dtype, bool backward);
 
 }  // namespace mhffn

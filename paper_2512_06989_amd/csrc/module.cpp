@@ -65,7 +65,9 @@ std::string module_plan(const Problem& p, int dtype, bool backward) {
   const int64_t dm = (int64_t)p.H * p.dh;
   std::string s = "rows " + (dtype == 1 ? gemm_bf16_plan(false, p.N, dm, dm) : std::string("generic"));
   if (backward) s += "; weights " + (dtype == 1 ? gemm_bf16_plan(true, dm, dm, p.N) : std::string("generic"));
-  return s + "; " + (backward ? bwd_plan(inner(p), dtype) : dtype == 1 ? fwd_bf16_plan(inner(p)) : fwd_f32_plan(inner(p)));
+  s += "; " + (backward ? bwd_plan(inner(p), dtype) : dtype == 1 ? fwd_bf16_plan(inner(p)) : fwd_f32_plan(inner(p)));
+  const int columns = dtype == 1 ? gemm_bf16_few_columns(!backward, p.N, dm, dm) : 0;   // (backward: the weights' rows)
+  return columns ? s + "; few rows columns=" + std::to_string(columns) : s;
 }
 
 size_t module_workspace_bytes(const Problem& p, int dtype, bool backward) {

@@ -38,6 +38,12 @@ def test_backward(N, H, dh, E, de, route_weights, shares):
     for k in got:
         assert torch.equal(got[k], again[k]), k
     assert torch.equal(mhffn.backward(*a, g["dY"], w.eps, mode, want=("dX",))["dX"], got["dX"])
+    dm = H * dh
+    Xs, dXs = (torch.full((N, dm + 24), 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    dYs = torch.full((N, dm + 56), 7.0, dtype=torch.bfloat16, device="cuda")
+    Xs[:, :dm], dYs[:, :dm] = g["X"], g["dY"]
+    mhffn.backward(Xs[:, :dm], *a[1:], dYs[:, :dm], w.eps, mode, want=("dX",), out={"dX": dXs[:, :dm]})
+    assert torch.equal(dXs[:, :dm], got["dX"]) and torch.all(dXs[:, dm:] == 7.0)
     for h in (0, H - 1):                              # heads are independent
         c, hs = slice(h * dh, (h + 1) * dh), slice(h, h + 1)
         one = [d[k][hs] for k in ("W_gate", "W_up", "W_down")] + [d["R"][:, hs] if route_weights else d["W_r"][hs]]

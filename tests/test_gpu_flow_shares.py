@@ -6,7 +6,7 @@ the bf16 bar with the per-row bound on the heads at both ends, and run-to-run bi
 import pytest
 
 from oracle import mhffn_oracle as orc
-from paper_2512_06989_amd import mhffn
+from paper_2512_06989_amd import inputs, mhffn
 from tests.helpers import TOL, check_parity, device_inputs, launch_plan, small_workload, to_host
 from tests.test_gpu_forward import run_forward
 
@@ -71,3 +71,21 @@ def test_flow_forward(N, H, E, de, route_weights, plan):
     again = [mhffn.forward(g["X"], g["W_gate"], g["W_up"], g["W_down"], g[key], w.eps, mode) for _ in range(2)]
     assert torch.equal(again[0], again[1])
     assert (to_host(again[0]) == Y).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,H,E,de,route_weights,plan", [c for c in CASES if c[0] in (141, 1000, 2200, 4097)])
+def test_strided_rows(N, H, E, de, route_weights, plan):
+    """Rows of X and Y wider than d_model and than each other: whole blocks, halves beside whole
+    rounds, halves alone (all store Y themselves) and the sum over shares."""
+    import torch
+    w = small_workload("flow_strided", N, H, E, de, "bf16")
+    g = device_inputs(inputs.make_inputs(w, seed=N, with_dy=False, route_weights=route_weights), "bf16")
+    key, mode = ("R", mhffn.ROUTE_WEIGHTS) if route_weights else ("W_r", mhffn.ROUTE_PARAMS)
+    a, dm = [g[k] for k in ("W_gate", "W_up", "W_down", key)], w.d_model
+    want = mhffn.forward(g["X"], *a, w.eps, mode)
+    Xs = torch.full((N, dm + 40), float("nan"), dtype=torch.bfloat16, device="cuda")
+    Xs[:, :dm] = g["X"]
+    Ys = torch.full((N, dm + 72), 7.0, dtype=torch.bfloat16, device="cuda")
+    mhffn.forward(Xs[:, :dm], *a, w.eps, mode, out=Ys[:, :dm])
+    assert torch.equal(Ys[:, :dm], want) and torch.all(Ys[:, dm:] == 7.0)

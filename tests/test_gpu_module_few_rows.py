@@ -1,7 +1,7 @@
 """The module's projections of up to 16 rows (8 where the weights lie in row form): row counts at
 both limits and one beyond, contractions of one slice of 64 (15 of 16 waves have none), of an odd
 number of slices, and of two slices for every wave.  Stage by stage against the oracle; strided X
-and O through the C ABI give the bits of dense ones."""
+and O give the bits of dense ones."""
 import pytest
 
 from paper_2512_06989_amd import mhffn
@@ -14,6 +14,8 @@ CASES = [(1, 1, 64), (7, 3, 64), (8, 1, 128), (9, 9, 64), (15, 16, 128), (16, 2,
 @pytest.mark.parametrize("N,H,dh", CASES)
 def test_plan(N, H, dh):
     assert launch_plan(mhffn.OP_MODULE_BACKWARD, N, H, 2, 32, dh=dh).startswith("rows few rows;")
+    for op, rows in ((mhffn.OP_MODULE_FORWARD, 16), (mhffn.OP_MODULE_BACKWARD, 8)):
+        assert launch_plan(op, N, H, 2, 32, dh=dh).endswith("; few rows columns=%d" % (16 if N <= rows else 32))
 
 
 @pytest.mark.gpu
@@ -34,5 +36,7 @@ def test_strided_rows():
     want = mhffn.module_forward(X, Wi, *W, Wr, Wo, 1e-6)
     Xs = torch.full((11, wide), float("nan"), dtype=torch.bfloat16, device="cuda")
     Xs[:, :dm] = X
-    got = mhffn.module_forward(Xs[:, :dm], Wi, *W, Wr, Wo, 1e-6)
+    Os = torch.full((11, wide + 8), 7.0, dtype=torch.bfloat16, device="cuda")
+    got = mhffn.module_forward(Xs[:, :dm], Wi, *W, Wr, Wo, 1e-6, out={"O": Os[:, :dm]})
     assert all(torch.equal(a, b) for a, b in zip(got, want))
+    assert torch.equal(Os[:, :dm], want[0]) and torch.all(Os[:, dm:] == 7.0)

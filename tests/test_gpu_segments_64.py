@@ -1,6 +1,7 @@
 """Weight-major backward at d_h = 64: token segments per neuron group by what the fullest CU gets, from
-one to eight, with a shorter last segment and a ragged last block.  Weight gradients of the heads at
-both ends against the oracle, and run-to-run bit identity."""
+one to eight, with a shorter last segment and a ragged last block, for one group and for several
+heads with several groups (also with an idle pair of waves in a head's last one).  Weight gradients
+of the heads at both ends against the oracle, and run-to-run bit identity."""
 import pytest
 
 from oracle import mhffn_oracle as orc
@@ -9,7 +10,8 @@ from tests.helpers import TOL, check_parity, device_inputs, launch_plan, small_w
 
 WANT = ("dW_gate", "dW_up", "dW_down")
 CASES = [(363, 1, 1, 32, 1), (1013, 1, 1, 32, 2), (1840, 1, 1, 32, 3), (2139, 1, 1, 32, 4),
-         (2807, 1, 1, 32, 5), (3075, 1, 1, 32, 6), (3610, 1, 1, 32, 7), (4723, 1, 1, 32, 8)]
+         (2807, 1, 1, 32, 5), (3075, 1, 1, 32, 6), (3610, 1, 1, 32, 7), (4723, 1, 1, 32, 8),
+         (2000, 4, 8, 128, 3), (4000, 8, 8, 128, 4), (4000, 3, 5, 96, 7)]
 
 
 @pytest.mark.parametrize("N,H,E,de,segs", CASES)
@@ -46,7 +48,7 @@ def test_weight_gradients(N, H, E, de, segs):
     again = mhffn.backward(*a, w.eps, want=WANT)
     for k in WANT:
         assert torch.equal(got[k], again[k]), k
-    for h in (0, H - 1):                              # heads are independent
+    for h in sorted({0, H - 1}):                      # heads are independent
         c, hs = slice(h * 64, (h + 1) * 64), slice(h, h + 1)
         one = [d[k][hs] for k in ("W_gate", "W_up", "W_down", "W_r")]
         want = orc.backward(d["X"][:, c], *one, d["dY"][:, c], w.eps)
