@@ -121,9 +121,12 @@ typedef struct {
  * but its inputs and Y, which is the "intermediate never reaches HBM" property
  * of eq:flash-ffn-loop stated as a number.  For fewer tokens (decode, short
  * prefill) the blocks of eq:flash-ffn-loop are shared out over several
- * workgroups per token tile and their fp32 partial outputs, n_split * N *
- * d_model * 4 bytes (a few output-sized buffers, never d_ff-sized ones), pass
- * through the workspace; ask this function rather than relying on the rule.
+ * workgroups per token tile and their fp32 partial outputs (a few output-sized
+ * buffers, never d_ff-sized ones) pass through the workspace: with d_head = 128 and
+ * up to 64 sub-networks one partial output per share of the tiles that are shared
+ * out, ragged tiles padded, 32 MiB at most; with d_head = 64 and 256 an upper bound
+ * that does not depend on the shares that a launch takes, and is asked for where it
+ * takes none as well.  Ask this function rather than relying on the rule.
  * In fp32 it depends on how evenly blocks of 64 tokens load the chip (not 0 for many large
  * inputs either), and it is optional: without it (or with less) the shares of a token block
  * run one after the other, which is slower and gives the same result (mhffn_module_forward

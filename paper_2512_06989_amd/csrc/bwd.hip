@@ -1443,7 +1443,8 @@ WgtSplit plan_wgt_split(const Problem& p) {
     // partials) and 0.5 % for every 100 MiB that the caller has to hold, a quarter at most.  Refused:
     // 8575 groups, 972 blocks 14590 | 14649 (two, 804 MiB, modelled gain 0.3 %), whole backwards of
     // 1788 groups, 879 blocks 5088 | 5083 (two, 167 MiB, 2.6 %); taken: 1088 groups, 217 blocks 856 |
-    // 838 (two, 102 MiB, 2.9 %), 2100 groups, 848 blocks 5983 | 5825 (four, 394 MiB, 4.3 %; two now).
+    // 838 (two, 102 MiB, 2.9 %), 2100 groups, 848 blocks two (197 MiB, 3.6 %), which come within 0.5 % of
+    // the four (394 MiB, 4.3 %) that take 5825 instead of 5983.
     const double mib = 3.0 * p.H * p.E * p.de * p.dh * sizeof(float) / (1 << 20), turn[kW64PerCu] = {0, 0.6, 0.9};
     double best_us = 0;
     for (int S = 1; S <= 8 && (S == 1 || nb / S >= 16); ++S) {

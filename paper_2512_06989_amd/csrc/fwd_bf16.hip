@@ -1555,12 +1555,15 @@ int shares_256(const Problem& p, bool pair, int64_t base, int T) {
 // The time is modelled from measurements (us): a step of 32 neurons takes 0.95 (half a block: 0.62)
 // on a CU, but the chip under its power limit takes no more than 197 (338) of them per us;
 // 11.4 (10.8) around a workgroup's steps; the partials 0.46 per MiB, written and read, and 1.
-// Where the two bounds meet, a tenth more than either.  Whole | this list, forward calls, E d_e / 32
-// tiles, us: 384 blocks, 64 tiles 165 | 153 (128 blocks in halves); 128 blocks, 32 tiles 42 | 33 and
-// 64 blocks 41 | 30 (halves; 36 in four shares); 96 blocks, 264 tiles 259 | 160 in two shares; 32 blocks
-// (300 tokens), 32 tiles 41 | 21 (halves in four shares; 27 whole in eight).  Partials of at most
-// 32 MiB: the interface promises it, and callers hold workspaces of that size (what it costs: the 96
-// blocks would take 151 in shares of 109, 109 and 46, which leave 36 MiB).
+// Where the two bounds meet, a tenth more than either.  (Ends and partials as they were before rows
+// moved whole; 8 and 7.4 choose another plan for 11 of 152 random calls, 0.33 per MiB beside them for 29, and those
+// calls take 0.2 and 1.2 % longer: the constants also stand for what the model leaves out.)  Whole |
+// this list, forward calls, E d_e / 32 tiles, us: 384 blocks, 64 tiles 160 | 147 (128 blocks in
+// halves); 128 blocks, 32 tiles 39 | 31 and 64 blocks 38 | 27.5 (halves; 39 in four shares); 96 blocks,
+// 264 tiles 259 | 160 in two shares; 32 blocks (300 tokens), 32 tiles 38 | 19 (halves in four shares; 29
+// whole in eight).  Partials of at most 32 MiB: the interface promises it, and callers hold workspaces
+// of that size (what it costs: the 96 blocks would take 151 in shares of 109, 109 and 46, which leave
+// 36 MiB).
 constexpr uint32_t kFlowScratch = 32u << 20;
 FlowShares flow_shares(const Problem& p) {
   const uint32_t T = (uint32_t)(p.E * (p.de / kBI)), slots = 256;
@@ -1620,9 +1623,10 @@ int shares_two_per_cu(int64_t base, int64_t T) {
 // Shares per block of 256 tokens at d_h = 64, where the plan above takes any.  A CU holds two
 // workgroups: a tile takes one 0.88 us, two 1.62, and c workgroups on the fullest CU c / 2 rounds of
 // that; 10 around the tiles, the partials (written and read) 0.2 per MiB, the second launch 3.  Plan
-// of two workgroups per CU | this one, us: 256 blocks, 40 tiles 57.2 | 45.8 (whole); 192 blocks, 320
-// tiles 292 | 238 (four shares, not three); 64 blocks, 84 tiles 39.3 | 37.4 (four, not eight); 320
-// blocks, 84 tiles 130 | 125 (three, not two).  No more scratch than that plan's or the static buffer's.
+// of two workgroups per CU | this one, us: 256 blocks, 40 tiles 54.5 | 45.6 (whole); 192 blocks, 320
+// tiles 284 | 266 (two shares, not three); 64 blocks, 84 tiles 40.0 | 37.2 (four, not eight).  No more
+// scratch than that plan's or the static buffer's, which costs the 192 blocks their four shares (234, 48
+// MiB) and 320 blocks of 84 tiles three (121 and 59 MiB, 126 in two).
 int shares_64(const Problem& p, int64_t base, int64_t T) {
   const int asked = shares_two_per_cu(base, T);
   if (asked == 1) return 1;

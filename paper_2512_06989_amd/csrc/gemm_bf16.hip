@@ -578,15 +578,16 @@ int launch_form(const TunedGemmArgs& a, int shape, hipStream_t stream) {
 
 }  // namespace
 
-// Where the few-rows kernel is the faster one: a round of its workgroups (one per CU) takes
-// about 520 clocks per 64-wide slice of k and 2000 around them.  It is chosen for up to 512 rows
-// at d_model = 1024, 160 at 1536, 128 at 2048, 45 .. 96 at 2560 and not at all from 3072 on.
+// Where a few-rows kernel is the faster one: a round of the 32-column kernel's workgroups (one per
+// CU) takes about 520 clocks per 64-wide slice of k and 2000 around them.  It is chosen for up to 512
+// rows at d_model = 1024, 160 at 1536, 128 at 2048, 45 .. 96 at 2560 and not at all from 3072 on.
 // Microseconds, few rows | tiled with its sum: d_model = 1024, 128 rows 5.0 | 9.1, 512 9.1 | 10.1,
-// 513 11.5 | 10.0; 1536, 160 rows 6.5 | 13.0; 2048, 1 row 7.1 | 8.6, 128 8.7 | 15.1, 320 18.8 |
-// 15.5; 2560, 1 row 10.0 | 9.4, 64 10.7 | 12.9, 128 16.9 | 14.6; 3072, 1 row 10.7 | 9.8; 5120, 1
-// row 20.6 | 14.9.  The tiled kernel gets some sizes too early: 2048, 129 .. 256 rows 12.4 ..
-// 13.8 | 14.6 .. 15.2; 1536, 192 .. 320 rows 10.0 .. 11.2 | 13.7 .. 14.8; 3072 and 4096, 64 rows
-// 12.6 | 14.7 and 15.2 | 17.1.
+// 513 11.5 | 10.0; 1536, 160 rows 6.5 | 13.0; 2048, 128 rows 8.7 | 15.1, 320 18.8 | 15.5; 2560, 64 rows
+// 10.7 | 12.9, 128 16.9 | 14.6.  The tiled kernel gets some sizes too early: 2048, 129 .. 256 rows
+// 12.4 .. 13.8 | 14.6 .. 15.2; 1536, 192 .. 320 rows 10.0 .. 11.2 | 13.7 .. 14.8; 3072 and 4096, 64 rows
+// 12.6 | 14.7 and 15.2 | 17.1.  For 1 .. 16 rows the 16-column kernel lies on the same side of the
+// tiled one: 2.7 .. 3.1 us less a product at 512, 3.4 .. 3.8 at 1024, 2.5 .. 2.9 at 2048; 1.1 .. 1.6
+// more at 2560, 2.4 .. 2.9 at 3072, 2.0 .. 4.0 at 4096, 23 .. 28 at 5120.
 bool skinny_takes(int64_t M, int64_t N, int64_t K) {
   if (N % kSkinnyCols != 0 || K % kSkinnyK != 0) return false;
   const int64_t wgs = ((M + kSkinnyRows - 1) / kSkinnyRows) * (N / kSkinnyCols);
