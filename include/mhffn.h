@@ -134,9 +134,10 @@ typedef struct {
  * their gradient as [H][E][N] fp32, the partial sums of dW_r, and, for the
  * neuron groups that would otherwise leave CUs idle in the last round of
  * workgroups, fp32 partial weight gradients of a few token segments (a multiple
- * of the parameter count, not of the token count), or, for few tokens, partial
- * dX of the workgroups that share a token block's sub-networks (a few dX-sized
- * fp32 buffers), whichever is larger; all summed in a fixed order: results are
+ * of the parameter count, not of the token count), or, for the token blocks behind
+ * the last whole round of workgroups (all of few tokens), partial dX of the
+ * workgroups that share a block's sub-networks (a few fp32 buffers of those blocks'
+ * size), whichever is larger; all summed in a fixed order: results are
  * bit-identical from run to run.  For the unfused ops it is the three
  * materialised [N][H][d_ff] activations plus the [N][H][E] weights, i.e. the
  * O((L*H + d_model)*d_ff) footprint of the naive multi-head FFN. */
