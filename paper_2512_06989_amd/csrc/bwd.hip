@@ -953,17 +953,19 @@ __global__ __launch_bounds__(64 * NW, DH == 64 ? 2 : 1) void bwd_tok_kernel(BwdA
     for (int tb = 0; tb < TB; ++tb) {
       for (int ks = 0; ks < 2 * EB; ++ks) {
         if (16 * ks >= E) break;
-        // dp as the sum of two bf16 operands: what one rounding leaves goes into the second product, so
-        // that dX does not depend on whether its block was shared out (there dp stays in fp32)
+        // dp as the sum of two bf16 operands, so that dX does not depend on whether its block was shared
+        // out (there dp stays in fp32).  The first is cut off, not rounded, and where nothing is left the
+        // second is 2^-24 of it: both have dp's sign, or an infinite weight would give NaN and not infinity.
         u32x4 pk, lo;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int e0 = 16 * ks + 8 * g + 2 * i;
           const float d0 = (e0 < E) ? DRs[e0 * BM + wtok + 32 * tb + r] : 0.f;
           const float d1 = (e0 + 1 < E) ? DRs[(e0 + 1) * BM + wtok + 32 * tb + r] : 0.f;
-          pk[i] = pack_bf16(d0, d1);
-          const float h0 = bf16_bits_to_f32((uint16_t)pk[i]), h1 = bf16_bits_to_f32((uint16_t)(pk[i] >> 16));
-          lo[i] = pack_bf16(fabsf(h0) < INFINITY ? d0 - h0 : 0.f, fabsf(h1) < INFINITY ? d1 - h1 : 0.f);
+          const uint32_t u0 = __builtin_bit_cast(uint32_t, d0), u1 = __builtin_bit_cast(uint32_t, d1) & 0xFFFF0000u;
+          pk[i] = (u0 >> 16) | u1;
+          const float l0 = d0 - __builtin_bit_cast(float, u0 & 0xFFFF0000u), l1 = d1 - __builtin_bit_cast(float, u1);
+          lo[i] = pack_bf16(fabsf(l0) > 0.f ? l0 : d0 * 0x1p-24f, fabsf(l1) > 0.f ? l1 : d1 * 0x1p-24f);
         }
         const bf16x8 bp = __builtin_bit_cast(bf16x8, pk), bl = __builtin_bit_cast(bf16x8, lo);
         u32x4 in;   // columns that exist (the others hold whatever the memory held)

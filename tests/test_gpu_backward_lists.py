@@ -51,3 +51,28 @@ def test_backward(N, H, dh, E, de, route_weights, shares):
         part = {k: to_host(v) for k, v in got.items()}
         part = {k: v[:, c] if k == "dX" else v[:, hs] if k == "d_route" and route_weights else v[hs] for k, v in part.items()}
         check_parity(part, want, TOL["bf16"], dh, "lists, head %d" % h, route_weights)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,H,dh,E,de,route_weights,shares", [c for c in CASES if not c[5]])
+def test_infinite_gating_weight(N, H, dh, E, de, route_weights, shares):
+    """An infinite element of W_r: its column of dX is dp (which the workspace holds) times infinity, of the
+    same kind in whole blocks, where dp is an operand of two products, and in shared ones."""
+    import torch
+    w = small_workload("lists_inf", N, H, E, de, "bf16", dh=dh, backward=True)
+    g = device_inputs(inputs.make_inputs(w, seed=N, with_dy=True), "bf16")
+    col, sub = 5, E - 1
+    g["W_r"][:, col, sub] = float("inf")
+    a = [g[k] for k in ("X", "W_gate", "W_up", "W_down", "W_r")]
+    need = mhffn.workspace_bytes(mhffn.make_desc(a[0], a[1], mhffn.ROUTE_PARAMS, w.eps), mhffn.OP_BACKWARD)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    dX = mhffn.backward(*a, g["dY"], w.eps, want=("dX",), workspace=ws)["dX"].float().view(N, H, dh)
+    at = (4 * H * E * N + 255) // 256 * 256          # R, then dp, both [H][E][N] fp32
+    dp = ws[at:at + 4 * H * E * N].view(torch.float32).view(H, E, N)
+    want = (dp[:, sub] * float("inf")).t()           # [N][H]: no sign and no NaN comes from elsewhere
+    got = dX[:, :, col]
+    assert int(torch.isinf(want).sum()) > want.numel() // 20
+    assert torch.equal(torch.isnan(got), torch.isnan(want))
+    assert torch.equal(got[~torch.isnan(got)], want[~torch.isnan(want)])
+    rest = torch.cat([dX[:, :, :col], dX[:, :, col + 1:]], 2)
+    assert torch.equal(torch.isfinite(rest).all(dim=2), torch.isfinite(dp).all(dim=1).t())
