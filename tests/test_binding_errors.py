@@ -1,6 +1,7 @@
 """Errors raised inside the native binding are Python exceptions of the type torch gives them: a
 training loop catches torch.OutOfMemoryError to go on with a smaller batch, and tensors without
 memory of their own (those of torch.func) are refused with torch's own message."""
+import gc
 import subprocess
 import sys
 
@@ -96,6 +97,7 @@ def test_tensors_without_memory_are_refused():
 def test_out_of_memory_on_the_gpu(call):
     fn = _calls(1 << 19, 2, 2, 32, 128, "cuda")[call]     # every output of N rows: 256 MiB
     torch.cuda.synchronize()
+    gc.collect()   # (an exception kept by pytest.raises is a cycle: the case before would free its tensors at any time)
     torch.cuda.empty_cache()
     total = torch.cuda.get_device_properties(0).total_memory
     torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (64 << 20)) / total)
